@@ -1,0 +1,649 @@
+"""The performance cases of the Hartree-Fock hot path on one GPU.
+
+listed() and draw() name work that a program does through the public entry
+points: direct, stored and single-precision J/K builds, the dense integral
+tensor and its contraction with many densities, exchange-correlation builds,
+nuclear gradients, the learned guess's training gradient, and two whole
+calls (one SCF from the geometry to convergence, one batched SCF).  The
+molecules are synthetic: water clusters, and small molecules of H, C, N and
+O, with contracted s, p and d shells whose exponents and coefficients are
+drawn once (a program keeps its basis set), while geometries and densities
+come from the seed.  prepare() makes what a program holds before the call,
+run() makes one pass, work() counts what a pass cannot do without, exact()
+evaluates the same quantities with torch in 64 bits by Hermite-Gaussian
+expansion, a method of its own.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2406_03121_amd import mess
+
+ELEMENT = {"H": (1, (0, 0)), "C": (6, (0, 0, 1)), "N": (7, (0, 0, 1)), "O": (8, (0, 0, 1, 2))}
+NCART = (1, 3, 6)
+POWERS = (((0, 0, 0),), ((1, 0, 0), (0, 1, 0), (0, 0, 1)),
+          ((2, 0, 0), (1, 1, 0), (1, 0, 1), (0, 2, 0), (0, 1, 1), (0, 0, 2)))
+F64 = torch.float64
+
+
+# ------------------------------------------------------------------ the cases
+
+def listed():
+    return [
+        # one Fock build of a six-atom s/p molecule, nothing screened: launches and latency
+        {"name": "jk small", "kind": "jk", "system": "sp", "size": 6, "tau": 0.0, "mode": "direct", "prec": 64},
+        # the Fock build of a 60-atom cluster (300 functions, s to d), recomputing its integrals
+        {"name": "jk direct", "kind": "jk", "system": "water", "size": 20, "tau": 1e-10, "mode": "direct", "prec": 64},
+        # a single-precision build of an odd-sized cluster, as mixed-precision iterations use it
+        {"name": "jk single", "kind": "jk", "system": "water", "size": 13, "tau": 1e-10, "mode": "direct", "prec": 32},
+        # a later Fock build of the 60-atom cluster, from the integrals kept in device memory
+        {"name": "jk stored", "kind": "jk", "system": "water", "size": 20, "tau": 1e-10, "mode": "stored", "prec": 64},
+        # the whole integral tensor of a small molecule
+        {"name": "eri tensor", "kind": "eri", "system": "water", "size": 3, "prec": 64},
+        # J and K of many densities (response vectors, ensembles) from a dense tensor
+        {"name": "dense jk", "kind": "dense", "n": 105, "dens": 64, "prec": 64},
+        # local-density exchange of the 60-atom cluster on its grid
+        {"name": "lda", "kind": "lda", "system": "water", "size": 20},
+        # gradient-corrected exchange-correlation of a 21-atom cluster
+        {"name": "pbe", "kind": "pbe", "system": "water", "size": 7},
+        # the forces on a small cluster, for a geometry step
+        {"name": "gradient", "kind": "grad", "system": "water", "size": 3, "tau": 1e-10},
+        # the training gradient of the learned guess on one mini-batch
+        {"name": "guess gradient", "kind": "mlp", "rows": 4096},
+        # whole call: geometry to converged energy and density, 60 atoms
+        {"name": "scf", "kind": "scf", "system": "water", "size": 20, "tau": 1e-10},
+        # whole call: the first iterations of many small molecules at once
+        {"name": "batched scf", "kind": "batch", "molecules": 64, "steps": 6, "tau": 1e-10},
+    ]
+
+
+def draw(rng):
+    def log_int(lo, hi):
+        return min(hi, max(lo, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+    tau = rng.choice((1e-10, 1e-9, 1e-12))
+    kind = rng.choice(("jk", "jk", "jk", "jk", "eri", "dense", "lda", "pbe", "grad", "mlp", "scf", "batch"))
+    if kind == "jk":
+        if rng.random() < 0.25:
+            return {"kind": "jk", "system": "sp", "size": rng.randint(2, 16), "tau": rng.choice((0.0, 1e-12)),
+                    "mode": rng.choice(("direct", "stored")), "prec": rng.choice((64, 64, 32))}
+        return {"kind": "jk", "system": "water", "size": log_int(1, 19), "tau": tau,
+                "mode": rng.choice(("direct", "direct", "stored")), "prec": rng.choice((64, 64, 32))}
+    if kind == "eri":
+        if rng.random() < 0.5:
+            return {"kind": "eri", "system": "sp", "size": rng.randint(2, 8), "prec": rng.choice((64, 64, 32))}
+        return {"kind": "eri", "system": "water", "size": rng.randint(1, 3), "prec": 32}
+    if kind == "dense":
+        return {"kind": "dense", "n": rng.randint(17, 104), "dens": log_int(1, 64), "prec": rng.choice((64, 32))}
+    if kind == "lda":
+        return {"kind": "lda", "system": "water", "size": log_int(1, 19)}
+    if kind == "pbe":
+        return {"kind": "pbe", "system": "water", "size": rng.randint(1, 6)}
+    if kind == "grad":
+        if rng.random() < 0.5:
+            return {"kind": "grad", "system": "sp", "size": rng.randint(2, 6), "tau": tau}
+        return {"kind": "grad", "system": "water", "size": rng.randint(1, 3), "tau": rng.choice((1e-9, 1e-12))}
+    if kind == "mlp":
+        return {"kind": "mlp", "rows": log_int(40, 20000)}
+    if kind == "scf":
+        return {"kind": "scf", "system": "water", "size": rng.randint(2, 19), "tau": tau}
+    return {"kind": "batch", "molecules": log_int(4, 60), "steps": rng.randint(2, 6), "tau": tau}
+
+
+# ------------------------------------------------------------------ molecules
+
+def _separated(rng, n, box, least):
+    """n points of a cube, no two nearer than least."""
+    while True:
+        pts = []
+        for _ in range(20000):
+            p = rng.uniform(0.0, box, 3)
+            if all(np.sum((p - q) ** 2) >= least * least for q in pts):
+                pts.append(p)
+                if len(pts) == n:
+                    return np.array(pts)
+
+
+def _shell(rng, l, nprim, lo, hi):
+    return l, np.exp(rng.uniform(math.log(lo), math.log(hi), nprim)), 1.0 - rng.random(nprim)
+
+
+class Molecule:
+    """Atoms and contracted shells as the arrays that mess_basis_create and mess_batch_create take."""
+
+    def __init__(self, Z, xyz, shells, charge=0):
+        self.Z, self.xyz, self.charge = np.array(Z, np.int32), np.array(xyz, np.float64), charge
+        self.shells = shells  # (atom, l, exponents, coefficients)
+        self.shell_atom = np.array([s[0] for s in shells], np.int32)
+        self.shell_l = np.array([s[1] for s in shells], np.int32)
+        self.shell_nprim = np.array([len(s[2]) for s in shells], np.int32)
+        self.exps = np.concatenate([s[2] for s in shells])
+        self.coefs = np.concatenate([s[3] for s in shells])
+        self.n_bf = int(sum(NCART[l] for l in self.shell_l))
+        self.n_occ = (int(self.Z.sum()) - charge) // 2
+
+
+def water_cluster(n, seed):
+    """n waters in a cube at the density of 20 in 18 bohr; 3 to 6 primitives a shell, exponents 0.05 to 5000."""
+    rng, basis = np.random.default_rng([1, n, seed]), np.random.default_rng(11)
+    half = math.radians(104.5) / 2
+    local = 1.81 * np.array([[0, 0, 0], [math.sin(half), math.cos(half), 0], [-math.sin(half), math.cos(half), 0]])
+    box, mols = max(18.0 * (n / 20) ** (1 / 3), 0.1), []
+    while len(mols) < n:
+        mols = []
+        for _ in range(20000):
+            q, r = np.linalg.qr(rng.normal(size=(3, 3)))
+            atoms = rng.uniform(0.0, box, 3) + local @ (q * np.sign(np.diag(r))).T
+            if all(np.linalg.norm(m[0] - atoms[0]) >= 5.0 and
+                   np.linalg.norm(m[:, None] - atoms[None], axis=-1).min() >= 1.8 for m in mols):
+                mols.append(atoms)
+                if len(mols) == n:
+                    break
+    shells = []
+    for a in range(3 * n):
+        for l in ELEMENT["O" if a % 3 == 0 else "H"][1]:
+            shells.append((a,) + _shell(basis, l, int(basis.integers(3, 7)), 0.05, 5000.0))
+    return Molecule([8, 1, 1] * n, np.concatenate(mols), shells)
+
+
+def sp_molecule(n, seed):
+    """n atoms of H, C and O with two s shells and a p shell of 3 primitives each, exponents 0.1 to 50."""
+    rng, basis = np.random.default_rng([2, n, seed]), np.random.default_rng(12)
+    Z = [(6, 1, 8, 1, 6, 8)[a % 6] for a in range(n)]
+    shells = [(a,) + _shell(basis, l, 3, 0.1, 50.0) for a in range(n) for l in (0, 0, 1)]
+    return Molecule(Z, _separated(rng, n, 6.0 * (n / 6) ** (1 / 3), 1.8), shells, charge=sum(Z) % 2)
+
+
+def small_molecules(count, seed):
+    """Molecules of 3 to 20 atoms of H, C, N and O with one basis per element; 10 to 120 functions, closed shells."""
+    rng, made = np.random.default_rng([3, count, seed]), np.random.default_rng(13)
+    basis = {e: [_shell(made, l, int(made.integers(3, 7)), 0.05, 5000.0) for l in ELEMENT[e][1]] for e in "HCNO"}
+    out = []
+    while len(out) < count:
+        n = int(made.integers(3, 21))
+        atoms = list(made.choice(list("HCNO"), n))
+        nbf = sum(NCART[l] for e in atoms for l in ELEMENT[e][1])
+        if sum(ELEMENT[e][0] for e in atoms) % 2 or not 10 <= nbf <= 120:
+            continue
+        xyz = _separated(rng, n, 6.0 * (n / 6) ** (1 / 3), 1.8)
+        out.append(Molecule([ELEMENT[e][0] for e in atoms], xyz,
+                            [(a,) + s for a, e in enumerate(atoms) for s in basis[e]]))
+    return out
+
+
+def molecule(case, seed):
+    return (water_cluster if case["system"] == "water" else sp_molecule)(case["size"], seed)
+
+
+def occupied_density(mol, seed):
+    """2 C C^T of n_occ orthonormal random columns: the shape of a closed-shell density."""
+    g = torch.Generator("cuda").manual_seed(seed)
+    q = torch.linalg.qr(torch.randn(mol.n_bf, mol.n_occ, dtype=F64, device="cuda", generator=g))[0]
+    D = 2.0 * q @ q.T
+    return (0.5 * (D + D.T)).contiguous()
+
+
+def zeros(*shape, dtype=F64):
+    return torch.zeros(*shape, dtype=dtype, device="cuda")
+
+
+def _prec(case):
+    return mess.MESS_FP64 if case["prec"] == 64 else mess.MESS_FP32
+
+
+def _dense_inputs(case, seed):
+    """A tensor with the symmetries and decay of repulsion integrals, and symmetric densities."""
+    g = torch.Generator("cuda").manual_seed(seed)
+    n, rank = case["n"], 8
+    L = torch.randn(rank, n, n, dtype=F64, device="cuda", generator=g)
+    L = (L + L.transpose(1, 2)).reshape(rank, n * n) * torch.logspace(0, -3, rank, dtype=F64, device="cuda")[:, None]
+    D = torch.randn(case["dens"], n, n, dtype=F64, device="cuda", generator=g)
+    real = torch.float64 if case["prec"] == 64 else torch.float32
+    return (L.T.contiguous() @ L).to(real).reshape(-1), (D + D.transpose(1, 2)).to(real).contiguous()
+
+
+def _mlp_inputs(case, seed):
+    """Initial parameters, features like those of atom pairs (one-hots, Gaussians of a distance, a unit vector and
+    its products, neighbour counts, a flag; 42 of 64 used), target blocks of a density and the mask of present ones."""
+    rng, n = np.random.default_rng([4, seed]), case["rows"]
+    params = []
+    for o, i in ((256, 64), (256, 256), (128, 256)):
+        lim = math.sqrt(6.0 / (i + o))
+        params += [rng.uniform(-lim, lim, o * i), np.zeros(o)]
+    g = torch.Generator("cuda").manual_seed(seed)
+    rand = lambda *s: torch.rand(*s, device="cuda", generator=g)  # noqa: E731
+    X, r = zeros(n, 64, dtype=torch.float32), 1.8 + 8.0 * rand(n, 1)
+    for base in (0, 4):
+        X[torch.arange(n, device="cuda"), base + (4 * rand(n)).long().clamp(max=3)] = 1.0
+    X[:, 8:24] = torch.exp(-((r - torch.arange(16, device="cuda") * 2 / 3) * 1.5) ** 2)
+    u = torch.nn.functional.normalize(rand(n, 3) - 0.5, dim=1)
+    X[:, 24:27] = u
+    X[:, 27:33] = torch.stack([u[:, a] * u[:, b] for a in range(3) for b in range(a, 3)], 1)
+    X[:, 33:41] = 3.0 * rand(n, 8)
+    self_pair = rand(n) < 0.1
+    X[self_pair, 8:33] = 0.0
+    X[:, 41] = self_pair.float()
+    T = 0.5 * torch.randn(n, 128, device="cuda", generator=g) * torch.exp(-0.3 * r)
+    na, nb = ((torch.tensor([2, 5, 5, 11], device="cuda")[X[:, b:b + 4].argmax(1)])[:, None] for b in (0, 4))
+    k = torch.arange(128, device="cuda")[None]
+    M = ((k < 121) & (k // 11 < na) & (k % 11 < nb)).float()
+    return np.concatenate([p.ravel() for p in params]).astype(np.float32), X, (T * M).contiguous(), M.contiguous()
+
+
+# ------------------------------------------------------------- prepare and run
+
+def prepare(case, seed):
+    kind, s = case["kind"], {"case": case}
+    if kind == "dense":
+        s["eri"], s["D"] = _dense_inputs(case, seed)
+        s["J"], s["K"] = torch.zeros_like(s["D"]), torch.zeros_like(s["D"])
+        return s
+    if kind == "mlp":
+        params, s["X"], s["T"], s["M"] = _mlp_inputs(case, seed)
+        s["mlp"] = mess.Mlp(params)
+        s["grad"] = zeros(mess.MESS_MLP_NPARAM, dtype=torch.float32)
+        return s
+    if kind == "batch":
+        s["mols"] = small_molecules(case["molecules"], seed)
+        return s
+    s["mol"] = mol = molecule(case, seed)
+    N = mol.n_bf
+    if kind == "scf":
+        return s
+    s["basis"] = B = mess.basis_from_molecule(mol)
+    if kind == "eri":
+        s["out"] = zeros(N, N, N, N)
+        return s
+    s["D"] = occupied_density(mol, seed)
+    if kind == "jk":
+        s["J"], s["K"] = zeros(N, N), zeros(N, N)
+        if case["mode"] == "stored":  # the first build of an SCF computes the blocks that later ones stream
+            _jk(s)
+    elif kind == "grad":
+        g = torch.Generator("cuda").manual_seed(seed + 1)
+        F = torch.randn(N, N, dtype=F64, device="cuda", generator=g)
+        s["F"] = (F + F.T).contiguous()
+    else:
+        s["V"], s["rho"] = zeros(N, N), zeros(mess.mess_grid(B))
+        if kind == "pbe":
+            s["grad_rho"] = zeros(3, s["rho"].numel())
+        run(s)  # the grid and the basis values on it stay with the basis
+    return s
+
+
+def _jk(s):
+    mess.mess_jk(s["basis"], s["D"], s["J"], s["K"], prec=_prec(s["case"]), schwarz_tol=s["case"]["tau"],
+                 mode=mess.MESS_JK_STORED if s["case"]["mode"] == "stored" else mess.MESS_JK_DIRECT)
+
+
+def run(s):
+    case = s["case"]
+    kind = case["kind"]
+    if kind == "jk":
+        _jk(s)
+        return {"J": s["J"], "K": s["K"]}
+    if kind == "eri":
+        mess.mess_eri(s["basis"], s["out"], prec=_prec(case))
+        return s["out"]
+    if kind == "dense":
+        mess.mess_jk_dense(s["eri"], case["n"], s["D"], s["J"], s["K"], prec=_prec(case))
+        return {"J": s["J"], "K": s["K"]}
+    if kind == "lda":
+        return {"E": mess.mess_lda_x(s["basis"], s["D"], s["V"], s["rho"]), "V": s["V"], "rho": s["rho"]}
+    if kind == "pbe":
+        E = mess.mess_pbe_xc(s["basis"], s["D"], s["V"], s["rho"], s["grad_rho"])
+        return {"E": E, "V": s["V"], "rho": s["rho"], "grad_rho": s["grad_rho"]}
+    if kind == "grad":
+        return mess.mess_hf_gradient(s["basis"], s["D"], s["F"], schwarz_tol=case["tau"])
+    if kind == "mlp":
+        return {"loss": s["mlp"].grad(s["X"], s["T"], s["M"], s["grad"]), "grad": s["grad"]}
+    if kind == "scf":
+        B = mess.basis_from_molecule(s["mol"])
+        scf = mess.mess_scf_create(B, schwarz_tol=case["tau"], conv_tol=1e-8)
+        for _ in range(30):
+            energy, _, _, converged = mess.mess_scf_step(scf)
+            if converged:
+                break
+        D, F = zeros(B.nbf, B.nbf), zeros(B.nbf, B.nbf)
+        mess.mess_scf_density(scf, D)
+        mess.mess_scf_fock(scf, F)
+        scf.close()
+        B.close()
+        return {"energy": energy, "D": D, "F": F}
+    B = mess.mess_batch_create(s["mols"])
+    scf = mess.mess_batch_scf_create(B, schwarz_tol=case["tau"], use_graph=True)
+    for _ in range(case["steps"]):
+        mess.mess_batch_scf_step(scf)
+    status = mess.mess_batch_scf_status(scf)
+    D = zeros(B.packed)
+    mess.mess_batch_scf_density(scf, D)
+    scf.close()
+    B.close()
+    return {"energy": status["energy"], "D": D}
+
+
+# ------------------------------------------------------------------------ work
+
+def _eri_ops(basis, tau):
+    """Operations of the recursion (vertical, contracted, horizontal, digestion) over the surviving unique quartets."""
+    return sum(mess.mess_work_stats(basis, tau, c)[2] for c in range(21))
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "dense":
+        n, size = case["n"], case["prec"] // 8
+        return {"bytes": size * (n ** 4 + 3 * case["dens"] * n * n), "flops": 4.0 * case["dens"] * n ** 4}
+    if kind == "mlp":  # forward and backward: three products of each layer, two of the first
+        n = case["rows"]
+        return {"bytes": 4.0 * (n * (42 + 128 + 128) + 2 * mess.MESS_MLP_NPARAM),
+                "flops": 2.0 * n * (2 * 64 * 256 + 3 * 256 * 256 + 3 * 256 * 128)}
+    if kind == "batch":
+        B = mess.mess_batch_create(small_molecules(case["molecules"], 0))
+        ops, elements = _eri_ops(B, case["tau"]), float(B.packed)
+        B.close()
+        return {"bytes": 8.0 * 3 * case["steps"] * elements, "flops": case["steps"] * ops}
+    mol = molecule(case, 0)
+    N = mol.n_bf
+    if kind in ("lda", "pbe"):  # D phi and phi f phi^T (the latter symmetric for the local part), values and gradients
+        points = 43350.0 * 3 * case["size"]
+        planes = 1 if kind == "lda" else 4
+        return {"bytes": 8.0 * points * (planes * N + planes), "flops": points * (4.0 if kind == "lda" else 4.0 + 12.0 / N) * N * N}
+    B = mess.basis_from_molecule(mol)
+    ops = _eri_ops(B, case.get("tau", 0.0))
+    quartets = [mess.mess_work_stats(B, case.get("tau", 0.0), c)[0] for c in range(21)]
+    B.close()
+    if kind == "eri":
+        return {"bytes": 8.0 * N ** 4, "flops": ops}
+    if kind == "scf":  # five builds at the least
+        return {"bytes": 8.0 * 5 * 3 * N * N, "flops": 5 * ops}
+    if kind == "grad":  # three centres of a quartet, one order higher
+        return {"bytes": 8.0 * 2 * N * N, "flops": 3 * ops}
+    if case["mode"] == "stored":
+        pair = [a * b for a, b in ((1, 1), (3, 1), (3, 3), (6, 1), (6, 3), (6, 6))]
+        values = sum(q * pair[cb] * pair[ck] for q, (cb, ck) in
+                     zip(quartets, [(cb, ck) for cb in range(6) for ck in range(cb + 1)]))
+        return {"bytes": case["prec"] / 8.0 * values + 24.0 * N * N, "flops": 12.0 * values}
+    return {"bytes": 8.0 * 3 * N * N, "flops": ops}
+
+
+# ----------------------------------------------------------------------- exact
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "dense":
+        eri, D = (x.double() for x in _dense_inputs(case, seed))
+        n, nd = case["n"], case["dens"]
+        T = eri.reshape(n, n, n, n)
+        d = D.reshape(nd, n * n).T.contiguous()
+        J = T.reshape(n * n, n * n) @ d
+        K = T.permute(0, 2, 1, 3).reshape(n * n, n * n) @ d
+        return {"J": J.T.reshape(nd, n, n).contiguous(), "K": K.T.reshape(nd, n, n).contiguous()}
+    if kind == "mlp":
+        return _exact_mlp(case, seed)
+    if kind in ("lda", "pbe"):
+        return _exact_xc(molecule(case, seed), occupied_density(molecule(case, seed), seed), kind)
+    if kind not in ("jk", "eri"):
+        return None
+    mol = molecule(case, seed)
+    if mol.n_bf > 48:
+        return None
+    eri = _exact_eri(mol)
+    if kind == "eri":
+        return eri
+    N, D = mol.n_bf, occupied_density(mol, seed).reshape(-1, 1)
+    return {"J": (eri.reshape(N * N, N * N) @ D).reshape(N, N),
+            "K": (eri.permute(0, 2, 1, 3).reshape(N * N, N * N) @ D).reshape(N, N)}
+
+
+def _exact_mlp(case, seed):
+    params, X, T, M = _mlp_inputs(case, seed)
+    p = torch.tensor(params, dtype=F64, device="cuda", requires_grad=True)
+    y, at = X.double(), 0
+    for k, (o, i) in enumerate(((256, 64), (256, 256), (128, 256))):
+        y = y @ p[at:at + o * i].reshape(o, i).T + p[at + o * i:at + o * i + o]
+        y = torch.nn.functional.silu(y) if k < 2 else y
+        at += o * i + o
+    loss = (M.double() * (y - T.double()) ** 2).sum() / M.double().sum()
+    loss.backward()
+    return {"loss": float(loss.detach()), "grad": p.grad}
+
+
+def _contracted(l, exps, coefs):
+    """Coefficients of x^l exp(-a r^2) in the normalised contraction of normalised primitives."""
+    double_factorial = (1.0, 1.0, 3.0)[l]
+    c = coefs * (2 * exps / math.pi) ** 0.75 * np.sqrt((4 * exps) ** l / double_factorial)
+    p = exps[:, None] + exps[None]
+    self_overlap = (c[:, None] * c[None] * (math.pi / p) ** 1.5 * double_factorial / (2 * p) ** l).sum()
+    return c / math.sqrt(self_overlap)
+
+
+def _component_scale(powers):
+    return math.sqrt(3.0) if sorted(powers) == [0, 1, 1] else 1.0
+
+
+def _boys(L, T):
+    """[F_0(T), ..., F_L(T)]: the series of F_L and downward recurrence below 40, upward from erf above."""
+    small = T < 40.0
+    t = torch.where(small, T, torch.ones_like(T))
+    term = torch.full_like(t, 1.0 / (2 * L + 1))
+    total = term.clone()
+    for k in range(1, 170):
+        term = term * (2.0 * t) / (2 * L + 2 * k + 1)
+        total += term
+    e = torch.exp(-t)
+    low = [e * total]
+    for m in range(L - 1, -1, -1):
+        low.insert(0, (2.0 * t * low[0] + e) / (2 * m + 1))
+    t = torch.where(small, torch.full_like(T, 40.0), T)
+    e = torch.exp(-t)
+    high = [0.5 * torch.sqrt(math.pi / t) * torch.erf(torch.sqrt(t))]
+    for m in range(L):
+        high.append(((2 * m + 1) * high[m] - e) / (2 * t))
+    return [torch.where(small, a, b) for a, b in zip(low, high)]
+
+
+def _triples(L):
+    return [(t, u, s - t - u) for s in range(L + 1) for t in range(s, -1, -1) for u in range(s - t, -1, -1)]
+
+
+def _hermite_coulomb(L, alpha, X):
+    """{(t, u, v): R_tuv} up to t + u + v = L for exponents alpha and distances X = (x, y, z)."""
+    F = _boys(L, alpha * (X[0] ** 2 + X[1] ** 2 + X[2] ** 2))
+    R = {}
+    for n in range(L, -1, -1):
+        new = {(0, 0, 0): (-2.0 * alpha) ** n * F[n]}
+        for tuv in _triples(L - n)[1:]:
+            k = max(range(3), key=lambda i: tuv[i])
+            a = tuple(v - (i == k) for i, v in enumerate(tuv))
+            new[tuv] = X[k] * R[a]
+            if a[k]:
+                new[tuv] = new[tuv] + a[k] * R[tuple(v - (i == k) for i, v in enumerate(a))]
+        R = new
+    return R
+
+
+def _pair_groups(mol):
+    """Primitive pairs of the shell pairs a >= b by (l_a, l_b): exponent, centre, first functions, and the Hermite
+    coefficients of every component pair, E[ca, cb][tuv]."""
+    first = np.concatenate([[0], np.cumsum([NCART[l] for l in mol.shell_l])])
+    groups = {}
+    for a, (ia, la, ea, ka) in enumerate(mol.shells):
+        for b, (ib, lb, eb, kb) in enumerate(mol.shells[:a + 1]):
+            sa, sb = (a, b) if la >= lb else (b, a)
+            (i, l, e, k), (j, m, f, h) = mol.shells[sa], mol.shells[sb]
+            cc = _contracted(l, e, k)[:, None] * _contracted(m, f, h)[None]
+            aa, bb = np.broadcast_arrays(e[:, None], f[None])
+            row = np.empty((aa.size, 11))
+            row[:, 0], row[:, 1], row[:, 2] = aa.ravel(), bb.ravel(), cc.ravel()
+            row[:, 3:6], row[:, 6:9], row[:, 9], row[:, 10] = mol.xyz[i], mol.xyz[j], first[sa], first[sb]
+            groups.setdefault((l, m), []).append(row)
+    out = []
+    for (l, m), rows in groups.items():
+        g = torch.tensor(np.concatenate(rows), device="cuda")
+        a, b, p = g[:, 0], g[:, 1], g[:, 0] + g[:, 1]
+        A, B = g[:, 3:6], g[:, 6:9]
+        P = (a[:, None] * A + b[:, None] * B) / p[:, None]
+        scale = g[:, 2] * torch.exp(-a * b / p * ((A - B) ** 2).sum(1))
+        E = []
+        for d in range(3):
+            e = {(0, 0, 0): torch.ones_like(p)}
+            get = lambda i, j, t: e.get((i, j, t), 0.0)  # noqa: E731
+            for i in range(l + 1):
+                for j in range(m + 1):
+                    for t in range(i + j + 1):
+                        if i + j:
+                            x, s = ((P - A), (i - 1, j)) if i else ((P - B), (i, j - 1))
+                            e[i, j, t] = get(*s, t - 1) / (2 * p) + x[:, d] * get(*s, t) + (t + 1) * get(*s, t + 1)
+            E.append(e)
+        herm = _triples(l + m)
+        coef = torch.zeros(NCART[l], NCART[m], len(herm), len(p), dtype=F64, device="cuda")
+        for ca, pa in enumerate(POWERS[l]):
+            for cb, pb in enumerate(POWERS[m]):
+                for h, tuv in enumerate(herm):
+                    if all(tuv[d] <= pa[d] + pb[d] for d in range(3)):
+                        coef[ca, cb, h] = scale * _component_scale(pa) * _component_scale(pb) * \
+                            E[0][pa[0], pb[0], tuv[0]] * E[1][pa[1], pb[1], tuv[1]] * E[2][pa[2], pb[2], tuv[2]]
+        out.append((p, P, g[:, 9].long(), g[:, 10].long(), l, m, herm, coef))
+    return out
+
+
+def _exact_eri(mol):
+    """The dense tensor (ij|kl) as H W H^T: H the Hermite coefficients of every function pair, W the Coulomb
+    interactions of the Hermite Gaussians of every two primitive pairs."""
+    N, groups = mol.n_bf, _pair_groups(mol)
+    T = torch.zeros(N * N, N * N, dtype=F64, device="cuda")
+    expand = []
+    for p, P, fa, fb, l, m, herm, coef in groups:  # H restricted to the group: [N^2, herm * primitive pairs]
+        H = torch.zeros(N * N, len(herm), len(p), dtype=F64, device="cuda")
+        at = torch.arange(len(p), device="cuda")
+        for ca in range(NCART[l]):
+            for cb in range(NCART[m]):
+                for h in range(len(herm)):
+                    H[(fa + ca) * N + fb + cb, h, at] = coef[ca, cb, h]
+        expand.append(H)
+    for x, (p, P, _, _, l, m, herm, _) in enumerate(groups):
+        for y, (q, Q, _, _, l2, m2, herm2, _) in enumerate(groups[:x + 1]):
+            block = torch.zeros(N * N, N * N, dtype=F64, device="cuda")
+            for at in range(0, len(p), 1024):  # bounded intermediates
+                pp, qq = p[at:at + 1024, None], q[None]
+                X = [P[at:at + 1024, d, None] - Q[None, :, d] for d in range(3)]
+                R = _hermite_coulomb(l + m + l2 + m2, pp * qq / (pp + qq), X)
+                pref = 2 * math.pi ** 2.5 / (pp * qq * torch.sqrt(pp + qq))
+                for h, u in enumerate(herm):
+                    for h2, v in enumerate(herm2):
+                        W = R[tuple(s + t for s, t in zip(u, v))] * pref * (-1.0) ** sum(v)
+                        block += (expand[x][:, h, at:at + 1024] @ W) @ expand[y][:, h2].T.contiguous()
+            T += block
+            if x != y:
+                T += block.T
+    # each unordered shell pair is held once: fill (ij) from (ji) where it is empty
+    T = T.reshape(N, N, N, N)
+    held = torch.zeros(N, N, dtype=torch.bool, device="cuda")
+    for p, P, fa, fb, l, m, _, _ in groups:
+        for ca in range(NCART[l]):
+            for cb in range(NCART[m]):
+                held[fa + ca, fb + cb] = True
+    T = torch.where(held[:, :, None, None], T, T.transpose(0, 1))
+    return torch.where(held[None, None], T, T.transpose(2, 3)).contiguous()
+
+
+def _grid(mol):
+    """Points and weights: per atom 75 Gauss-Chebyshev radii by (1 + x) / (1 - x), 17 Gauss-Legendre cosines, 34
+    azimuths; Becke's cells, three iterations, no size adjustment."""
+    x = np.cos(np.arange(1, 76) * math.pi / 76)
+    r = (1 + x) / (1 - x)
+    wr = math.pi / 76 * np.sqrt(1 - x * x) * 2 / (1 - x) ** 2 * r * r
+    u, wu = np.polynomial.legendre.leggauss(17)
+    phi = 2 * math.pi * np.arange(34) / 34
+    st = np.sqrt(1 - u * u)
+    unit = np.stack(np.broadcast_arrays(st[:, None] * np.cos(phi), st[:, None] * np.sin(phi), u[:, None]), -1)
+    local = (r[:, None, None] * unit.reshape(1, -1, 3)).reshape(-1, 3)
+    w = (wr[:, None, None] * wu[None, :, None] * np.full((1, 1, 34), 2 * math.pi / 34)).reshape(-1)
+    xyz = torch.tensor(mol.xyz, device="cuda")
+    R = torch.cdist(xyz, xyz, compute_mode="donot_use_mm_for_euclid_dist").fill_diagonal_(1.0)
+    points, weights = [], []
+    for a in range(len(xyz)):
+        pts = torch.tensor(local, device="cuda") + xyz[a]
+        d = torch.sqrt(((pts[:, None] - xyz[None]) ** 2).sum(-1))
+        cells = torch.empty_like(d)
+        for c in range(len(xyz)):
+            mu = (d[:, c, None] - d) / R[c]
+            for _ in range(3):
+                mu = 1.5 * mu - 0.5 * mu ** 3
+            s = 0.5 * (1 - mu)
+            s[:, c] = 1.0
+            cells[:, c] = s.prod(1)
+        points.append(pts)
+        weights.append(torch.tensor(w, device="cuda") * cells[:, a] / cells.sum(1))
+    return torch.cat(points), torch.cat(weights)
+
+
+def _basis_values(mol, pts, gradients):
+    """phi [points, N], and with gradients d phi / dx, dy, dz too."""
+    planes = [[] for _ in range(4 if gradients else 1)]
+    for atom, l, exps, coefs in mol.shells:
+        d = pts - torch.tensor(mol.xyz[atom], device="cuda")
+        a = torch.tensor(exps, device="cuda")
+        e = torch.tensor(_contracted(l, exps, coefs), device="cuda") * torch.exp(-(d ** 2).sum(1)[:, None] * a)
+        rad, drad = e.sum(1), -2.0 * (e * a).sum(1)  # d rad / dx_k = x_k drad
+        for pw in POWERS[l]:
+            s = _component_scale(pw)
+            mono = d[:, 0] ** pw[0] * d[:, 1] ** pw[1] * d[:, 2] ** pw[2] * s
+            planes[0].append(mono * rad)
+            for k in range(3 if gradients else 0):
+                low = s * pw[k] * torch.ones_like(rad)
+                for j in range(3):
+                    low = low * d[:, j] ** (max(pw[j] - 1, 0) if j == k else pw[j])
+                planes[1 + k].append(low * rad + mono * d[:, k] * drad)
+    return [torch.stack(p, 1) for p in planes]
+
+
+def _pbe_density(rho, sigma):
+    """PBE energy per volume of a closed shell (Perdew-Wang 1992 correlation)."""
+    beta, gamma, kappa = 0.06672455060314922, (1 - math.log(2)) / math.pi ** 2, 0.804
+    mu = beta * math.pi ** 2 / 3
+    kf = (3 * math.pi ** 2 * rho) ** (1 / 3)
+    s2 = sigma / (2 * kf * rho) ** 2
+    ex = -0.75 * (3 / math.pi) ** (1 / 3) * rho ** (4 / 3) * (1 + kappa - kappa / (1 + mu * s2 / kappa))
+    rs = (3 / (4 * math.pi * rho)) ** (1 / 3)
+    A = 0.031091
+    q = 2 * A * (7.5957 * rs ** 0.5 + 3.5876 * rs + 1.6382 * rs ** 1.5 + 0.49294 * rs ** 2)
+    ec = -2 * A * (1 + 0.21370 * rs) * torch.log1p(1 / q)
+    t2 = sigma / (2 * torch.sqrt(4 * kf / math.pi) * rho) ** 2
+    a = beta / gamma / torch.expm1(-ec / gamma)
+    h = gamma * torch.log1p(beta / gamma * t2 * (1 + a * t2) / (1 + a * t2 + (a * t2) ** 2))
+    return ex + rho * (ec + h)
+
+
+def _exact_xc(mol, D, kind):
+    pts, w = _grid(mol)
+    V, E, rhos, grads = torch.zeros_like(D), 0.0, [], []
+    for at in range(0, len(w), 1 << 18):
+        f = _basis_values(mol, pts[at:at + (1 << 18)], kind == "pbe")
+        phi, wt = f[0], w[at:at + (1 << 18)]
+        U = phi @ D
+        rho = (U * phi).sum(1)
+        rhos.append(rho)
+        if kind == "lda":
+            pos = rho.clamp(min=0.0)
+            E += float((wt * -0.75 * (3 / math.pi) ** (1 / 3) * pos ** (4 / 3)).sum())
+            V += (phi * (wt * -(3 / math.pi) ** (1 / 3) * pos ** (1 / 3))[:, None]).T.contiguous() @ phi
+            continue
+        g = torch.stack([2.0 * (U * f[1 + k]).sum(1) for k in range(3)])
+        grads.append(g)
+        live = rho >= 1e-10
+        r = torch.where(live, rho, torch.ones_like(rho)).requires_grad_()
+        sg = torch.where(live, (g ** 2).sum(0), torch.ones_like(rho)).requires_grad_()
+        e = _pbe_density(r, sg)
+        fr, fs = torch.autograd.grad(e.sum(), (r, sg))
+        wt = torch.where(live, wt, torch.zeros_like(wt))
+        E += float((wt * e.detach()).sum())
+        z = phi * (0.5 * wt * fr)[:, None]
+        for k in range(3):
+            z = z + f[1 + k] * (2.0 * wt * fs * g[k])[:, None]
+        half = phi.T.contiguous() @ z
+        V += half + half.T
+    out = {"E": E, "V": V, "rho": torch.cat(rhos)}
+    return out if kind == "lda" else {**out, "grad_rho": torch.cat(grads, 1)}
