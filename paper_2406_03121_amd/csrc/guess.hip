@@ -193,157 +193,59 @@ __device__ __forceinline__ float dsilu_f(float z) {
     return s * (1.0f + z * (1.0f - s));
 }
 
-enum { kEpiHidden = 0, kEpiOut = 1, kEpiBackHidden = 2, kEpiAtomic = 3 };
+// Fragment order.  v_mfma_f32_16x16x16_bf16 takes from lane l the four
+// elements A[l % 16][4 (l / 16) + 0..3] and B[4 (l / 16) + 0..3][l % 16] and
+// returns in lane l the rows 4 (l / 16) + 0..3 of column l % 16.  A matrix
+// whose contracted index is r and whose other index is c is kept as
+// [c / 16][r / 16][lane][r % 4], lane = c % 16 + 16 ((r % 16) / 4), so a
+// wave reads one operand as 512 consecutive bytes, and an accumulator tile
+// rounded to BF16 is, lane by lane, an operand of a product contracted over
+// its rows: what the row kernel writes is what the weight gradient reads.
+//
+// Weights are held in fragment order with the fragments of two consecutive
+// contraction steps side by side (16 bytes a lane), once for the forward
+// products (contracted over inputs) and, for layers 2 and 3, once for the
+// backward ones (contracted over outputs).
+constexpr int kW1f = 0, kW2f = kW1f + kHid * kIn, kW3f = kW2f + kHid * kHid, kW2b = kW3f + kOut * kHid,
+              kW3b = kW2b + kHid * kHid, kNPacked = kW3b + kOut * kHid;
 
-constexpr int kGT = 64;   // output tile edge
-constexpr int kGK = 32;   // K per LDS stage (two MFMA steps)
-constexpr int kLdsK = kGK + 4;  // row stride (bf16 elements), 8-byte aligned fragments
+// Place of element (c, r) of a weight operand contracted over R values of r.
+__host__ __device__ __forceinline__ int packed_at(int c, int r, int R) {
+    const int lane = c % 16 + 16 * ((r % 16) / 4);
+    return (((c / 16) * (R / 32) + r / 32) * 64 + lane) * 8 + ((r / 16) % 2) * 4 + r % 4;
+}
 
-// C[M x N] = op(A)[M x K] op(B)[K x N] with BF16 operands and FP32
-// accumulation.  op(A) = A (M x K row-major, lda) or, with TA, A stored
-// K x M; op(B) = B (K x N row-major) or, with TB, B stored N x K.
-// Epilogues:
-//   kEpiHidden:     Zf = acc + bias[n];  Hb = bf16(silu(Zf))
-//   kEpiOut:        Zf = acc + bias[n]
-//   kEpiBackHidden: Zf = acc * dsilu(aux[m][n]);  Hb = bf16(Zf)
-//   kEpiAtomic:     Zf[m][n] += acc (split K over blockIdx.z, kSplit rows each)
-// A 256-thread block computes a 64 x 64 tile; wave w owns the 32 x 32
-// quadrant (w / 2, w % 2) as 2 x 2 MFMA 16 x 16 tiles.  MFMA operand
-// layout (16 x 16 x 16): lane l holds A[l % 16][4 (l / 16) + 0..3],
-// B[4 (l / 16) + 0..3][l % 16], and the result rows 4 (l / 16) + 0..3 of
-// column l % 16.
-template <bool TA, bool TB, int EPI>
-__global__ void __launch_bounds__(256) k_gemm_bf16(int M, int N, int K, int kSplit,
-                                                   const unsigned short *__restrict__ A, int lda,
-                                                   const unsigned short *__restrict__ B, int ldb,
-                                                   const float *__restrict__ bias, const float *__restrict__ aux,
-                                                   float *__restrict__ Zf, unsigned short *__restrict__ Hb, int ldc) {
-    __shared__ __align__(16) unsigned short As[kGT][kLdsK];
-    __shared__ __align__(16) unsigned short Bs[kGT][kLdsK];  // [n][k]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT;
-    const int kbeg = EPI == kEpiAtomic ? blockIdx.z * kSplit : 0;
-    const int kend = EPI == kEpiAtomic ? min(K, kbeg + kSplit) : K;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    v4f acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k0 = kbeg; k0 < kend; k0 += kGK) {
-        // stage A tile [64 m][32 k] and B tile [64 n][32 k]
-        for (int t = threadIdx.x; t < kGT * kGK; t += 256) {
-            int m, k;
-            if (TA) {
-                k = t / kGT;
-                m = t % kGT;  // global contiguous in m
-            } else {
-                m = t / kGK;
-                k = t % kGK;  // contiguous in k
-            }
-            const int gm = m0 + m, gk = k0 + k;
-            unsigned short v = 0;
-            if (gm < M && gk < kend) v = TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk];
-            As[m][k] = v;
-        }
-        for (int t = threadIdx.x; t < kGT * kGK; t += 256) {
-            int n, k;
-            if (TB) {
-                n = t / kGK;
-                k = t % kGK;
-            } else {
-                k = t / kGT;
-                n = t % kGT;
-            }
-            const int gn = n0 + n, gk = k0 + k;
-            unsigned short v = 0;
-            if (gn < N && gk < kend) v = TB ? B[(int64_t)gn * ldb + gk] : B[(int64_t)gk * ldb + gn];
-            Bs[n][k] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < kGK; ks += 16) {
-            const int kk = ks + 4 * (lane >> 4);
-            v4s a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const v4s *>(&As[wm + 16 * i + (lane & 15)][kk]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const v4s *>(&Bs[wn + 16 * j + (lane & 15)][kk]);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
+// Writes parameter i (a weight) to its packed places.
+__device__ __forceinline__ void pack_weight(int64_t i, float x, unsigned short *__restrict__ pk) {
+    const unsigned short v = to_bf16(x);
+    if (i < kOffB1) {
+        pk[kW1f + packed_at((int)i / kIn, (int)i % kIn, kIn)] = v;
+    } else if (i >= kOffW2 && i < kOffB2) {
+        const int o = (int)(i - kOffW2) / kHid, k = (int)(i - kOffW2) % kHid;
+        pk[kW2f + packed_at(o, k, kHid)] = v;
+        pk[kW2b + packed_at(k, o, kHid)] = v;
+    } else if (i >= kOffW3 && i < kOffB3) {
+        const int o = (int)(i - kOffW3) / kHid, k = (int)(i - kOffW3) % kHid;
+        pk[kW3f + packed_at(o, k, kHid)] = v;
+        pk[kW3b + packed_at(k, o, kOut)] = v;
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int gm = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-                const int gn = n0 + wn + 16 * j + (lane & 15);
-                if (gm >= M || gn >= N) continue;
-                const int64_t o = (int64_t)gm * ldc + gn;
-                const float v = acc[i][j][r];
-                if (EPI == kEpiHidden) {
-                    const float z = v + bias[gn];
-                    Zf[o] = z;
-                    Hb[o] = to_bf16(silu_f(z));
-                } else if (EPI == kEpiOut) {
-                    Zf[o] = v + bias[gn];
-                } else if (EPI == kEpiBackHidden) {
-                    const float z = v * dsilu_f(aux[o]);
-                    Zf[o] = z;
-                    Hb[o] = to_bf16(z);
-                } else {
-                    unsafeAtomicAdd(&Zf[o], v);
-                }
-            }
 }
 
-__global__ void k_to_bf16(int64_t n, const float *__restrict__ x, unsigned short *__restrict__ y) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = to_bf16(x[i]);
+__global__ void k_pack(const float *__restrict__ p, unsigned short *__restrict__ pk) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < kNParam) pack_weight(i, p[i], pk);
 }
 
-__global__ void k_fill_f32(int64_t n, float *__restrict__ p) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0f;
-}
+constexpr int kMaskBlocks = 256;
+constexpr int kRowBlocksMax = 1024;  // blocks of the row kernel (bias and loss partials)
+constexpr int kBias = 2 * kHid + kOut;
+constexpr int kLdsRow = kHid + 8;    // BF16 elements of an activation row in LDS: 4 banks from row to row
 
-// sum of the mask (one block)
-__global__ void __launch_bounds__(256) k_mask_sum(int64_t n, const float *__restrict__ M, float *__restrict__ out) {
+// Partial sums of the mask, one per block.
+__global__ void __launch_bounds__(256) k_mask_sum(int64_t n, const float *__restrict__ M, double *__restrict__ part) {
     __shared__ double red[256];
     double s = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) s += M[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = (float)red[0];
-}
-
-// dY = 2 M (Y - T) / sum(M) (FP32 and BF16); per-block partial sums of
-// M (Y - T)^2 (FP64).
-__global__ void __launch_bounds__(256) k_mse(int64_t n, const float *__restrict__ Y, const float *__restrict__ T,
-                                             const float *__restrict__ M, const float *__restrict__ msum,
-                                             float *__restrict__ dY, unsigned short *__restrict__ dYb,
-                                             double *__restrict__ part) {
-    __shared__ double red[256];
-    const float inv = 2.0f / msum[0];
-    double s = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float d = M[i] * (Y[i] - T[i]);
-        s += (double)d * d;
-        const float g = d * inv;
-        dY[i] = g;
-        dYb[i] = to_bf16(g);
-    }
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)kMaskBlocks * 256) s += M[i];
     red[threadIdx.x] = s;
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {
@@ -353,44 +255,325 @@ __global__ void __launch_bounds__(256) k_mse(int64_t n, const float *__restrict_
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void __launch_bounds__(256) k_loss_finish(int nb, const double *__restrict__ part,
-                                                     const float *__restrict__ msum, double *__restrict__ loss) {
+// acc[i][j] += A (rows 16 i.., R values of r, LDS) times NT column tiles of
+// a packed weight operand starting at column tile ct0.
+template <int RT, int NT, int R>
+__device__ __forceinline__ void row_product(const unsigned short *__restrict__ As, int lda,
+                                            const unsigned short *__restrict__ W, int ct0, int lane,
+                                            v4f (&acc)[RT][NT]) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    // four steps of loads in flight; unrolled further, the loads of all five
+    // products are hoisted to the top and spill
+#pragma unroll RT == 1 ? 4 : 2
+    for (int s2 = 0; s2 < R / 32; ++s2) {
+        struct alignas(16) Pair { v4s f[2]; } b[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            b[j] = *reinterpret_cast<const Pair *>(W + (((ct0 + j) * (R / 32) + s2) * 64 + lane) * 8);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const v4s a = *reinterpret_cast<const v4s *>(As + (16 * i + lane % 16) * lda + 32 * s2 + 16 * h + 4 * (lane / 16));
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b[j].f[h], acc[i][j], 0, 0, 0);
+            }
+    }
+}
+
+// Activations and back-propagated gradients kept for the weight gradients,
+// in fragment order over the rows (ns steps of 16 rows).
+struct RowFrags {
+    unsigned short *X, *H1, *H2, *dY, *dZ2, *dZ1;
+    int64_t ns;
+};
+
+__device__ __forceinline__ void put_frag(unsigned short *__restrict__ F, int64_t ns, int ct, int64_t rs, int lane, v4s v) {
+    *reinterpret_cast<v4s *>(F + (((int64_t)ct * ns + rs) * 64 + lane) * 4) = v;
+}
+
+// The whole network over 16 RT rows a block: the three layers and, with
+// GRAD, the loss, both hidden gradients and the partial sums of the bias
+// gradients and of the loss.  The chain of five products is short and every
+// layer needs all of the one before it, so what bounds it is latency, then
+// the 416 KB of weights that every block reads from the L2: the rows stay in
+// one block, the activations in LDS, the pre-activations in the registers of
+// the lanes that need them again (the tile of Z that a lane computes is the
+// tile of dZ that it computes later), and a wave owns 64 of the 256 hidden
+// columns, its weight fragments as 1 KB loads.  Each product accumulates in
+// ascending contraction order.  Before, every layer was a launch of its own
+// that read and wrote its operands in global memory (gradient call of 4096
+// rows, all kernels: 1480 -> 68 us, of which the one-block mask sum was 525,
+// the three split weight products with FP32 atomics 410, the three column
+// sums with one row group a block 360).
+template <int RT, bool GRAD>
+__global__ void __launch_bounds__(256) k_mlp_rows(int64_t n, const float *__restrict__ X, const float *__restrict__ p,
+                                                  const unsigned short *__restrict__ pk, float *__restrict__ Y,
+                                                  const float *__restrict__ T, const float *__restrict__ M,
+                                                  const double *__restrict__ mpart, RowFrags fr,
+                                                  double *__restrict__ lpart, float *__restrict__ bpart) {
+    __shared__ __align__(16) unsigned short Xs[16 * RT][kIn + 8];
+    __shared__ __align__(16) unsigned short Ha[16 * RT][kLdsRow];
+    __shared__ __align__(16) unsigned short Hb[16 * RT][kLdsRow];
     __shared__ double red[256];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < nb; i += 256) s += part[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, rq = 4 * (lane >> 4);
+    float inv = 0.0f;
+    if constexpr (GRAD) {
+        red[threadIdx.x] = mpart[threadIdx.x];
+        __syncthreads();
+        for (int st = 128; st > 0; st >>= 1) {
+            if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+            __syncthreads();
+        }
+        inv = 2.0f / (float)red[0];
         __syncthreads();
     }
-    if (threadIdx.x == 0) loss[0] = red[0] / (double)msum[0];
+    double loss = 0.0;
+    float db1[4] = {}, db2[4] = {}, db3[2] = {};
+    const int64_t ntile = (n + 16 * RT - 1) / (16 * RT);
+    for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+        const int64_t r0 = tile * 16 * RT;
+#pragma unroll
+        for (int t = threadIdx.x; t < 16 * RT * kIn; t += 256) {
+            const int64_t r = r0 + t / kIn;
+            Xs[t / kIn][t % kIn] = r < n ? to_bf16(X[r * kIn + t % kIn]) : 0;
+        }
+        __syncthreads();
+        if constexpr (GRAD)
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                v4s v;
+                for (int q = 0; q < 4; ++q) v[q] = (short)Xs[16 * i + rq + q][16 * wave + col];
+                put_frag(fr.X, fr.ns, wave, tile * RT + i, lane, v);
+            }
+        // Z = A W^T + b into z, silu(Z) as BF16 to the next layer's rows
+        v4f z1[RT][4], z2[RT][4];
+        auto hidden = [&](v4f(&z)[RT][4], const float *bias, unsigned short (*H)[kLdsRow], unsigned short *F) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int c = 64 * wave + 16 * j + col;
+                const float b = bias[c];
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    v4s h;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        z[i][j][q] += b;
+                        h[q] = (short)to_bf16(silu_f(z[i][j][q]));
+                        H[16 * i + rq + q][c] = (unsigned short)h[q];
+                    }
+                    if constexpr (GRAD) put_frag(F, fr.ns, 4 * wave + j, tile * RT + i, lane, h);
+                }
+            }
+        };
+        row_product<RT, 4, kIn>(&Xs[0][0], kIn + 8, pk + kW1f, 4 * wave, lane, z1);
+        hidden(z1, p + kOffB1, Ha, fr.H1);
+        __syncthreads();
+        row_product<RT, 4, kHid>(&Ha[0][0], kLdsRow, pk + kW2f, 4 * wave, lane, z2);
+        hidden(z2, p + kOffB2, Hb, fr.H2);
+        __syncthreads();
+        v4f y[RT][2];
+        row_product<RT, 2, kHid>(&Hb[0][0], kLdsRow, pk + kW3f, 2 * wave, lane, y);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int c = 32 * wave + 16 * j + col;
+            const float b = p[kOffB3 + c];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                v4s g4;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t r = r0 + 16 * i + rq + q;
+                    const float v = y[i][j][q] + b;
+                    if constexpr (GRAD) {
+                        // dY = 2 M (Y - T) / sum(M)
+                        const float d = r < n ? M[r * kOut + c] * (v - T[r * kOut + c]) : 0.0f;
+                        loss += (double)d * d;
+                        const float g = d * inv;
+                        db3[j] += g;
+                        g4[q] = (short)to_bf16(g);
+                        Ha[16 * i + rq + q][c] = (unsigned short)g4[q];
+                    } else if (r < n) {
+                        Y[r * kOut + c] = v;
+                    }
+                }
+                if constexpr (GRAD) put_frag(fr.dY, fr.ns, 2 * wave + j, tile * RT + i, lane, g4);
+            }
+        }
+        __syncthreads();
+        if constexpr (GRAD) {
+            // dZ = (dOut W) .* silu'(Z)
+            auto back = [&](v4f(&acc)[RT][4], const v4f(&z)[RT][4], float(&db)[4], unsigned short (*H)[kLdsRow],
+                            unsigned short *F) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) {
+                        v4s h;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float d = acc[i][j][q] * dsilu_f(z[i][j][q]);
+                            db[j] += d;
+                            h[q] = (short)to_bf16(d);
+                            if (H) H[16 * i + rq + q][64 * wave + 16 * j + col] = (unsigned short)h[q];
+                        }
+                        put_frag(F, fr.ns, 4 * wave + j, tile * RT + i, lane, h);
+                    }
+            };
+            v4f acc[RT][4];
+            row_product<RT, 4, kOut>(&Ha[0][0], kLdsRow, pk + kW3b, 4 * wave, lane, acc);
+            back(acc, z2, db2, Hb, fr.dZ2);
+            __syncthreads();
+            row_product<RT, 4, kHid>(&Hb[0][0], kLdsRow, pk + kW2b, 4 * wave, lane, acc);
+            back(acc, z1, db1, nullptr, fr.dZ1);
+        }
+    }
+    if constexpr (GRAD) {
+        // column sums over the block's rows: the four row groups of a wave
+        float *bp = bpart + (int64_t)blockIdx.x * kBias;
+        auto put = [&](float v, int c) {
+            v += __shfl_xor(v, 16, 64);
+            v += __shfl_xor(v, 32, 64);
+            if (lane < 16) bp[c + lane] = v;
+        };
+#pragma unroll
+        for (int j = 0; j < 4; ++j) put(db1[j], 64 * wave + 16 * j);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) put(db2[j], kHid + 64 * wave + 16 * j);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) put(db3[j], 2 * kHid + 32 * wave + 16 * j);
+        red[threadIdx.x] = loss;
+        __syncthreads();
+        for (int st = 128; st > 0; st >>= 1) {
+            if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) lpart[blockIdx.x] = red[0];
+    }
 }
 
-// db[j] = sum over rows of G[r][j] (FP32), one thread per column, rows split
-// over blockIdx.y with atomics.
-__global__ void k_colsum(int64_t nrows, int ncol, int rows_per, const float *__restrict__ G, float *__restrict__ db) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= ncol) return;
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per;
-    const int64_t r1 = r0 + rows_per < nrows ? r0 + rows_per : nrows;
-    float s = 0.0f;
-    for (int64_t r = r0; r < r1; ++r) s += G[r * ncol + j];
-    unsafeAtomicAdd(&db[j], s);
+// Weight gradients dW[o][i] = sum over rows of dOut[row][o] In[row][i]: a
+// block takes one of the 28 tiles of 64 x 64 (8 of W3, 16 of W2, 4 of W1)
+// and one of gridDim.y chunks of row steps, its four waves every fourth step
+// each, summed in LDS; chunks leave partial sums for k_mlp_finish.  Both
+// operands are read in fragment order, 512 consecutive bytes a wave.  The
+// weights are too few to fill the chip with one block a tile, so the rows are
+// split, into at most 32 chunks so that the partial sums stay below 15 MB.
+// (FP32 atomics in their place cost 137 us a layer at 4096 rows.)
+__global__ void __launch_bounds__(256) k_mlp_wgrad(RowFrags fr, int64_t steps_per, float *__restrict__ part) {
+    __shared__ float red[4][64 * 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int t = blockIdx.x;
+    const unsigned short *A, *B;
+    int64_t off;
+    int ldw, ot, it;
+    if (t < 8) {
+        A = fr.dY, B = fr.H2, off = kOffW3, ldw = kHid, ot = t / 4, it = t % 4;
+    } else if (t < 24) {
+        t -= 8;
+        A = fr.dZ2, B = fr.H1, off = kOffW2, ldw = kHid, ot = t / 4, it = t % 4;
+    } else {
+        A = fr.dZ1, B = fr.X, off = kOffW1, ldw = kIn, ot = t - 24, it = 0;
+    }
+    const int64_t s0 = blockIdx.y * steps_per, s1 = s0 + steps_per < fr.ns ? s0 + steps_per : fr.ns;
+    v4f acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 2
+    for (int64_t s = s0 + wave; s < s1; s += 4) {
+        v4s a[4], b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i] = *reinterpret_cast<const v4s *>(A + (((4 * ot + i) * fr.ns + s) * 64 + lane) * 4);
+            b[i] = *reinterpret_cast<const v4s *>(B + (((4 * it + i) * fr.ns + s) * 64 + lane) * 4);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) red[wave][(16 * i + 4 * (lane >> 4) + q) * 64 + 16 * j + (lane & 15)] = acc[i][j][q];
+    __syncthreads();
+    float *o = part + blockIdx.y * kNParam + off;
+    for (int e = threadIdx.x; e < 64 * 64; e += 256)
+        o[(64 * ot + e / 64) * ldw + 64 * it + e % 64] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
 }
 
-__global__ void k_adam(int64_t n, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
-                       const float *__restrict__ g, float lr, float b1, float b2, float eps, float c1, float c2,
-                       unsigned short *__restrict__ pb) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.0f - b1) * gi;
-        const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-        p[i] = pi;
-        pb[i] = to_bf16(pi);
+struct AdamArgs {
+    float *p, *m, *v;
+    unsigned short *pk;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+constexpr int kFinishW = (int)((kNParam + 255) / 256), kFinishB = kBias / 16;
+
+// Sums the partial gradients (blocks below kFinishW: 256 weights each; the
+// next kFinishB: 16 bias columns each) and the loss (last block); the sums
+// go to g (may be NULL) or, with ADAM, into the parameters.
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_mlp_finish(int nchunk, const float *__restrict__ part, int nrow,
+                                                    const float *__restrict__ bpart, const double *__restrict__ lpart,
+                                                    const double *__restrict__ mpart, double *__restrict__ loss,
+                                                    float *__restrict__ g, AdamArgs ad) {
+    __shared__ double red[256];
+    auto put = [&](int64_t i, float gi) {
+        if constexpr (ADAM) {
+            const float mi = ad.b1 * ad.m[i] + (1.0f - ad.b1) * gi;
+            const float vi = ad.b2 * ad.v[i] + (1.0f - ad.b2) * gi * gi;
+            ad.m[i] = mi;
+            ad.v[i] = vi;
+            const float pi = ad.p[i] - ad.lr * (mi / ad.c1) / (sqrtf(vi / ad.c2) + ad.eps);
+            ad.p[i] = pi;
+            pack_weight(i, pi, ad.pk);
+        } else if (g) {
+            g[i] = gi;
+        }
+    };
+    const int t = threadIdx.x;
+    if (blockIdx.x < kFinishW) {
+        const int64_t i = blockIdx.x * (int64_t)256 + t;
+        const bool bias = (i >= kOffB1 && i < kOffW2) || (i >= kOffB2 && i < kOffW3) || i >= kOffB3;
+        if (i >= kNParam || bias) return;
+        float s = 0.0f;
+        for (int c = 0; c < nchunk; ++c) s += part[c * kNParam + i];
+        put(i, s);
+    } else if (blockIdx.x < kFinishW + kFinishB) {
+        const int c = 16 * (blockIdx.x - kFinishW) + t % 16;
+        float s = 0.0f;
+        for (int b = t / 16; b < nrow; b += 16) s += bpart[(int64_t)b * kBias + c];
+        float *rf = reinterpret_cast<float *>(red);
+        rf[t] = s;
+        __syncthreads();
+        if (t >= 16) return;
+        s = 0.0f;
+        for (int k = 0; k < 16; ++k) s += rf[16 * k + t];
+        put(c < kHid ? kOffB1 + c : c < 2 * kHid ? kOffB2 + c - kHid : kOffB3 + c - 2 * kHid, s);
+    } else {
+        auto total = [&](const double *x, int n) {
+            double s = 0.0;
+            for (int i = t; i < n; i += 256) s += x[i];
+            red[t] = s;
+            __syncthreads();
+            for (int st = 128; st > 0; st >>= 1) {
+                if (t < st) red[t] += red[t + st];
+                __syncthreads();
+            }
+            s = red[0];
+            __syncthreads();
+            return s;
+        };
+        const double ls = total(lpart, nrow), ms = total(mpart, kMaskBlocks);
+        if (t == 0) loss[0] = ls / (double)(float)ms;
     }
 }
 
@@ -399,137 +582,112 @@ __global__ void k_adam(int64_t n, float *__restrict__ p, float *__restrict__ m, 
 // ------------------------------------------------------------ the model
 
 struct mess_mlp {
-    float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
-    unsigned short *pb = nullptr;
+    float *p = nullptr, *m = nullptr, *v = nullptr;
+    unsigned short *pk = nullptr;  // weights as BF16 fragments
     int t = 0;
-    int64_t cap = 0;  // rows the workspace holds
-    unsigned short *Xb = nullptr, *H1b = nullptr, *H2b = nullptr, *dYb = nullptr, *dZ2b = nullptr, *dZ1b = nullptr;
-    float *Z1 = nullptr, *Z2 = nullptr, *dY = nullptr, *dZ2 = nullptr, *dZ1 = nullptr, *Yw = nullptr;
-    float *msum = nullptr;
-    double *part = nullptr, *loss = nullptr;
+    int64_t cap = 0;               // rows the workspace holds
+    unsigned short *frags = nullptr;
+    float *wpart = nullptr, *bpart = nullptr;
+    double *mpart = nullptr, *lpart = nullptr, *loss = nullptr;
 };
 
 namespace mess {
 
-constexpr int kMseBlocks = 512;
+constexpr int kFragCols = kIn + 4 * kHid + kOut;
+constexpr int kMaxChunks = 32;
 
-static void free_ws(mess_mlp *L) {
-    for (void *q : {(void *)L->Xb, (void *)L->H1b, (void *)L->H2b, (void *)L->dYb, (void *)L->dZ2b, (void *)L->dZ1b,
-                    (void *)L->Z1, (void *)L->Z2, (void *)L->dY, (void *)L->dZ2, (void *)L->dZ1, (void *)L->Yw})
-        hipFree(q);
-    L->Xb = L->H1b = L->H2b = L->dYb = L->dZ2b = L->dZ1b = nullptr;
-    L->Z1 = L->Z2 = L->dY = L->dZ2 = L->dZ1 = L->Yw = nullptr;
-    L->cap = 0;
-}
-
+// Workspace of a gradient over n rows, kept until more rows are asked for.
 static int ensure_ws(mess_mlp *L, int64_t n) {
     if (n <= L->cap) return MESS_OK;
     MESS_HIP(hipDeviceSynchronize());
-    free_ws(L);
-    hipError_t e = hipSuccess;
-    auto al = [&](void **q, size_t bytes) {
-        if (e == hipSuccess) e = hipMalloc(q, bytes);
-    };
-    al((void **)&L->Xb, 2 * n * kIn);
-    al((void **)&L->H1b, 2 * n * kHid);
-    al((void **)&L->H2b, 2 * n * kHid);
-    al((void **)&L->dYb, 2 * n * kOut);
-    al((void **)&L->dZ2b, 2 * n * kHid);
-    al((void **)&L->dZ1b, 2 * n * kHid);
-    al((void **)&L->Z1, 4 * n * kHid);
-    al((void **)&L->Z2, 4 * n * kHid);
-    al((void **)&L->dY, 4 * n * kOut);
-    al((void **)&L->dZ2, 4 * n * kHid);
-    al((void **)&L->dZ1, 4 * n * kHid);
-    al((void **)&L->Yw, 4 * n * kOut);
+    hipFree(L->frags);
+    L->frags = nullptr;
+    L->cap = 0;
+    const int64_t rows = (n + 31) / 32 * 32;
+    const hipError_t e = hipMalloc(&L->frags, sizeof(unsigned short) * kFragCols * rows);
     if (e != hipSuccess) {
-        free_ws(L);
+        L->frags = nullptr;
         set_error("perceptron workspace for %lld rows: %s", (long long)n, hipGetErrorString(e));
         return MESS_E_NOMEM;
     }
-    L->cap = n;
+    L->cap = rows;
     return MESS_OK;
 }
 
-static unsigned g1(int64_t n) { return (unsigned)std::min<int64_t>(std::max<int64_t>((n + 255) / 256, 1), 4096); }
-
-template <bool TA, bool TB, int EPI>
-static int gemm16(hipStream_t s, int M, int N, int K, const unsigned short *A, int lda, const unsigned short *Bm,
-                  int ldb, const float *bias, const float *aux, float *Zf, unsigned short *Hb, int ldc) {
-    int split = K, nz = 1;
-    if (EPI == kEpiAtomic) {
-        split = 1024;
-        nz = (K + split - 1) / split;
-    }
-    dim3 grid((N + kGT - 1) / kGT, (M + kGT - 1) / kGT, nz);
-    hipLaunchKernelGGL((k_gemm_bf16<TA, TB, EPI>), grid, dim3(256), 0, s, M, N, K, split, A, lda, Bm, ldb, bias, aux,
-                       Zf, Hb, ldc);
+// Launches the row kernel: 16 rows a block while that leaves at most one
+// block a CU (4096 rows: the chip is filled and the chain of layers is as
+// short as it gets), 32 above (half the weight traffic from the L2).
+template <bool GRAD>
+static int mlp_rows(mess_mlp *L, int64_t n, const float *X, float *Y, const float *T, const float *M, RowFrags fr,
+                    int *nrow, hipStream_t s) {
+    const bool small = n <= 256 * 16;
+    const int64_t tiles = small ? (n + 15) / 16 : (n + 31) / 32;
+    const unsigned g = (unsigned)std::min<int64_t>(tiles, kRowBlocksMax);
+    if (small)
+        hipLaunchKernelGGL((k_mlp_rows<1, GRAD>), dim3(g), dim3(256), 0, s, n, X, L->p, L->pk, Y, T, M, L->mpart, fr,
+                           L->lpart, L->bpart);
+    else
+        hipLaunchKernelGGL((k_mlp_rows<2, GRAD>), dim3(g), dim3(256), 0, s, n, X, L->p, L->pk, Y, T, M, L->mpart, fr,
+                           L->lpart, L->bpart);
     MESS_LAUNCH_CHECK();
+    if (nrow) *nrow = (int)g;
     return MESS_OK;
 }
 
-// Forward over n rows of X (FP32): Y (FP32); keeps Z1, H1b, Z2, H2b.
+// Forward over n rows of X (FP32): Y (FP32).
 static int mlp_forward(mess_mlp *L, int64_t n, const float *X, float *Y, hipStream_t s) {
-    MESS_TRY(ensure_ws(L, n));
-    const unsigned short *W1 = L->pb + kOffW1, *W2 = L->pb + kOffW2, *W3 = L->pb + kOffW3;
-    hipLaunchKernelGGL(k_to_bf16, dim3(g1(n * kIn)), dim3(256), 0, s, n * kIn, X, L->Xb);
-    MESS_LAUNCH_CHECK();
-    const int nn = (int)n;
-    MESS_TRY((gemm16<false, true, kEpiHidden>(s, nn, kHid, kIn, L->Xb, kIn, W1, kIn, L->p + kOffB1, nullptr, L->Z1,
-                                              L->H1b, kHid)));
-    MESS_TRY((gemm16<false, true, kEpiHidden>(s, nn, kHid, kHid, L->H1b, kHid, W2, kHid, L->p + kOffB2, nullptr,
-                                              L->Z2, L->H2b, kHid)));
-    MESS_TRY((gemm16<false, true, kEpiOut>(s, nn, kOut, kHid, L->H2b, kHid, W3, kHid, L->p + kOffB3, nullptr, Y,
-                                           nullptr, kOut)));
-    return MESS_OK;
+    return mlp_rows<false>(L, n, X, Y, nullptr, nullptr, RowFrags{}, nullptr, s);
 }
 
-// Loss and gradient (into L->g) of the masked MSE over n rows.
-static int mlp_grad(mess_mlp *L, int64_t n, const float *X, const float *T, const float *M, hipStream_t s) {
-    // the workspace (L->Yw among it) must exist before its pointers are taken
+// Loss (into L->loss) and gradient of the masked MSE over n rows: into g
+// (may be NULL), or into the parameters by one Adam step (ad not NULL).
+static int mlp_grad(mess_mlp *L, int64_t n, const float *X, const float *T, const float *M, float *g,
+                    const AdamArgs *ad, hipStream_t s) {
     MESS_TRY(ensure_ws(L, n));
-    MESS_TRY(mlp_forward(L, n, X, L->Yw, s));
-    const int nn = (int)n;
-    const int64_t no = n * kOut;
-    hipLaunchKernelGGL(k_mask_sum, dim3(1), dim3(256), 0, s, no, M, L->msum);
-    hipLaunchKernelGGL(k_mse, dim3(kMseBlocks), dim3(256), 0, s, no, L->Yw, T, M, L->msum, L->dY, L->dYb, L->part);
-    hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(256), 0, s, kMseBlocks, L->part, L->msum, L->loss);
-    hipLaunchKernelGGL(k_fill_f32, dim3(g1(kNParam)), dim3(256), 0, s, (int64_t)kNParam, L->g);
-    MESS_LAUNCH_CHECK();
-    const unsigned short *W2 = L->pb + kOffW2, *W3 = L->pb + kOffW3;
-    const int rows_per = 512;
-    const unsigned ry = (unsigned)((n + rows_per - 1) / rows_per);
-    // layer 3: dW3 = dY^T H2, db3 = sum dY, dZ2 = (dY W3) .* silu'(Z2)
-    MESS_TRY((gemm16<true, false, kEpiAtomic>(s, kOut, kHid, nn, L->dYb, kOut, L->H2b, kHid, nullptr, nullptr,
-                                              L->g + kOffW3, nullptr, kHid)));
-    hipLaunchKernelGGL(k_colsum, dim3(1, ry), dim3(kOut), 0, s, n, kOut, rows_per, L->dY, L->g + kOffB3);
-    MESS_TRY((gemm16<false, false, kEpiBackHidden>(s, nn, kHid, kOut, L->dYb, kOut, W3, kHid, nullptr, L->Z2, L->dZ2,
-                                                   L->dZ2b, kHid)));
-    // layer 2
-    MESS_TRY((gemm16<true, false, kEpiAtomic>(s, kHid, kHid, nn, L->dZ2b, kHid, L->H1b, kHid, nullptr, nullptr,
-                                              L->g + kOffW2, nullptr, kHid)));
-    hipLaunchKernelGGL(k_colsum, dim3(1, ry), dim3(kHid), 0, s, n, kHid, rows_per, L->dZ2, L->g + kOffB2);
-    MESS_TRY((gemm16<false, false, kEpiBackHidden>(s, nn, kHid, kHid, L->dZ2b, kHid, W2, kHid, nullptr, L->Z1,
-                                                   L->dZ1, L->dZ1b, kHid)));
-    // layer 1
-    MESS_TRY((gemm16<true, false, kEpiAtomic>(s, kHid, kIn, nn, L->dZ1b, kHid, L->Xb, kIn, nullptr, nullptr,
-                                              L->g + kOffW1, nullptr, kIn)));
-    hipLaunchKernelGGL(k_colsum, dim3(1, ry), dim3(kHid), 0, s, n, kHid, rows_per, L->dZ1, L->g + kOffB1);
+    // rows in steps of 16, to a whole block of the row kernel
+    const int64_t ns = n <= 256 * 16 ? (n + 15) / 16 : (n + 31) / 32 * 2;
+    unsigned short *f = L->frags;
+    auto take = [&](int cols) {
+        unsigned short *q = f;
+        f += ns * 16 * cols;
+        return q;
+    };
+    RowFrags fr;
+    fr.X = take(kIn);
+    fr.H1 = take(kHid);
+    fr.H2 = take(kHid);
+    fr.dY = take(kOut);
+    fr.dZ2 = take(kHid);
+    fr.dZ1 = take(kHid);
+    fr.ns = ns;
+    int nrow = 0;
+    hipLaunchKernelGGL(k_mask_sum, dim3(kMaskBlocks), dim3(256), 0, s, n * kOut, M, L->mpart);
+    MESS_TRY(mlp_rows<true>(L, n, X, nullptr, T, M, fr, &nrow, s));
+    // chunks of at least 32 steps (512 rows)
+    int64_t nchunk = std::max<int64_t>(1, std::min<int64_t>(ns / 32, kMaxChunks));
+    const int64_t per = (ns + nchunk - 1) / nchunk;
+    nchunk = (ns + per - 1) / per;
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(28, (unsigned)nchunk), dim3(256), 0, s, fr, per, L->wpart);
+    const dim3 fg(kFinishW + kFinishB + 1);
+    if (ad)
+        hipLaunchKernelGGL(k_mlp_finish<true>, fg, dim3(256), 0, s, (int)nchunk, L->wpart, nrow, L->bpart, L->lpart,
+                           L->mpart, L->loss, nullptr, *ad);
+    else
+        hipLaunchKernelGGL(k_mlp_finish<false>, fg, dim3(256), 0, s, (int)nchunk, L->wpart, nrow, L->bpart, L->lpart,
+                           L->mpart, L->loss, g, AdamArgs{});
     MESS_LAUNCH_CHECK();
     return MESS_OK;
 }
 
 static void free_mlp(mess_mlp *L) {
     if (!L) return;
-    free_ws(L);
-    for (void *q : {(void *)L->p, (void *)L->m, (void *)L->v, (void *)L->g, (void *)L->pb, (void *)L->msum,
-                    (void *)L->part, (void *)L->loss})
+    for (void *q : {(void *)L->p, (void *)L->m, (void *)L->v, (void *)L->pk, (void *)L->frags, (void *)L->wpart,
+                    (void *)L->bpart, (void *)L->mpart, (void *)L->lpart, (void *)L->loss})
         hipFree(q);
     delete L;
 }
 
 static int check_rows(int64_t n, const char *who) {
-    // grid.y = rows / 64 must stay below 65536
     if (n <= 0 || n > (int64_t)1 << 21) {
         set_error("%s: row count %lld out of range (1 .. 2^21)", who, (long long)n);
         return MESS_E_ARG;
@@ -588,16 +746,17 @@ int mess_mlp_create(const float *params, mess_mlp **out) {
     al((void **)&L->p, 4 * kNParam);
     al((void **)&L->m, 4 * kNParam);
     al((void **)&L->v, 4 * kNParam);
-    al((void **)&L->g, 4 * kNParam);
-    al((void **)&L->pb, 2 * kNParam);
-    al((void **)&L->msum, 4);
-    al((void **)&L->part, 8 * kMseBlocks);
+    al((void **)&L->pk, 2 * kNPacked);
+    al((void **)&L->wpart, 4 * kMaxChunks * kNParam);
+    al((void **)&L->bpart, 4 * kRowBlocksMax * kBias);
+    al((void **)&L->mpart, 8 * kMaskBlocks);
+    al((void **)&L->lpart, 8 * kRowBlocksMax);
     al((void **)&L->loss, 8);
     if (e == hipSuccess) e = hipMemcpy(L->p, params, 4 * kNParam, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(L->m, 0, 4 * kNParam);
     if (e == hipSuccess) e = hipMemset(L->v, 0, 4 * kNParam);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_to_bf16, dim3(g1(kNParam)), dim3(256), 0, nullptr, (int64_t)kNParam, L->p, L->pb);
+        hipLaunchKernelGGL(k_pack, dim3((unsigned)((kNParam + 255) / 256)), dim3(256), 0, nullptr, L->p, L->pk);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -639,8 +798,7 @@ int mess_mlp_grad(mess_mlp *mlp, int64_t n, const float *X, const float *T, cons
     }
     MESS_TRY(check_rows(n, "mess_mlp_grad"));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    MESS_TRY(mlp_grad(mlp, n, X, T, M, s));
-    if (grad) MESS_HIP(hipMemcpyAsync(grad, mlp->g, 4 * kNParam, hipMemcpyDeviceToDevice, s));
+    MESS_TRY(mlp_grad(mlp, n, X, T, M, grad, nullptr, s));
     if (loss) {
         MESS_HIP(hipMemcpyAsync(loss, mlp->loss, 8, hipMemcpyDeviceToHost, s));
         MESS_HIP(hipStreamSynchronize(s));
@@ -656,13 +814,10 @@ int mess_mlp_train_step(mess_mlp *mlp, int64_t n, const float *X, const float *T
     }
     MESS_TRY(check_rows(n, "mess_mlp_train_step"));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    MESS_TRY(mlp_grad(mlp, n, X, T, M, s));
+    const float b1 = 0.9f, b2 = 0.999f, t = (float)(mlp->t + 1);
+    const AdamArgs ad{mlp->p, mlp->m, mlp->v, mlp->pk, lr, b1, b2, 1e-8f, 1.0f - std::pow(b1, t), 1.0f - std::pow(b2, t)};
+    MESS_TRY(mlp_grad(mlp, n, X, T, M, nullptr, &ad, s));
     mlp->t += 1;
-    const float b1 = 0.9f, b2 = 0.999f;
-    const float c1 = 1.0f - std::pow(b1, (float)mlp->t), c2 = 1.0f - std::pow(b2, (float)mlp->t);
-    hipLaunchKernelGGL(k_adam, dim3(g1(kNParam)), dim3(256), 0, s, (int64_t)kNParam, mlp->p, mlp->m, mlp->v, mlp->g,
-                       lr, b1, b2, 1e-8f, c1, c2, mlp->pb);
-    MESS_LAUNCH_CHECK();
     if (loss) {
         MESS_HIP(hipMemcpyAsync(loss, mlp->loss, 8, hipMemcpyDeviceToHost, s));
         MESS_HIP(hipStreamSynchronize(s));

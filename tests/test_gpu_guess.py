@@ -135,6 +135,39 @@ def test_gradient_matches_bf16_oracle():
     assert np.dot(gg, gexact) > 0.9 * np.linalg.norm(gg) * np.linalg.norm(gexact)
 
 
+@pytest.mark.parametrize("n", [1, 15, 17, 33, 4096, 4097, 4130])
+def test_gradient_row_edges(n):
+    """Row counts at the edges of the row kernel's tiles (16 rows to 4096, 32
+    above) and of the weight gradient's chunks: gradient and loss against the
+    oracle, and the forward of the parameters that one training step leaves
+    (whose packed copies the step writes).  A hidden activation that rounds
+    the other way moves what it feeds by 2^-8 of itself, so no element is off
+    by more than two of those of the largest; the bulk by FP32 summation."""
+    mess = need_gpu()
+    p, X, T, M = _data(n, seed=n)
+    M[0, 0] = 1.0
+    mlp = mess.Mlp(p)
+    g = torch.zeros(mess.MESS_MLP_NPARAM, dtype=torch.float32, device="cuda")
+    loss = mlp.grad(f32dev(X), f32dev(T), f32dev(M), g)
+    Lr, gr = og.loss_and_grad_bf16(p.astype(np.float64), X.astype(np.float64), T.astype(np.float64),
+                                   M.astype(np.float64))
+    gg = g.cpu().numpy().astype(np.float64)
+    assert abs(loss - Lr) <= 2.0 ** -7 * Lr
+    offs = np.cumsum([0] + [int(np.prod(s)) for s in og.SHAPES])
+    for t in range(6):
+        a, b = offs[t], offs[t + 1]
+        e, sc = np.abs(gg[a:b] - gr[a:b]), np.abs(gr[a:b]).max()
+        assert np.median(e) <= 1e-4 * sc and e.max() <= 2.0 ** -7 * sc, (t, e.max() / sc)
+    mlp.train_step(f32dev(X), f32dev(T), f32dev(M), lr=1e-3, want_loss=False)
+    p1 = mlp.params()
+    assert np.abs(p1 - p).max() <= 1.001e-3 and np.abs(p1 - p).max() > 0
+    Y = torch.zeros(n, 128, dtype=torch.float32, device="cuda")
+    mlp.forward(f32dev(X), Y)
+    ref, _ = og.forward_bf16(p1.astype(np.float64), X.astype(np.float64))
+    err = np.abs(Y.cpu().numpy() - ref)
+    assert np.median(err) <= 1e-6 * np.abs(ref).max() and err.max() <= 2.0 ** -7 * np.abs(ref).max()
+
+
 def test_adam_step_and_training_lowers_loss():
     mess = need_gpu()
     p, X, T, M = _data()
