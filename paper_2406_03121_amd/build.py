@@ -70,6 +70,10 @@ def _units():
             for cb, ck in UNROLLED_CLASSES:
                 units.append((src, os.path.join(OBJ, f"eri_class_{cb}{ck}.o"),
                               [f"-DMESS_CB={cb}", f"-DMESS_CK={ck}"]))
+        elif name == "grad_class":
+            for cb, ck in CLASSES:
+                units.append((src, os.path.join(OBJ, f"grad_class_{cb}{ck}.o"),
+                              [f"-DMESS_GCB={cb}", f"-DMESS_GCK={ck}"]))
         elif name == "wave":
             for cb, ck in WAVE_CLASSES:
                 for real in ("double", "float"):

@@ -574,6 +574,8 @@ static void free_basis(mess_basis *B) {
     free_xc(B);
     void free_guess_tables(mess_basis *);
     free_guess_tables(B);
+    void free_grad(mess_basis *);
+    free_grad(B);
     hipFree(B->d_xyz);
     hipFree(B->d_Zd);
     hipFree(B->d_boys);

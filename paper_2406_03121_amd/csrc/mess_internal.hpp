@@ -284,4 +284,6 @@ struct mess_basis {
     void *det_acc = nullptr;      // deterministic J/K: 128-bit accumulators (built on first use)
     void *xc = nullptr;           // LDA grid and basis values (built on first use)
     void *guess = nullptr;        // learned-guess pair tables (built on first use)
+    void *grad_ws = nullptr;      // workspace of the nuclear gradient (built on first use)
+    size_t grad_ws_bytes = 0;
 };
