@@ -17,12 +17,13 @@
 // transposed, PhiT[mu][g] with G (the point count rounded up to 64)
 // contiguous, so that the basis-value kernel writes coalesced rows and both
 // contractions stream G-contiguous tiles.  Both are built once per basis.
-// Per density: one kernel forms U = D PhiT on a 64-point tile, chunk by
-// chunk of 64 rows, and reduces rho_g = sum_nu PhiT[nu][g] U[nu][g] in the
-// same pass (2 N^2 flops per point), then the weights f_g = w_g v_x(rho_g);
-// a second kernel forms V_x = PhiT diag(f) PhiT^T on 64 x 64 tiles of the
-// upper block triangle over chunks of points, adding tile partials into
-// V_x with FP64 atomics (2 N^2 flops per point in all).
+// Per density, both contractions on the FP64 matrix cores: one kernel forms
+// U = D PhiT for a tile of points held in LDS and reduces rho_g = sum_nu
+// PhiT[nu][g] U[nu][g] in the same pass (with D + D^T above the diagonal
+// blocks and nothing below: N^2 flops per point), then the weights f_g = w_g
+// v_x(rho_g); a second kernel forms V_x = PhiT diag(f) PhiT^T on 64 x 64
+// tiles of the upper block triangle over chunks of points (N^2 flops per
+// point), whose partial sums are added in a fixed order.
 //
 // PBE exchange-correlation (the generalised-gradient functional the paper
 // selects for its DFT examples, section 5), closed shell, on the same grid:
@@ -38,7 +39,9 @@
 // dPhiT (rho and grad rho in one pass, 2 N^2 + 6 N flops per point), the
 // functional per point, and V_xc = PhiT Z^T + Z PhiT^T with
 // Z[nu][g] = w (f_rho/2 phi_nu + 2 f_sigma grad rho . grad phi_nu) formed
-// while the tiles are staged (all tile pairs, 2 N^2 flops per point).
+// while the tiles are staged (all tile pairs, 2 N^2 flops per point; at a
+// hundred functions both passes are bound by the 32 bytes per function and
+// point that they read).
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -50,9 +53,7 @@ namespace mess {
 
 constexpr int kNRad = 75, kNTheta = 17, kNPhi = 34, kNAng = kNTheta * kNPhi;
 constexpr int kPtsPerAtom = kNRad * kNAng;
-constexpr int kXT = 64;      // tile edge of both contractions
-constexpr int kXK = 16;      // contraction step staged in LDS
-constexpr int kVChunk = 32768;  // points per V_x partial
+constexpr int kXT = 64;      // points are padded to a multiple of this; edge of a V_x tile
 
 struct XcShell {
     double x, y, z;
@@ -61,7 +62,7 @@ struct XcShell {
 
 struct XcGrid {
     int64_t npts = 0, G = 0;
-    int nbf = 0, nrho_blocks = 0;
+    int nbf = 0;
     double *dphiT = nullptr;  // [3][nbf][G] basis gradients (PBE only)
     double *grad = nullptr;   // [3][G] grad rho (PBE)
     double *hv = nullptr;     // [3][G] 2 w f_sigma grad rho (PBE)
@@ -69,7 +70,11 @@ struct XcGrid {
     double *phiT = nullptr;   // [nbf][G]
     double *f = nullptr;      // [G] w_g v_x(rho_g)
     double *rho = nullptr;    // [G]
-    double *epart = nullptr;  // [nrho_blocks] partial sums of w_g e_x
+    double *epart = nullptr;  // [G / 16] partial sums of w_g e_x
+    double *Dp = nullptr;     // D in fragment order
+    double *vpart = nullptr;  // partial sums of V_x tiles
+    size_t vpart_n = 0;       // doubles it holds
+    int4 *groups = nullptr;   // V_x tile groups (VGroup), LDA then PBE
     double *ex = nullptr;     // [1] E_x of the last build
     double *Vacc = nullptr;   // [nbf][nbf] accumulation of the upper block triangle
 };
@@ -77,7 +82,10 @@ struct XcGrid {
 void free_xc(mess_basis *B) {
     XcGrid *X = static_cast<XcGrid *>(B->xc);
     if (!X) return;
-    for (double *p : {X->xyzw, X->phiT, X->f, X->rho, X->epart, X->ex, X->Vacc, X->dphiT, X->grad, X->hv}) hipFree(p);
+    for (double *p : {X->xyzw, X->phiT, X->f, X->rho, X->epart, X->ex, X->Vacc, X->dphiT, X->grad, X->hv, X->Dp,
+                      X->vpart})
+        hipFree(p);
+    hipFree(X->groups);
     delete X;
     B->xc = nullptr;
 }
@@ -275,148 +283,354 @@ __device__ __forceinline__ void exchange_terms(double rho, double &ex, double &v
     }
 }
 
-// rho over a 64-point tile: U = D PhiT[:, tile] by 64-row chunks (4 x 4
-// register blocking per thread, K staged through LDS), rho_g accumulated
-// from the chunk and PhiT; then f_g and the block's partial sum of w e_x.
-__global__ void __launch_bounds__(256) k_lda_rho(int N, int64_t G, const double *__restrict__ D,
-                                                 const double *__restrict__ phiT, const double *__restrict__ xyzw,
-                                                 double *__restrict__ rho_out, double *__restrict__ f,
-                                                 double *__restrict__ epart) {
-    __shared__ double As[kXK][kXT + 1];
-    __shared__ double Bs[kXK][kXT + 1];
-    __shared__ double red[16][kXT + 1];
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int64_t g0 = (int64_t)blockIdx.x * kXT;
-    double part[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int nu0 = 0; nu0 < N; nu0 += kXT) {
-        double acc[4][4] = {};
-        for (int k0 = 0; k0 < N; k0 += kXK) {
-            for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-                const int kk = t % kXK, mm = t / kXK;  // D rows, K contiguous
-                const int r = nu0 + mm, k = k0 + kk;
-                As[kk][mm] = (r < N && k < N) ? D[(int64_t)r * N + k] : 0.0;
-            }
-            for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-                const int kk = t / kXT, nn = t % kXT;  // PhiT rows, points contiguous
-                const int k = k0 + kk;
-                Bs[kk][nn] = k < N ? phiT[(int64_t)k * G + g0 + nn] : 0.0;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int kk = 0; kk < kXK; ++kk) {
-                double a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-            }
-            __syncthreads();
+typedef double xc_d4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ xc_d4 xc_mfma(double a, double b, xc_d4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// v_mfma_f64_16x16x4 takes A[l % 16][l / 16] and B[l / 16][l % 16] from lane
+// l and returns C[l / 16 + 4 q][l % 16] in element q.  D in that order:
+// Dp[row tile][k / 4][lane].  TRI: tiles above the diagonal hold D + D^T (the
+// ones below are not read).
+template <bool TRI>
+__global__ void k_xc_pack_d(int N, int T, const double *__restrict__ D, double *__restrict__ Dp) {
+    const int64_t n = (int64_t)T * T * 256;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        const int l = (int)(e % 64), ks = (int)(e / 64 % (4 * T)), i = (int)(e / 64 / (4 * T));
+        const int r = 16 * i + l % 16, k = 4 * ks + l / 16;
+        double v = 0.0;
+        if (r < N && k < N) {
+            v = D[(int64_t)r * N + k];
+            if (TRI && ks / 4 > i) v += D[(int64_t)k * N + r];
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int nu = nu0 + ty + 16 * i;
-            if (nu >= N) continue;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) part[j] = fma(phiT[(int64_t)nu * G + g0 + tx + 16 * j], acc[i][j], part[j]);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[ty][tx + 16 * j] = part[j];
-    __syncthreads();
-    double e = 0.0;
-    if (threadIdx.x < kXT) {
-        const int c = threadIdx.x;
-        double r = 0.0;
-        for (int k = 0; k < 16; ++k) r += red[k][c];
-        const int64_t g = g0 + c;
-        const double w = xyzw[4 * g + 3];
-        double ex, vx;
-        exchange_terms(r, ex, vx);
-        rho_out[g] = r;
-        f[g] = w * vx;
-        e = w * ex;
-    }
-    __syncthreads();
-    // block sum of w e_x (fixed order)
-    if (threadIdx.x < kXT) red[0][threadIdx.x] = e;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int c = 0; c < kXT; ++c) s += red[0][c];
-        epart[blockIdx.x] = s;
+        Dp[e] = v;
     }
 }
 
-__global__ void __launch_bounds__(256) k_sum_partials(int n, const double *__restrict__ part, double *__restrict__ out) {
-    __shared__ double red[256];
+// rho (and, GGA, grad rho) over PT points: the basis values of the tile lie in
+// LDS ([row][point], points of odd rows exchanged between halves so that the
+// four rows of a B operand fall on all banks), a wave takes row tiles of 16
+// and streams its rows of D from the L2 in fragment order, four products of
+// 16 points an operand.  Bound by the FP64 matrix rate for LDA (the local part needs
+// only the upper block triangle: N^2 flops per point) and by the three
+// gradient planes read from memory for GGA at small N.  60-atom cluster, 300
+// functions (LDA): 17.7 ms on vector FMAs with the whole product, 4.85 here
+// (52 TFLOP/s of the matrix unit with the blocks' padding).  Rows beyond one LDS
+// panel (RC rows) are taken by pairs of panels.  LDA also leaves f_g and the
+// block's sum of w e_x.
+template <bool GGA, int PT>
+__global__ void __launch_bounds__(512) k_xc_rho(int N, int64_t G, int TC, const double *__restrict__ Dp,
+                                                const double *__restrict__ phiT, const double *__restrict__ dphiT,
+                                                const double *__restrict__ xyzw, double *__restrict__ rho_out,
+                                                double *__restrict__ grad_out, double *__restrict__ f,
+                                                double *__restrict__ epart) {
+    constexpr int NC = PT / 16, NQ = GGA ? 4 : 1;
+    extern __shared__ double xlds[];
+    const int T = (N + 15) / 16, W = blockDim.x / 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t g0 = blockIdx.x * (int64_t)PT, plane = (int64_t)N * G;
+    const bool one = TC >= T;
+    double *const pa = xlds, *const pb = one ? xlds : xlds + 16 * TC * PT;
+    auto at = [](int row, int pt) { return row * PT + (PT >= 32 ? pt ^ ((row & 1) << 4) : pt); };
+    auto load = [&](double *p, int r0, int rows) {
+        for (int e = threadIdx.x; e < rows * (PT / 2); e += blockDim.x) {
+            const int r = e / (PT / 2), c = 2 * (e % (PT / 2));
+            double2 v = make_double2(0.0, 0.0);
+            if (r0 + r < N) v = *reinterpret_cast<const double2 *>(phiT + (int64_t)(r0 + r) * G + g0 + c);
+            *reinterpret_cast<double2 *>(p + at(r, c)) = v;
+        }
+    };
+    double part[NQ][NC];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) part[q][c] = 0.0;
+    for (int ta = 0; ta < T; ta += TC) {
+        const int na = min(TC, T - ta);
+        __syncthreads();
+        load(pa, 16 * ta, 16 * na);
+        for (int tb = GGA ? 0 : ta; tb < T; tb += TC) {
+            const int nb = min(TC, T - tb);
+            if (!one) {
+                __syncthreads();
+                load(pb, 16 * tb, 16 * nb);
+            }
+            __syncthreads();
+            for (int j = 0;; ++j) {
+                // row tiles dealt to the waves forwards and backwards (the triangle's rows shorten)
+                const int ir = j * W + ((j & 1) ? W - 1 - wave : wave);
+                if (j * W >= na) break;
+                if (ir >= na) continue;
+                const int i = ta + ir, kt0 = GGA || tb > ta ? 0 : ir;
+                xc_d4 acc[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[c] = xc_d4{0.0, 0.0, 0.0, 0.0};
+                const double *dp = Dp + ((int64_t)i * 4 * T + 4 * tb) * 64 + lane;
+                double a[4], an[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) an[k] = dp[(4 * kt0 + k) * 64];
+                for (int kt = kt0; kt < nb; ++kt) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) a[k] = an[k];
+                    if (kt + 1 < nb)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) an[k] = dp[(4 * (kt + 1) + k) * 64];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int row = 16 * kt + 4 * k + lane / 16;
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) acc[c] = xc_mfma(a[k], pb[at(row, 16 * c + lane % 16)], acc[c]);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int row = 16 * ir + lane / 16 + 4 * q;
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        part[0][c] = fma(pa[at(row, 16 * c + lane % 16)], acc[c][q], part[0][c]);
+                        if constexpr (GGA) {
+                            const int mu = 16 * ta + row;
+                            const int64_t o = (int64_t)mu * G + g0 + 16 * c + lane % 16;
+                            if (mu < N)
+#pragma unroll
+                                for (int k = 0; k < 3; ++k) part[1 + k][c] = fma(dphiT[k * plane + o], acc[c][q], part[1 + k][c]);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();  // the panels give way to the waves' sums
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            double v = part[q][c];
+            v += __shfl_xor(v, 16, 64);
+            v += __shfl_xor(v, 32, 64);
+            if (lane < 16) xlds[(q * W + wave) * PT + 16 * c + lane] = v;
+        }
+    __syncthreads();
+    double e = 0.0;
+    if (threadIdx.x < PT) {
+        const int64_t g = g0 + threadIdx.x;
+        double r[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            r[q] = 0.0;
+            for (int w = 0; w < W; ++w) r[q] += xlds[(q * W + w) * PT + threadIdx.x];
+        }
+        rho_out[g] = r[0];
+        if constexpr (GGA) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) grad_out[k * G + g] = 2.0 * r[1 + k];
+        } else {
+            const double w = xyzw[4 * g + 3];
+            double ex, vx;
+            exchange_terms(r[0], ex, vx);
+            f[g] = w * vx;
+            e = w * ex;
+        }
+    }
+    if constexpr (!GGA) {
+        // block sum of w e_x: the first wave holds all points
+        if (wave == 0) {
+            for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o, 64);
+            if (lane == 0) epart[blockIdx.x] = e;
+        }
+    }
+}
+
+__global__ void __launch_bounds__(1024) k_sum_partials(int n, const double *__restrict__ part, double *__restrict__ out) {
+    __shared__ double red[1024];
     double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) s += part[i];
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n; i += 1024) s += part[i];
     red[threadIdx.x] = s;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
+    for (int st = 512; st > 0; st >>= 1) {
         if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
         __syncthreads();
     }
     if (threadIdx.x == 0) out[0] = red[0];
 }
 
-// Vacc[mu][nu] += sum_{g in chunk} PhiT[mu][g] f_g PhiT[nu][g] for the tile
-// pair (bi <= bj) given by blockIdx.y; blockIdx.x is the point chunk.
-__global__ void __launch_bounds__(256) k_lda_v(int N, int64_t G, int nblk, const double *__restrict__ phiT,
-                                               const double *__restrict__ f, double *__restrict__ Vacc) {
-    __shared__ double As[kXK][kXT + 1];
-    __shared__ double Bs[kXK][kXT + 1];
-    int bi = 0, rem = blockIdx.y;
-    while (rem >= nblk - bi) {
-        rem -= nblk - bi;
-        ++bi;
+// A group of up to 8 tiles of 64 x 64 of V, one a wave, and the row blocks of
+// 64 that they read: blocks of the left factor, then of the right one.
+struct VGroup {
+    int nsup, na, nb, first;  // tiles, row blocks, index of the first tile
+    int a[12], b[12];         // row blocks (left, right)
+    int ai[8], bj[8];         // a tile's positions among them
+};
+static_assert(sizeof(VGroup) % sizeof(int4) == 0, "VGroup is copied as int4");
+
+// pairs of points that a thread loads per step, left and right rows
+template <bool GGA>
+inline constexpr int kVLoadA = GGA ? 2 : 5;
+constexpr int kVLoadB = 4;
+
+// Partial sums over a chunk of points of the tiles (bi, bj) of a group:
+//   LDA: sum_g PhiT[mu][g] f_g PhiT[nu][g], bi <= bj;
+//   GGA: sum_g PhiT[mu][g] Z[nu][g], Z[nu][g] = f_g PhiT[nu][g] + hv[.][g] . dPhiT[.][nu][g],
+// a wave per tile with 4 x 4 products of 16 x 16 in its accumulators.  Steps
+// of KP points of the group's rows are staged in LDS ([row][point] with the
+// points of a row permuted in fours, so that 16 rows x 4 points fall on all
+// banks), the next step's values on their way meanwhile; every tile of a row
+// block shares them, which keeps the reads of PhiT near one (LDA: the 15
+// tiles of 300 functions are two groups).  Bound by the FP64 matrix rate, and
+// for GGA at small N by the four planes read.  60-atom cluster, 2.6e6 points
+// x 300 functions (LDA): 13.8 ms on vector FMAs with atomic partial sums, 5.2
+// here; 21 atoms x 105 functions (PBE): 10.4 (112 blocks) and 1.2.
+template <bool GGA, int KP>
+__global__ void __launch_bounds__(512) k_xc_v(int N, int64_t G, int64_t chunk, const double *__restrict__ phiT,
+                                              const double *__restrict__ dphiT, const double *__restrict__ f,
+                                              const double *__restrict__ hv, const VGroup *__restrict__ groups,
+                                              int ntile, double *__restrict__ vpart) {
+    constexpr int NPA = kVLoadA<GGA>, NPB = GGA ? kVLoadB : 1;  // pairs of points a thread has on their way
+    extern __shared__ double xlds[];
+    const VGroup &gr = groups[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nthr = blockDim.x;
+    const int ra = 64 * gr.na, rb = GGA ? 64 * gr.nb : 0, rows = ra + rb;
+    const int64_t plane = (int64_t)N * G, gs = blockIdx.x * chunk, ge = gs + chunk < G ? gs + chunk : G;
+    double *const fl = xlds + 2 * rows * KP;  // LDA: f of the step's points, two buffers
+    const int na2 = ra * (KP / 2), nb2 = rb * (KP / 2);
+    auto at = [](int row, int pt) { return row * KP + (pt ^ (((row / (32 / KP)) % (KP / 4)) * 4)); };
+    // a thread's rows (function index, -1 beyond the last) and its pair of points
+    int mua[NPA], mub[NPB];
+#pragma unroll
+    for (int i = 0; i < NPA; ++i) {
+        const int r = (threadIdx.x + i * nthr) / (KP / 2);
+        const int mu = r < ra ? 64 * gr.a[r / 64] + r % 64 : N;
+        mua[i] = mu < N ? mu : -1;
     }
-    const int bj = bi + rem;
-    const int row0 = bi * kXT, col0 = bj * kXT;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int64_t gs = (int64_t)blockIdx.x * kVChunk;
-    const int64_t ge = gs + kVChunk < G ? gs + kVChunk : G;
-    double acc[4][4] = {};
-    for (int64_t k0 = gs; k0 < ge; k0 += kXK) {
-        for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-            const int kk = t % kXK, mm = t / kXK;
-            const int r = row0 + mm;
-            As[kk][mm] = r < N ? phiT[(int64_t)r * G + k0 + kk] : 0.0;
+    if constexpr (GGA)
+#pragma unroll
+        for (int i = 0; i < NPB; ++i) {
+            const int r = (threadIdx.x + i * nthr) / (KP / 2);
+            const int mu = r < rb ? 64 * gr.b[r / 64] + r % 64 : N;
+            mub[i] = mu < N ? mu : -1;
         }
-        for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-            const int kk = t % kXK, nn = t / kXK;
-            const int c = col0 + nn;
-            Bs[kk][nn] = c < N ? f[k0 + kk] * phiT[(int64_t)c * G + k0 + kk] : 0.0;
+    const int c2 = 2 * (threadIdx.x % (KP / 2));
+    double2 va[NPA], vb[NPB];
+    double fv = 0.0;
+    auto fetch = [&](int64_t g0) {
+#pragma unroll
+        for (int i = 0; i < NPA; ++i)
+            va[i] = mua[i] >= 0 ? *reinterpret_cast<const double2 *>(phiT + (int64_t)mua[i] * G + g0 + c2) : make_double2(0.0, 0.0);
+        if constexpr (GGA) {
+            const double2 w = *reinterpret_cast<const double2 *>(f + g0 + c2);
+            double2 h[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) h[k] = *reinterpret_cast<const double2 *>(hv + k * G + g0 + c2);
+#pragma unroll
+            for (int i = 0; i < NPB; ++i) {
+                double2 z = make_double2(0.0, 0.0);
+                if (mub[i] >= 0) {
+                    const int64_t o = (int64_t)mub[i] * G + g0 + c2;
+                    const double2 p = *reinterpret_cast<const double2 *>(phiT + o);
+                    z.x = w.x * p.x;
+                    z.y = w.y * p.y;
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const double2 d = *reinterpret_cast<const double2 *>(dphiT + k * plane + o);
+                        z.x += h[k].x * d.x;
+                        z.y += h[k].y * d.y;
+                    }
+                }
+                vb[i] = z;
+            }
+        } else if (threadIdx.x < KP) {
+            fv = f[g0 + threadIdx.x];
         }
+    };
+    auto put = [&](int buf) {
+        double *p = xlds + buf * rows * KP;
+#pragma unroll
+        for (int i = 0; i < NPA; ++i) {
+            const int e = threadIdx.x + i * nthr;
+            if (e < na2) *reinterpret_cast<double2 *>(p + at(e / (KP / 2), 2 * (e % (KP / 2)))) = va[i];
+        }
+        if constexpr (GGA) {
+#pragma unroll
+            for (int i = 0; i < NPB; ++i) {
+                const int e = threadIdx.x + i * nthr;
+                if (e < nb2) *reinterpret_cast<double2 *>(p + at(ra + e / (KP / 2), 2 * (e % (KP / 2)))) = vb[i];
+            }
+        } else if (threadIdx.x < KP) {
+            fl[buf * KP + threadIdx.x] = fv;
+        }
+    };
+    const bool work = wave < gr.nsup;
+    const int ai = work ? gr.ai[wave] : 0, bj = work ? gr.bj[wave] : 0;
+    const bool diag = !GGA && ai == bj;
+    const int ar = 64 * ai + lane % 16, br = (GGA ? ra : 0) + 64 * bj + lane % 16;
+    xc_d4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = xc_d4{0.0, 0.0, 0.0, 0.0};
+    fetch(gs);
+    put(0);
+    __syncthreads();
+    int buf = 0;
+    for (int64_t g0 = gs; g0 < ge; g0 += KP, buf ^= 1) {
+        const bool more = g0 + KP < ge;
+        if (more) fetch(g0 + KP);
+        if (work) {
+            const double *p = xlds + buf * rows * KP;
+#pragma unroll
+            for (int k = 0; k < KP / 4; ++k) {
+                const int pt = 4 * k + lane / 16;
+                double a[4], b[4];
+                const double fk = GGA ? 1.0 : fl[buf * KP + pt];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    a[i] = p[at(ar + 16 * i, pt)];
+                    b[i] = GGA ? p[at(br + 16 * i, pt)] : fk * p[at(br + 16 * i, pt)];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (!(diag && j < i)) acc[i][j] = xc_mfma(a[i], b[j], acc[i][j]);
+            }
+        }
+        if (more) put(buf ^ 1);
         __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < kXK; ++kk) {
-            double a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
     }
+    if (!work) return;
+    double *o = vpart + ((int64_t)blockIdx.x * ntile + gr.first + wave) * (kXT * kXT);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + ty + 16 * i;
-        if (r >= N) continue;
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = col0 + tx + 16 * j;
-            if (c < N) unsafeAtomicAdd(&Vacc[(int64_t)r * N + c], acc[i][j]);
-        }
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[(16 * i + lane / 16 + 4 * q) * kXT + 16 * j + lane % 16] = acc[i][j][q];
+}
+
+// Vacc <- the tiles' partial sums over the chunks, a block per 64 elements of
+// a tile (four shares of the chunks, added in order).
+template <bool GGA>
+__global__ void __launch_bounds__(256) k_xc_v_sum(int N, int nblk, int ntile, int nchunk, const double *__restrict__ vpart,
+                                                  double *__restrict__ Vacc) {
+    __shared__ double red[4][64];
+    const int tile = blockIdx.y, e = blockIdx.x * 64 + threadIdx.x % 64, w = threadIdx.x / 64;
+    double s = 0.0;
+#pragma unroll 8
+    for (int c = w; c < nchunk; c += 4) s += vpart[((int64_t)c * ntile + tile) * (kXT * kXT) + e];
+    red[w][threadIdx.x % 64] = s;
+    __syncthreads();
+    if (w) return;
+    s = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+    int bi = 0, bj = tile;
+    if (GGA) {
+        bi = tile / nblk;
+        bj = tile % nblk;
+    } else {
+        while (bj >= nblk - bi) bj -= nblk - bi, ++bi;
+        bj += bi;
     }
+    const int r = kXT * bi + e / kXT, c = kXT * bj + e % kXT;
+    if (r < N && c < N) Vacc[(int64_t)r * N + c] = s;
 }
 
 // V[i][j] from the upper triangle of Vacc (the upper block triangle was
@@ -488,77 +702,6 @@ __device__ __forceinline__ void pbe_point(double rho, double sigma, double &f, d
     fs = exs + dHdu * kCt * ir43;
 }
 
-// rho and grad rho over a 64-point tile: U = D PhiT[:, tile] by 64-row
-// chunks as in k_lda_rho, reduced against PhiT (rho) and the three basis
-// gradient planes (grad rho = 2 sum_nu dPhiT[k][nu][g] U[nu][g]).
-__global__ void __launch_bounds__(256) k_gga_rho(int N, int64_t G, const double *__restrict__ D,
-                                                 const double *__restrict__ phiT, const double *__restrict__ dphiT,
-                                                 double *__restrict__ rho_out, double *__restrict__ grad_out) {
-    __shared__ double As[kXK][kXT + 1];
-    __shared__ double Bs[kXK][kXT + 1];
-    __shared__ double red[16][kXT + 1];
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int64_t g0 = (int64_t)blockIdx.x * kXT;
-    const int64_t plane = (int64_t)N * G;
-    double part[4][4] = {};
-    for (int nu0 = 0; nu0 < N; nu0 += kXT) {
-        double acc[4][4] = {};
-        for (int k0 = 0; k0 < N; k0 += kXK) {
-            for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-                const int kk = t % kXK, mm = t / kXK;
-                const int r = nu0 + mm, k = k0 + kk;
-                As[kk][mm] = (r < N && k < N) ? D[(int64_t)r * N + k] : 0.0;
-            }
-            for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-                const int kk = t / kXT, nn = t % kXT;
-                const int k = k0 + kk;
-                Bs[kk][nn] = k < N ? phiT[(int64_t)k * G + g0 + nn] : 0.0;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int kk = 0; kk < kXK; ++kk) {
-                double a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int nu = nu0 + ty + 16 * i;
-            if (nu >= N) continue;
-            const int64_t o = (int64_t)nu * G + g0 + tx;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                part[0][j] = fma(phiT[o + 16 * j], acc[i][j], part[0][j]);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) part[1 + k][j] = fma(dphiT[k * plane + o + 16 * j], acc[i][j], part[1 + k][j]);
-            }
-        }
-    }
-    // fixed-order reductions over the 16 row groups, one quantity at a time
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) red[ty][tx + 16 * j] = part[q][j];
-        __syncthreads();
-        if (threadIdx.x < kXT) {
-            double r = 0.0;
-            for (int k = 0; k < 16; ++k) r += red[k][threadIdx.x];
-            const int64_t g = g0 + threadIdx.x;
-            if (q == 0) rho_out[g] = r;
-            else grad_out[(q - 1) * G + g] = 2.0 * r;
-        }
-        __syncthreads();
-    }
-}
-
 // The functional per point: energy partial sums per 256-point block (fixed
 // order), f_g = w f_rho / 2 and hv[k][g] = 2 w f_sigma d_k rho.
 __global__ void __launch_bounds__(256) k_pbe_point(int64_t G, const double *__restrict__ xyzw,
@@ -589,62 +732,6 @@ __global__ void __launch_bounds__(256) k_pbe_point(int64_t G, const double *__re
     if (threadIdx.x == 0) epart[blockIdx.x] = red[0];
 }
 
-// Vacc[mu][nu] += sum_{g in chunk} PhiT[mu][g] Z[nu][g] for every tile pair
-// (bi, bj) = blockIdx.y, with Z[nu][g] = f_g PhiT[nu][g] + hv[.][g] . dPhiT[.][nu][g]
-// formed as the tile is staged; V = Vacc + Vacc^T afterwards.
-__global__ void __launch_bounds__(256) k_gga_v(int N, int64_t G, int nblk, const double *__restrict__ phiT,
-                                               const double *__restrict__ dphiT, const double *__restrict__ f,
-                                               const double *__restrict__ hv, double *__restrict__ Vacc) {
-    __shared__ double As[kXK][kXT + 1];
-    __shared__ double Bs[kXK][kXT + 1];
-    const int bi = blockIdx.y / nblk, bj = blockIdx.y % nblk;
-    const int row0 = bi * kXT, col0 = bj * kXT;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int64_t plane = (int64_t)N * G;
-    const int64_t gs = (int64_t)blockIdx.x * kVChunk;
-    const int64_t ge = gs + kVChunk < G ? gs + kVChunk : G;
-    double acc[4][4] = {};
-    for (int64_t k0 = gs; k0 < ge; k0 += kXK) {
-        for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-            const int kk = t % kXK, mm = t / kXK;
-            const int r = row0 + mm;
-            As[kk][mm] = r < N ? phiT[(int64_t)r * G + k0 + kk] : 0.0;
-        }
-        for (int t = threadIdx.x; t < kXK * kXT; t += 256) {
-            const int kk = t % kXK, nn = t / kXK;
-            const int c = col0 + nn;
-            const int64_t g = k0 + kk, o = (int64_t)c * G + g;
-            Bs[kk][nn] = c < N ? f[g] * phiT[o] + hv[g] * dphiT[o] + hv[G + g] * dphiT[plane + o] +
-                                     hv[2 * G + g] * dphiT[2 * plane + o]
-                               : 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < kXK; ++kk) {
-            double a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + ty + 16 * i;
-        if (r >= N) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = col0 + tx + 16 * j;
-            if (c < N) unsafeAtomicAdd(&Vacc[(int64_t)r * N + c], acc[i][j]);
-        }
-    }
-}
-
 // V = Vacc + Vacc^T (exactly symmetric)
 __global__ void k_gga_sym(int N, const double *__restrict__ Vacc, double *__restrict__ V) {
     const int64_t NN = (int64_t)N * N;
@@ -671,7 +758,6 @@ static int get_xc(mess_basis *B, XcGrid **out) {
     X->npts = (int64_t)B->nat * kPtsPerAtom;
     X->G = (X->npts + kXT - 1) / kXT * kXT;
     X->nbf = B->nbf;
-    X->nrho_blocks = (int)(X->G / kXT);
     // radial (r, w) and angular (ux, uy, uz, w) rules
     std::vector<double> rad(2 * kNRad), ang(4 * kNAng);
     for (int i = 1; i <= kNRad; ++i) {
@@ -715,9 +801,11 @@ static int get_xc(mess_basis *B, XcGrid **out) {
     chk(hipMalloc(&X->phiT, sizeof(double) * (size_t)X->nbf * X->G));
     chk(hipMalloc(&X->f, sizeof(double) * X->G));
     chk(hipMalloc(&X->rho, sizeof(double) * X->G));
-    chk(hipMalloc(&X->epart, sizeof(double) * X->nrho_blocks));
+    chk(hipMalloc(&X->epart, sizeof(double) * (X->G / 16)));
     chk(hipMalloc(&X->ex, sizeof(double)));
     chk(hipMalloc(&X->Vacc, sizeof(double) * (size_t)X->nbf * X->nbf));
+    const int64_t T = (X->nbf + 15) / 16;
+    chk(hipMalloc(&X->Dp, sizeof(double) * 256 * T * T));
     chk(hipMalloc(&d_rad, sizeof(double) * rad.size()));
     chk(hipMalloc(&d_ang, sizeof(double) * ang.size()));
     chk(hipMalloc(&d_alpha, sizeof(double) * np));
@@ -801,27 +889,152 @@ static int ensure_gga(mess_basis *B, XcGrid *X) {
     return MESS_OK;
 }
 
+// rho (GGA: and grad rho) of density D on the grid.
+template <bool GGA>
+static int rho_async(XcGrid *X, const double *D, hipStream_t s, int *nblocks) {
+    const int N = X->nbf, T = (N + 15) / 16;
+    hipLaunchKernelGGL(k_xc_pack_d<!GGA>, dim3((unsigned)std::min<int64_t>((int64_t)T * T, 4096)), dim3(256), 0, s, N, T, D,
+                       X->Dp);
+    // Point tile: 32, so that two blocks share a CU up to 320 rows (160 KB of
+    // LDS) and one loads its panel while the other multiplies (LDA, 300
+    // functions: 6.3 ms with 64 points and one block a CU, 4.85 with 32; PBE,
+    // 105 functions, whose gradient planes are read as rows finish: 1.25 and
+    // 0.83); 64 for LDA to 160 rows, where two such blocks fit as well and a
+    // row of D serves four products instead of two; 16 where 32 points do not
+    // fit; beyond 1280 rows, panels of 512 rows in pairs.  Few row tiles are
+    // dealt to four waves, so that the triangle's rows even out.
+    const int W = T <= 10 ? 4 : 8;
+    auto go = [&](auto PTc, int TC, int panels) {
+        constexpr int PT = decltype(PTc)::value;
+        const size_t lds = std::max(sizeof(double) * 16 * TC * PT * panels, sizeof(double) * 4 * W * PT);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_xc_rho<GGA, PT>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) (void)hipGetLastError();  // the launch itself reports a size it cannot take
+        *nblocks = (int)(X->G / PT);
+        hipLaunchKernelGGL((k_xc_rho<GGA, PT>), dim3((unsigned)*nblocks), dim3(64 * W), lds, s, N, X->G, TC, X->Dp, X->phiT,
+                           X->dphiT, X->xyzw, X->rho, X->grad, X->f, X->epart);
+    };
+    if (!GGA && T <= 10) go(std::integral_constant<int, 64>{}, T, 1);
+    else if (T <= 40) go(std::integral_constant<int, 32>{}, T, 1);
+    else if (T <= 80) go(std::integral_constant<int, 16>{}, T, 1);
+    else go(std::integral_constant<int, 16>{}, 32, 2);
+    MESS_LAUNCH_CHECK();
+    return MESS_OK;
+}
+
+// The tiles of V in groups of up to 8 (rows of tiles in order).
+static std::vector<VGroup> v_groups(int nblk, bool gga) {
+    std::vector<VGroup> out;
+    int first = 0;
+    for (int bi = 0; bi < nblk; ++bi)
+        for (int bj = gga ? 0 : bi; bj < nblk; ++bj) {
+            auto find = [](int *list, int &n, int v) {
+                for (int i = 0; i < n; ++i)
+                    if (list[i] == v) return i;
+                list[n] = v;
+                return n++;
+            };
+            if (out.empty() || out.back().nsup == 8) {
+                out.push_back(VGroup{});
+                out.back().first = first;
+            }
+            VGroup &g = out.back();
+            // LDA reads both factors from one panel
+            g.ai[g.nsup] = find(g.a, g.na, bi);
+            g.bj[g.nsup] = gga ? find(g.b, g.nb, bj) : find(g.a, g.na, bj);
+            ++g.nsup;
+            ++first;
+        }
+    return out;
+}
+
+// Vacc <- sum over the grid (k_xc_v).
+template <bool GGA>
+static int v_async(XcGrid *X, hipStream_t s) {
+    const int N = X->nbf, nblk = (N + kXT - 1) / kXT;
+    const int ntile = GGA ? nblk * nblk : nblk * (nblk + 1) / 2, ngroup = (ntile + 7) / 8;
+    if (!X->groups) {
+        const std::vector<VGroup> l = v_groups(nblk, false), g = v_groups(nblk, true);
+        // what a group's threads load in a step (see kVLoadA) covers its rows
+        bool fits = true;
+        for (const VGroup &q : l) fits &= 64 * q.na * (nblk <= 5 ? 8 : 4) <= kVLoadA<false> * 64 * std::min(8, ((int)l[0].nsup + 1) / 2 * 2);
+        for (const VGroup &q : g) {
+            const int thr = 64 * std::min(8, ((int)g[0].nsup + 1) / 2 * 2);
+            fits &= 64 * q.na * 4 <= kVLoadA<true> * thr && 64 * q.nb * 4 <= kVLoadB * thr && q.na <= 3;
+        }
+        if (!fits) {
+            set_error("internal: exchange-correlation tile groups of %d row blocks", nblk);
+            return MESS_E_ARG;
+        }
+        std::vector<VGroup> all(l);
+        all.insert(all.end(), g.begin(), g.end());
+        MESS_HIP(hipMalloc(&X->groups, sizeof(VGroup) * all.size()));
+        const hipError_t e = hipMemcpy(X->groups, all.data(), sizeof(VGroup) * all.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            hipFree(X->groups);
+            X->groups = nullptr;
+            set_error("exchange-correlation tile groups: %s", hipGetErrorString(e));
+            return MESS_E_DEVICE;
+        }
+    }
+    const VGroup *groups = reinterpret_cast<const VGroup *>(X->groups) + (GGA ? (nblk * (nblk + 1) / 2 + 7) / 8 : 0);
+    // chunks of points: two rounds of blocks where a block takes a CU's
+    // registers (8 waves), 2048 waves where it holds fewer
+    const int nw = std::min(8, (ntile + 1) / 2 * 2);
+    int64_t nchunk = std::max<int64_t>(1, nw > 4 ? 512 / ngroup : 2048 / ntile);
+    // a group reads at most 8 tiles' row blocks: all of them up to 5 blocks,
+    // at most 10 beyond (GGA: 3 left, 8 right); steps of 16 points where two
+    // buffers of their rows fit the LDS, of 8 else
+    const bool wide = !GGA && nblk <= 5;
+    const int KP = wide ? 16 : 8;
+    int64_t chunk = ((X->G + nchunk - 1) / nchunk + KP - 1) / KP * KP;
+    nchunk = (X->G + chunk - 1) / chunk;
+    const size_t need = (size_t)nchunk * ntile * kXT * kXT;
+    if (need > X->vpart_n) {
+        MESS_HIP(hipStreamSynchronize(s));
+        hipFree(X->vpart);
+        X->vpart = nullptr;
+        X->vpart_n = 0;
+        MESS_HIP(hipMalloc(&X->vpart, sizeof(double) * need));
+        X->vpart_n = need;
+    }
+    const int na = std::min(nblk, GGA ? 3 : 10), nb = GGA ? std::min(nblk, 8) : 0;
+    const size_t lds = sizeof(double) * (2 * (size_t)64 * (na + nb) * KP + 2 * KP);
+    auto go = [&](auto kernel) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) (void)hipGetLastError();
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nchunk, (unsigned)ngroup), dim3(64 * nw), lds, s, N, X->G, chunk, X->phiT,
+                           X->dphiT, X->f, X->hv, groups, ntile, X->vpart);
+    };
+    if constexpr (!GGA) {
+        if (wide) go(&k_xc_v<false, 16>);
+        else go(&k_xc_v<false, 8>);
+    } else {
+        go(&k_xc_v<true, 8>);
+    }
+    hipLaunchKernelGGL(k_xc_v_sum<GGA>, dim3(64, (unsigned)ntile), dim3(256), 0, s, N, nblk, ntile, (int)nchunk, X->vpart,
+                       X->Vacc);
+    MESS_LAUNCH_CHECK();
+    return MESS_OK;
+}
+
 // PBE: V (device N x N, may be NULL) and the device scalar X->ex (E_xc)
 // from density D.
 int pbe_xc_async(mess_basis *B, const double *D, double *V, hipStream_t s, const double **ex_dev) {
     XcGrid *X = nullptr;
     MESS_TRY(get_xc(B, &X));
     MESS_TRY(ensure_gga(B, X));
-    const int N = X->nbf;
     const unsigned npb = (unsigned)((X->G + 255) / 256);
-    hipLaunchKernelGGL(k_gga_rho, dim3((unsigned)X->nrho_blocks), dim3(256), 0, s, N, X->G, D, X->phiT, X->dphiT,
-                       X->rho, X->grad);
+    int nrho = 0;
+    MESS_TRY(rho_async<true>(X, D, s, &nrho));
     hipLaunchKernelGGL(k_pbe_point, dim3(npb), dim3(256), 0, s, X->G, X->xyzw, X->rho, X->grad, X->f, X->hv,
                        X->epart);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, (int)npb, X->epart, X->ex);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, s, (int)npb, X->epart, X->ex);
     MESS_LAUNCH_CHECK();
     if (V) {
-        const int nblk = (N + kXT - 1) / kXT;
-        const unsigned chunks = (unsigned)((X->G + kVChunk - 1) / kVChunk);
-        MESS_TRY(zero_async(X->Vacc, (int64_t)N * N, s));
-        hipLaunchKernelGGL(k_gga_v, dim3(chunks, nblk * nblk), dim3(256), 0, s, N, X->G, nblk, X->phiT, X->dphiT,
-                           X->f, X->hv, X->Vacc);
-        hipLaunchKernelGGL(k_gga_sym, dim3(256), dim3(256), 0, s, N, X->Vacc, V);
+        MESS_TRY(v_async<true>(X, s));
+        hipLaunchKernelGGL(k_gga_sym, dim3(256), dim3(256), 0, s, X->nbf, X->Vacc, V);
         MESS_LAUNCH_CHECK();
     }
     if (ex_dev) *ex_dev = X->ex;
@@ -832,18 +1045,13 @@ int pbe_xc_async(mess_basis *B, const double *D, double *V, hipStream_t s, const
 int lda_x_async(mess_basis *B, const double *D, double *V, hipStream_t s, const double **ex_dev) {
     XcGrid *X = nullptr;
     MESS_TRY(get_xc(B, &X));
-    const int N = X->nbf;
-    hipLaunchKernelGGL(k_lda_rho, dim3((unsigned)X->nrho_blocks), dim3(256), 0, s, N, X->G, D, X->phiT, X->xyzw,
-                       X->rho, X->f, X->epart);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, X->nrho_blocks, X->epart, X->ex);
+    int nrho = 0;
+    MESS_TRY(rho_async<false>(X, D, s, &nrho));
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, s, nrho, X->epart, X->ex);
     MESS_LAUNCH_CHECK();
     if (V) {
-        const int nblk = (N + kXT - 1) / kXT;
-        const unsigned chunks = (unsigned)((X->G + kVChunk - 1) / kVChunk);
-        MESS_TRY(zero_async(X->Vacc, (int64_t)N * N, s));
-        hipLaunchKernelGGL(k_lda_v, dim3(chunks, nblk * (nblk + 1) / 2), dim3(256), 0, s, N, X->G, nblk, X->phiT,
-                           X->f, X->Vacc);
-        hipLaunchKernelGGL(k_lda_mirror, dim3(256), dim3(256), 0, s, N, X->Vacc, V);
+        MESS_TRY(v_async<false>(X, s));
+        hipLaunchKernelGGL(k_lda_mirror, dim3(256), dim3(256), 0, s, X->nbf, X->Vacc, V);
         MESS_LAUNCH_CHECK();
     }
     if (ex_dev) *ex_dev = X->ex;

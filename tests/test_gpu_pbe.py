@@ -121,3 +121,51 @@ def test_pbe_full_size_water60():
     Ex_lda = mess.mess_lda_x(B, dev(D))
     announce(f"  E_xc {E:.6f}, LDA exchange {Ex_lda:.6f}")
     assert E < Ex_lda
+
+
+def _many_shells(nbf):
+    """One oxygen atom with s, p, d, s, p, d, ... shells of one primitive, nbf functions in all."""
+    rng = np.random.Generator(np.random.PCG64(nbf))
+    ls, n = [], 0
+    while n < nbf:
+        l = next(k for k in (len(ls) % 3, 1, 0) if n + (k + 1) * (k + 2) // 2 <= nbf)
+        ls.append(l)
+        n += (l + 1) * (l + 2) // 2
+    exps = np.exp(rng.uniform(math.log(0.1), math.log(50.0), len(ls)))
+    return G.Molecule(np.array([8], np.int32), np.zeros((1, 3)), np.zeros(len(ls), np.int32), np.array(ls, np.int32),
+                      np.ones(len(ls), np.int32), exps, np.ones(len(ls)), 0, f"shells/{nbf}")
+
+
+@pytest.mark.parametrize("nbf", [1, 17, 64, 65, 161, 321, 641, 1281])
+def test_xc_at_tile_edges(nbf):
+    """LDA and PBE where the contractions change their tiles: rows of 16 and
+    tiles of 64 functions and one beyond, more than four waves' rows (161),
+    point tiles of 32 (321) and 16 (641) and pairs of row panels (1281).  The
+    bars of the small molecules: relative to the largest element, of which
+    sums of up to 1281^2 terms in FP64 stay below 1e-13 off."""
+    mess = need_gpu()
+    mol = _many_shells(nbf)
+    assert mol.n_bf == nbf
+    announce(f"exchange-correlation tiles, {nbf} functions")
+    D = _psd_density(nbf, min(4, nbf), nbf)
+    B = mess.basis_from_molecule(mol)
+    xyzw = zeros(mess.mess_grid(B), 4)
+    mess.mess_grid(B, xyzw)
+    xyzw = host(xyzw)
+    grid = (xyzw[:, :3], xyzw[:, 3])  # the device's own points: only the contractions are compared
+    n = len(xyzw)
+    for lda in (True, False):
+        V, rho, grad = zeros(nbf, nbf), zeros(n), zeros(3, n)
+        if lda:
+            E_ref, V_ref, rho_ref = olda.lda_x(mol, D, grid=grid)
+            E = mess.mess_lda_x(B, dev(D), V, rho)
+        else:
+            E_ref, V_ref, rho_ref, grad_ref = opbe.pbe_xc(mol, D, grid=grid)
+            E = mess.mess_pbe_xc(B, dev(D), V, rho, grad)
+            assert np.abs(host(grad) - grad_ref).max() <= 1e-12 * np.abs(grad_ref).max()
+        Vh = host(V)
+        assert np.abs(host(rho) - rho_ref).max() <= 1e-12 * np.abs(rho_ref).max()
+        assert abs(E - E_ref) <= 1e-11 * abs(E_ref)
+        assert np.abs(Vh - V_ref).max() <= 1e-10 * np.abs(V_ref).max()
+        assert np.abs(Vh - Vh.T).max() == 0.0
+    B.close()
