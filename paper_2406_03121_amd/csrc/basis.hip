@@ -343,6 +343,7 @@ int fill_class_launch(const mess_basis *B, const ClassList &cl, hipStream_t s, C
     L.ngroups = cl.d_groups ? cl.ngroups : 0;
     L.nmax = B->nbf_max;
     L.total = cl.total;
+    L.prims = cl.prim_quartets;
     return MESS_OK;
 }
 

@@ -18,6 +18,7 @@ struct ClassLaunch {
     const int64_t *rowstart;
     const int2 *rowmap;  // per row: {bra index, first ket index}
     int64_t total;
+    int64_t prims = 0;   // primitive quartets of the list
     int N;
     hipStream_t stream;
     // stored-block digestion by bra-row segments (NULL: one lane per quartet)

@@ -457,10 +457,13 @@ __device__ constexpr double comp_scale(int local) {
 // components a, b, c, d of the bra pair's shells (sa, sb) and the ket
 // pair's shells (sc, sd).
 
-template <class Dm, typename Real>
+// P > 1: a group of P consecutive lanes shares the quartet; lane sub of the
+// group takes every P-th primitive quartet, the contracted intermediates are
+// summed over the group, and every lane of it returns the whole block.
+template <class Dm, typename Real, int P = 1>
 __device__ __forceinline__ void eri_quartet(const PairInfo &bra, const PairInfo &ket,
                                             const PrimPairT<Real> *__restrict__ pp, const BoysTabs &bt,
-                                            Real (&out)[Dm::NOUT]) {
+                                            Real (&out)[Dm::NOUT], int sub = 0) {
     // acc[f - F0][e - E0] = contracted [e0|f0], e on the bra side.  The
     // per-lane kernels keep the bra on the e side in every class: their
     // registers go mostly to the contracted intermediates, and the swapped
@@ -480,8 +483,28 @@ __device__ __forceinline__ void eri_quartet(const PairInfo &bra, const PairInfo 
         constexpr int x = decltype(X)::value;
         acc[x / Dm::NEA][x % Dm::NEA] += v;
     };
-    const int pbu = __builtin_amdgcn_readfirstlane(bra.pp0);
-    if (__all(bra.pp0 == pbu)) {
+    if constexpr (P > 1) {
+        // primitive quartets numbered ket-major, k = sub, sub + P, ...
+        const int nb = bra.npp, n = nb * ket.npp, dk = P / nb, db = P - dk * nb;
+        int ik = sub / nb, ib = sub - ik * nb;
+        for (int k = sub; k < n; k += P) {
+            prim_quartet<Dm, Real>(pp[bra.pp0 + ib], pp[ket.pp0 + ik], AC, bt, add);
+            ik += dk;
+            ib += db;
+            if (ib >= nb) {
+                ib -= nb;
+                ++ik;
+            }
+        }
+        static_for<0, Dm::NFA>([&](auto F) {
+            static_for<0, Dm::NEA>([&](auto E) {
+                Real v = acc[decltype(F)::value][decltype(E)::value];
+#pragma unroll
+                for (int o = P / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+                acc[decltype(F)::value][decltype(E)::value] = v;
+            });
+        });
+    } else if (const int pbu = __builtin_amdgcn_readfirstlane(bra.pp0); __all(bra.pp0 == pbu)) {
         const int nbu = __builtin_amdgcn_readfirstlane(bra.npp);
         const PrimPairT<Real> *__restrict__ pb = pp + pbu;
         for (int ik = 0; ik < ket.npp; ++ik) {
@@ -521,13 +544,6 @@ __device__ __forceinline__ void eri_quartet(const PairInfo &bra, const PairInfo 
                 out[ab * Dm::NCD + cd] = Yk[cd] * Real(s);
         });
     });
-}
-
-template <class Dm>
-__device__ __forceinline__ void eri_quartet_f64(const PairInfo &bra, const PairInfo &ket,
-                                                const PrimPair *__restrict__ pp, const BoysTabs &bt,
-                                                double (&out)[Dm::NOUT]) {
-    eri_quartet<Dm, double>(bra, ket, pp, bt, out);
 }
 
 }  // namespace mess

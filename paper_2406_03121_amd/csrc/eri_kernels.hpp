@@ -27,43 +27,56 @@ __device__ __forceinline__ int2 quartet_pairs(const int64_t *__restrict__ rowsta
     return make_int2(m.x, m.y + static_cast<int>(t - rowstart[r]));
 }
 
-// Q = sqrt(max_{a in sa, b in sb} |(ab|ab)|) for every pair of one class.
+// Lanes that share a shell quartet in the kernels with one lane per quartet
+// (FP64).  A lane's loop over the quartet's primitive quartets (up to 1296
+// of 6 x 6 x 6 x 6 primitives) is a serial chain, so a list that leaves the
+// chip's SIMDs with less than about two waves each is as slow as its longest
+// quartet: then P lanes take every P-th primitive quartet and sum the
+// contracted intermediates (log2 P exchanges each, a few hundred cycles
+// against the chain).  The sum's order depends on the list's size alone.
+// FP32 keeps one lane: its sums round where they are taken.
+constexpr int kSplits[3] = {64, 16, 4};
+
+// Q = sqrt(max_{a in sa, b in sb} |(ab|ab)|) for every pair of one class, 16
+// lanes a pair.
 template <class Dm>
 __global__ void __launch_bounds__(64) k_schwarz(const PairInfo *__restrict__ pairs, int off, int n,
                                                 const PrimPair *__restrict__ pp, BoysTabs bt,
                                                 double *__restrict__ Q) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * 4 + threadIdx.x / 16;
     if (i >= n) return;
     const PairInfo pr = pairs[off + i];
     double out[Dm::NOUT];
-    eri_quartet_f64<Dm>(pr, pr, pp, bt, out);
+    eri_quartet<Dm, double, 16>(pr, pr, pp, bt, out, threadIdx.x % 16);
     double m = 0.0;
     static_for<0, Dm::NAB>([&](auto I) {
         constexpr int ab = decltype(I)::value;
         m = fmax(m, fabs(out[ab * Dm::NCD + ab]));
     });
-    Q[off + i] = sqrt(m);
+    if (threadIdx.x % 16 == 0) Q[off + i] = sqrt(m);
 }
 
 // Dense N^4 store: every unique quartet writes its block to all eight
-// index permutations.
-template <class Dm, typename Real>
+// index permutations (P lanes a quartet, which share the stores).
+template <class Dm, typename Real, int P = 1>
 __global__ void __launch_bounds__(128) k_eri_dense(const PairInfo *__restrict__ pairs, int bra_off,
                                                    int ket_off, int nbra,
                                                    const int64_t *__restrict__ rowstart, const int2 *__restrict__ rowmap,
                                                    const PrimPairT<Real> *__restrict__ pp, BoysTabs bt,
                                                    int64_t N, double *__restrict__ eri) {
     const int64_t total = rowstart[nbra];
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
+    const int sub = threadIdx.x % P;
+    for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / P; t < total;
+         t += (int64_t)gridDim.x * blockDim.x / P) {
         const int2 ij = quartet_pairs(rowstart, rowmap, nbra, t);
         const int i = ij.x, j = ij.y;
         const PairInfo bra = pairs[bra_off + i];
         const PairInfo ket = pairs[ket_off + j];
         Real out[Dm::NOUT];
-        eri_quartet<Dm, Real>(bra, ket, pp, bt, out);
+        eri_quartet<Dm, Real, P>(bra, ket, pp, bt, out, sub);
         static_for<0, Dm::NOUT>([&](auto I) {
             constexpr int k = decltype(I)::value;
+            if (P > 1 && k % P != sub) return;
             constexpr int a = k / (Dm::NB * Dm::NCD), b = (k / Dm::NCD) % Dm::NB;
             constexpr int c = (k / Dm::ND) % Dm::NC, d = k % Dm::ND;
             const int64_t ia = bra.bfa + a, ib = bra.bfb + b, ic = ket.bfa + c, id = ket.bfb + d;
@@ -82,21 +95,25 @@ __global__ void __launch_bounds__(128) k_eri_dense(const PairInfo *__restrict__ 
 
 // Stored layout of one class: element k of quartet t at base[k * nq + t]
 // (structure of arrays, so that consecutive lanes touch consecutive words).
-template <class Dm, typename Real>
+template <class Dm, typename Real, int P = 1>
 __global__ void __launch_bounds__(128) k_eri_store(const PairInfo *__restrict__ pairs, int bra_off, int ket_off,
                                                    int nbra, const int64_t *__restrict__ rowstart, const int2 *__restrict__ rowmap,
                                                    const PrimPairT<Real> *__restrict__ pp, BoysTabs bt,
                                                    Real *__restrict__ base) {
     const int64_t total = rowstart[nbra];
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
+    const int sub = threadIdx.x % P;
+    for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / P; t < total;
+         t += (int64_t)gridDim.x * blockDim.x / P) {
         const int2 ij = quartet_pairs(rowstart, rowmap, nbra, t);
         const int i = ij.x, j = ij.y;
         const PairInfo bra = pairs[bra_off + i];
         const PairInfo ket = pairs[ket_off + j];
         Real out[Dm::NOUT];
-        eri_quartet<Dm, Real>(bra, ket, pp, bt, out);
-        static_for<0, Dm::NOUT>([&](auto I) { base[(int64_t)decltype(I)::value * total + t] = out[I]; });
+        eri_quartet<Dm, Real, P>(bra, ket, pp, bt, out, sub);
+        static_for<0, Dm::NOUT>([&](auto I) {
+            constexpr int k = decltype(I)::value;
+            if (P == 1 || k % P == sub) base[(int64_t)k * total + t] = out[k];
+        });
     }
 }
 
@@ -163,7 +180,8 @@ __device__ __forceinline__ void digest_jk(const Real (&out)[Dm::NOUT], double fa
     }
 }
 
-template <class Dm, typename Real>
+// Direct J/K, one lane (or P, see kSplits) per quartet.
+template <class Dm, typename Real, int P = 1>
 __global__ void __launch_bounds__(128) k_jk_direct(const PairInfo *__restrict__ pairs, int bra_off,
                                                    int ket_off, int nbra, int same_class,
                                                    const int64_t *__restrict__ rowstart, const int2 *__restrict__ rowmap,
@@ -171,14 +189,16 @@ __global__ void __launch_bounds__(128) k_jk_direct(const PairInfo *__restrict__ 
                                                    const double *__restrict__ D, int N,
                                                    double *__restrict__ Gj, double *__restrict__ Gk) {
     const int64_t total = rowstart[nbra];
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
+    const int sub = threadIdx.x % P;
+    for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / P; t < total;
+         t += (int64_t)gridDim.x * blockDim.x / P) {
         const int2 ij = quartet_pairs(rowstart, rowmap, nbra, t);
         const int i = ij.x, j = ij.y;
         const PairInfo bra = pairs[bra_off + i];
         const PairInfo ket = pairs[ket_off + j];
         Real out[Dm::NOUT];
-        eri_quartet<Dm, Real>(bra, ket, pp, bt, out);
+        eri_quartet<Dm, Real, P>(bra, ket, pp, bt, out, sub);
+        if (P > 1 && sub != 0) continue;
         double fac = 1.0;
         if (bra.sa == bra.sb) fac *= 0.5;
         if (ket.sa == ket.sb) fac *= 0.5;

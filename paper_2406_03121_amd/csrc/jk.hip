@@ -20,17 +20,20 @@ __global__ void k_fill_zero(double *__restrict__ p, int64_t n) {
         p[i] = 0.0;
 }
 
-// out = G + G^T for every diagonal block of a packed block-diagonal matrix
-// (block m: n_m x n_m at offset moff[m]); blockIdx.z strides over blocks.
-__global__ void k_symmetrise(const double *__restrict__ G, int nmol, const int64_t *__restrict__ moff,
-                             const int *__restrict__ nb, double *__restrict__ out) {
+// J = Gj + Gj^T, K = Gk + Gk^T (either may be NULL) for every diagonal block
+// of a packed block-diagonal matrix (block m: n_m x n_m at offset moff[m]);
+// blockIdx.z strides over blocks.
+__global__ void k_symmetrise(const double *__restrict__ Gj, const double *__restrict__ Gk, int nmol,
+                             const int64_t *__restrict__ moff, const int *__restrict__ nb, double *__restrict__ J,
+                             double *__restrict__ K) {
     const int i = blockIdx.y * blockDim.y + threadIdx.y;
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     for (int m = blockIdx.z; m < nmol; m += gridDim.z) {
         const int n = nb[m];
         if (i < n && j < n) {
-            const int64_t o = moff[m];
-            out[o + (int64_t)i * n + j] = G[o + (int64_t)i * n + j] + G[o + (int64_t)j * n + i];
+            const int64_t o = moff[m], ij = o + (int64_t)i * n + j, ji = o + (int64_t)j * n + i;
+            if (J) J[ij] = Gj[ij] + Gj[ji];
+            if (K) K[ij] = Gk[ij] + Gk[ji];
         }
     }
 }
@@ -44,11 +47,19 @@ int zero_async(double *p, int64_t n, hipStream_t s) {
     return MESS_OK;
 }
 
-int symmetrise_async(const mess_basis *B, const double *G, double *out, hipStream_t s) {
+int symmetrise_async(const mess_basis *B, const double *Gj, const double *Gk, double *J, double *K, hipStream_t s) {
     const int N = B->nbf_max;
     dim3 blk(32, 8), grd((N + 31) / 32, (N + 7) / 8, (unsigned)std::min(B->n_mol, 65535));
-    hipLaunchKernelGGL(k_symmetrise, grd, blk, 0, s, G, B->n_mol, B->d_mol_moff, B->d_mol_nbf, out);
+    hipLaunchKernelGGL(k_symmetrise, grd, blk, 0, s, Gj, Gk, B->n_mol, B->d_mol_moff, B->d_mol_nbf, J, K);
     MESS_LAUNCH_CHECK();
+    return MESS_OK;
+}
+
+// Clears the half matrices (either may be NULL), in one launch where they are adjacent.
+int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s) {
+    if (Gj && Gk == Gj + B->packed) return zero_async(Gj, 2 * B->packed, s);
+    if (Gj) MESS_TRY(zero_async(Gj, B->packed, s));
+    if (Gk) MESS_TRY(zero_async(Gk, B->packed, s));
     return MESS_OK;
 }
 
@@ -57,8 +68,7 @@ int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int p
                    hipStream_t s) {
     WorkLists *W = nullptr;
     MESS_TRY(get_work_lists(B, tau, s, &W));
-    if (Gj) MESS_TRY(zero_async(Gj, B->packed, s));
-    if (Gk) MESS_TRY(zero_async(Gk, B->packed, s));
+    MESS_TRY(zero_halves(B, Gj, Gk, s));
     const bool prof = prof_on();
     for (const ClassList &cl : W->classes) {
         if (cl.total == 0) continue;
@@ -93,9 +103,7 @@ int jk_full(mess_basis *B, const double *D, double *J, double *K, int mode, int 
         MESS_TRY(jk_det(B, D, Gj, Gk, prec, tau, s));
     else
         MESS_TRY(jk_stored(B, D, Gj, Gk, prec, tau, s));
-    if (J) MESS_TRY(symmetrise_async(B, Gj, J, s));
-    if (K) MESS_TRY(symmetrise_async(B, Gk, K, s));
-    return MESS_OK;
+    return symmetrise_async(B, Gj, Gk, J, K, s);
 }
 
 // Fixed device workspace of the allocation-free J/K entry point: the two
@@ -235,11 +243,9 @@ int mess_jk_noalloc(const mess_basis *basis, const double *D, double *J, double 
     MESS_TRY(scratch_address(&ws));
     hipStream_t s = static_cast<hipStream_t>(stream);
     double *Gj = J ? ws : nullptr;
-    double *Gk = K ? ws + kNoAllocMaxPacked : nullptr;
+    double *Gk = K ? ws + B->packed : nullptr;
     MESS_TRY(jk_direct_half(B, D, Gj, Gk, prec, tau, s));
-    if (J) MESS_TRY(symmetrise_async(B, Gj, J, s));
-    if (K) MESS_TRY(symmetrise_async(B, Gk, K, s));
-    return MESS_OK;
+    return symmetrise_async(B, Gj, Gk, J, K, s);
 }
 
 }  // extern "C"

@@ -221,6 +221,7 @@ enum : int { kFormAuto = 0, kFormLane = 1, kFormRows = 2, kFormPlane = 3, kFormC
 constexpr int kNumClasses = 21;
 int class_form(int cb, int ck, int prec = MESS_FP64);  // active form (built-in default unless set)
 bool form_valid(int cb, int ck, int form, int prec = MESS_FP64);
+bool form_is_default(int cb, int ck, int prec = MESS_FP64);           // no form was asked for
 bool plane_compiled(int cb, int ck);  // primitive-lane kernel built for the class
 bool wave_compiled(int cb, int ck);   // wave-per-primitive-quartet kernel built for the class
 bool rows_compiled(int cb, int ck);   // bra-segment kernel built for the class

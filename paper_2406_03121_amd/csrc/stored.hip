@@ -104,14 +104,13 @@ static int get_stored(mess_basis *B, int prec, double tau, hipStream_t s, WorkLi
     return MESS_OK;
 }
 
-int zero_async(double *p, int64_t n, hipStream_t s);
+int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s);
 
 int jk_stored(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau, hipStream_t s) {
     WorkLists *W = nullptr;
     StoredEri *E = nullptr;
     MESS_TRY(get_stored(B, prec, tau, s, &W, &E));
-    if (Gj) MESS_TRY(zero_async(Gj, B->packed, s));
-    if (Gk) MESS_TRY(zero_async(Gk, B->packed, s));
+    MESS_TRY(zero_halves(B, Gj, Gk, s));
     const bool prof = prof_on();
     for (size_t c = 0; c < W->classes.size(); ++c) {
         const ClassList &cl = W->classes[c];

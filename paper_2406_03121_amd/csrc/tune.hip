@@ -81,6 +81,11 @@ int class_form(int cb, int ck, int prec) {
     return f == kFormAuto ? default_form(cb, ck, prec) : f;
 }
 
+bool form_is_default(int cb, int ck, int prec) {
+    std::lock_guard<std::mutex> lk(g_form_mutex);
+    return g_form[prec == MESS_FP32 ? 1 : 0][class_index(cb, ck)] == kFormAuto;
+}
+
 static void set_form(int prec, int cls, int form) {
     std::lock_guard<std::mutex> lk(g_form_mutex);
     g_form[prec == MESS_FP32 ? 1 : 0][cls] = form;
@@ -183,7 +188,9 @@ int mess_autotune(const mess_basis *basis, int32_t prec, double schwarz_tol, con
             set_form(prec, cls, kFormAuto);
             break;
         }
-        set_form(prec, cls, best);
+        // the built-in form stays the default, which short lists may leave for
+        // several lanes per quartet
+        set_form(prec, cls, best == default_form(cl.cb, cl.ck, prec) ? (int)kFormAuto : best);
         if (forms) forms[cls] = best == kFormAuto ? class_form(cl.cb, cl.ck, prec) : best;
     }
     hipEventDestroy(e0);

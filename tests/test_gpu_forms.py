@@ -102,3 +102,32 @@ def test_fp32_form_parity(ref, cb, ck, form):
         B.close()
     finally:
         mess.mess_kernel_form(cls, mess.MESS_FORM_AUTO, prec=mess.MESS_FP32)
+
+
+@pytest.mark.parametrize("waters", [1, 3, 7, 13])
+def test_shared_quartets_match_single_lanes(waters):
+    """Direct J/K with the built-in forms, which on lists of these lengths put
+    64, 16, 4 or 1 lanes on a quartet by class, against every unrolled class
+    forced to one lane per quartet: sums of the same terms in another order,
+    1e-12 * max(1, |x|) apart at the most (the bar of one form against the
+    oracle is 1e-11)."""
+    mess = need_gpu()
+    mol = G.water_cluster(3, n_waters=waters, box=18.0 * (waters / 20) ** (1 / 3) + 3.0)
+    announce(f"shared quartets, {waters} waters, {mol.n_bf} functions")
+    B = mess.basis_from_molecule(mol)
+    N = mol.n_bf
+    D = dev(random_density(N, seed=7))
+    got, ref = [zeros(N, N), zeros(N, N)], [zeros(N, N), zeros(N, N)]
+    mess.mess_jk(B, D, *got, schwarz_tol=1e-10)
+    forced = [c for c in range(21)
+              if mess.lib().mess_kernel_form(mess.MESS_FP64, c, mess.MESS_FORM_LANE, None) == mess.MESS_OK]
+    try:
+        assert len(forced) == 14
+        mess.mess_jk(B, D, *ref, schwarz_tol=1e-10)
+    finally:
+        for c in forced:
+            mess.mess_kernel_form(c, mess.MESS_FORM_AUTO)
+    for a, b in zip(got, ref):
+        a, b = host(a), host(b)
+        assert np.all(np.abs(a - b) <= 1e-12 * np.maximum(1.0, np.abs(b)).max())
+    B.close()
