@@ -621,7 +621,7 @@ __global__ void __launch_bounds__(NT) k_coop(CoopArgs A, int region, int vstride
             }
         }
         __syncthreads();
-        coop_finish<MODE, NT>(A, H, hc, lane, bra, ket, i, j, bra_off, same_class, D, N, out0, out1, q, total);
+        coop_finish<MODE>(A, H, hc, lane, NT, bra, ket, i, j, bra_off, same_class, D, N, out0, out1, q, total);
         __syncthreads();  // H reused by the next quartet
     }
 }
@@ -633,11 +633,11 @@ static bool plane_class(int cb, int ck, int prec) {
 }
 
 static void launch_plane(int mode, int cb, int ck, int prec, const CoopArgs &A, const ClassLaunch &L, int64_t total,
-                         unsigned g, size_t lds, const double *D, double *out0, double *out1) {
+                         unsigned g, int nw, size_t lds, const double *D, double *out0, double *out1) {
 #define MESS_PL(B, K)                                                                                  \
     if (cb == B && ck == K) {                                                                          \
-        if (prec == MESS_FP32) PlaneOps<B, K, float>::launch(mode, A, L, total, g, lds, D, out0, out1);  \
-        else PlaneOps<B, K, double>::launch(mode, A, L, total, g, lds, D, out0, out1);                   \
+        if (prec == MESS_FP32) PlaneOps<B, K, float>::launch(mode, A, L, total, g, nw, lds, D, out0, out1);  \
+        else PlaneOps<B, K, double>::launch(mode, A, L, total, g, nw, lds, D, out0, out1);                   \
     }
     MESS_PL(5, 4)
     MESS_PL(5, 3)
@@ -650,16 +650,37 @@ static void launch_plane(int mode, int cb, int ck, int prec, const CoopArgs &A, 
 }
 
 static void launch_wave(int mode, int cb, int ck, int prec, const CoopArgs &A, const ClassLaunch &L, int64_t total,
-                        unsigned g, const double *D, double *out0, double *out1, size_t *lds) {
+                        unsigned g, int nw, int nshare, const double *D, double *out0, double *out1,
+                        size_t *lds) {
 #define MESS_WV(B, K)                                                                                        \
     if (cb == B && ck == K) {                                                                                \
-        if (prec == MESS_FP32) WaveOps<B, K, float>::launch(mode, A, L, total, g, D, out0, out1, lds);        \
-        else WaveOps<B, K, double>::launch(mode, A, L, total, g, D, out0, out1, lds);                         \
+        if (prec == MESS_FP32) WaveOps<B, K, float>::launch(mode, A, L, total, g, nw, nshare, D, out0, out1, lds);        \
+        else WaveOps<B, K, double>::launch(mode, A, L, total, g, nw, nshare, D, out0, out1, lds);                         \
     }
     MESS_WV(5, 5)
     MESS_WV(5, 4)
     MESS_WV(5, 3)
 #undef MESS_WV
+}
+
+// Waves a block (nw) and blocks a quartet (nshare) of the primitive-lane and
+// wave forms: one (four in the wave form) and one, except for FP64 lists of
+// up to 2048 quartets, where the chip has room and the longest quartet (1296
+// primitive quartets of 6 x 6 x 6 x 6 primitives) sets the time.  The
+// primitive-lane form then has four waves take the rounds of 64 in turn; in
+// the wave form whole blocks share a quartet (J/K and the dense tensor, whose
+// outputs are sums) until about 2048 blocks, or 12 waves do.  Measured per
+// J/K build on water clusters, us: (dd|dd) of 3, 7 and 13 waters (21, 271,
+// 1458 quartets) 1757 -> 97, 1821 -> 325, 1949 -> 1084 (6489 quartets: 3150
+// as it is, 3860 with 12 waves a block); (dd|dp) of 3 and 7 waters 685 -> 210,
+// 702 -> 258, but of 13 (5420) 757 -> 1177; (dp|pp) of 1150 quartets 160 -> 81.
+static void quartet_waves(bool wave, int mode, int cb, int ck, int prec, int64_t total, int *nw, int *nshare) {
+    *nw = wave ? 4 : 1;
+    *nshare = 1;
+    if (prec != MESS_FP64 || total > 2048) return;
+    if (!wave) *nw = 4;
+    else if (mode == kModeJK || mode == kModeDense) *nshare = (int)std::min<int64_t>(32, std::max<int64_t>(2, 2048 / total));
+    else if (cb == 5 && ck == 5) *nw = 12;
 }
 
 static int coop_launch(int mode, int cb, int ck, const ClassLaunch &L, int64_t total, double *out0, double *out1,
@@ -679,21 +700,25 @@ static int coop_launch(int mode, int cb, int ck, const ClassLaunch &L, int64_t t
     A.NA = ncart(P->LA); A.NB = ncart(P->LB); A.NC = ncart(P->LC); A.ND = ncart(P->LD);
     int64_t g = total;
     if (g > (1 << 20)) g = 1 << 20;
-    if (wave_compiled(cb, ck) && class_form(cb, ck, prec) == kFormWave) {
+    const bool wave = wave_compiled(cb, ck) && class_form(cb, ck, prec) == kFormWave;
+    int nw = 1, nshare = 1;
+    quartet_waves(wave, mode, cb, ck, prec, total, &nw, &nshare);
+    if (wave) {
         size_t lds = 0;
-        launch_wave(mode, cb, ck, prec, A, L, total, (unsigned)g, D, out0, out1, &lds);
-        if (lds > 64 * 1024) {
+        launch_wave(mode, cb, ck, prec, A, L, total, (unsigned)g, nw, nshare, D, out0, out1, &lds);
+        if (lds > 160 * 1024) {
             set_error("internal: class (%d,%d) needs %zu bytes of LDS in the wave form", cb, ck, lds);
             return MESS_E_UNSUPPORTED;
         }
-        launch_wave(mode, cb, ck, prec, A, L, total, (unsigned)g, D, out0, out1, nullptr);
+        launch_wave(mode, cb, ck, prec, A, L, total, (unsigned)(g * nshare), nw, nshare, D, out0, out1, nullptr);
         MESS_LAUNCH_CHECK();
         return MESS_OK;
     }
     if (plane_class(cb, ck, prec)) {
-        // H, the coefficients, and 64 lanes' base values (L + 1 each)
-        const size_t lds = sizeof(double) * ((size_t)P->nH + kNHCoef + 64 * (size_t)(P->L + 1));
-        launch_plane(mode, cb, ck, prec, A, L, total, (unsigned)g, lds, D, out0, out1);
+        // H, the coefficients, and each wave's 64 lanes' base values (L + 1
+        // each), which its sums replace at the end
+        const size_t lds = sizeof(double) * ((size_t)P->nH + kNHCoef + 64 * (size_t)(P->L + 1) * nw);
+        launch_plane(mode, cb, ck, prec, A, L, total, (unsigned)g, nw, lds, D, out0, out1);
         MESS_LAUNCH_CHECK();
         return MESS_OK;
     }
@@ -774,7 +799,7 @@ __global__ void __launch_bounds__(64) k_jk_stored_wave(const PairInfo *__restric
         auto O = [&](int a, int b, int cc, int d) {
             return (double)base[(int64_t)(((a * NB + b) * NC + cc) * ND + d) * total + q];
         };
-        wave_digest(lane, NA, NB, NC, ND, fac, bra.bfa, bra.bfb, ket.bfa, ket.bfb, O, D + bra.moff, bra.mN,
+        wave_digest(lane, 64, NA, NB, NC, ND, fac, bra.bfa, bra.bfb, ket.bfa, ket.bfb, O, D + bra.moff, bra.mN,
                     Gj ? Gj + bra.moff : nullptr, Gk ? Gk + bra.moff : nullptr);
     }
 }

@@ -93,11 +93,11 @@ __device__ __forceinline__ double run_op(const int4 op, const double *__restrict
     return v;
 }
 
-// J/K digestion of one quartet's block by a wave: lanes over the elements of
+// J/K digestion of one quartet's block by nt threads: over the elements of
 // the six target families Gj[a,b], Gj[c,d], Gk[a,c], Gk[b,c], Gk[a,d],
 // Gk[b,d] (each a sum over the block weighted by density elements).
-template <int NT = 64, typename OF>
-__device__ __forceinline__ void wave_digest(const int lane, const int NA, const int NB, const int NC, const int ND,
+template <typename OF>
+__device__ __forceinline__ void wave_digest(const int lane, const int nt, const int NA, const int NB, const int NC, const int ND,
                                             const double fac, const int a0, const int b0, const int c0, const int d0,
                                             OF &&O, const double *__restrict__ D, const int N,
                                             double *__restrict__ Gj, double *__restrict__ Gk) {
@@ -106,7 +106,7 @@ __device__ __forceinline__ void wave_digest(const int lane, const int NA, const 
     const int t_ab = Gj ? nab : 0, t_cd = Gj ? ncd : 0;
     const int t_ac = Gk ? NA * NC : 0, t_bc = Gk ? NB * NC : 0, t_ad = Gk ? NA * ND : 0, t_bd = Gk ? NB * ND : 0;
     const int ntgt = t_ab + t_cd + t_ac + t_bc + t_ad + t_bd;
-    for (int t = lane; t < ntgt; t += NT) {
+    for (int t = lane; t < ntgt; t += nt) {
         int r = t;
         double s = 0.0;
         if (r < t_ab) {
@@ -159,14 +159,17 @@ __device__ __forceinline__ void wave_digest(const int lane, const int NA, const 
 }
 
 // Horizontal recursion of the accumulated [e0|f0] (in H[0, nacc)) and the
-// per-mode output of one quartet, shared by the wave.
-// NT: threads of the block sharing the quartet (lane = thread index).
-template <int MODE, int NT = 64>
+// per-mode output of one quartet, shared by the nt threads of the block
+// (lane = thread index).  add: the block holds a part of the quartet's sum,
+// and dense elements are added to a cleared tensor (one that several
+// permutations reach, by as many equal parts).
+template <int MODE>
 __device__ __forceinline__ void coop_finish(const CoopArgs &A, double *__restrict__ H, double *__restrict__ hc,
-                                            const int lane, const PairInfo &bra, const PairInfo &ket, const int i,
+                                            const int lane, const int nt, const PairInfo &bra, const PairInfo &ket, const int i,
                                             const int j, const int bra_off, const int same_class,
                                             const double *__restrict__ D, const int N, double *__restrict__ out0,
-                                            double *__restrict__ out1, const int64_t q = 0, const int64_t total = 0) {
+                                            double *__restrict__ out1, const int64_t q = 0, const int64_t total = 0,
+                                            const bool add = false) {
         if (lane == 0) {
             hc[kH0] = 0.0; hc[kH1] = 1.0;
             hc[kHAB + 0] = bra.ABx; hc[kHAB + 1] = bra.ABy; hc[kHAB + 2] = bra.ABz;
@@ -175,7 +178,7 @@ __device__ __forceinline__ void coop_finish(const CoopArgs &A, double *__restric
         __syncthreads();
         for (int lv = 0; lv < A.nhlev; ++lv) {
             const int b0 = A.hlev[lv], b1 = A.hlev[lv + 1];
-            for (int o = b0 + lane; o < b1; o += NT) {
+            for (int o = b0 + lane; o < b1; o += nt) {
                 const int4 op = A.hops[o];
                 H[op.x & 0xffff] = run_op(op, H, hc);
             }
@@ -195,51 +198,61 @@ __device__ __forceinline__ void coop_finish(const CoopArgs &A, double *__restric
                 out0[bra_off + i] = sqrt(m);
             }
         } else if (MODE == kModeStore64 || MODE == kModeStore32) {
-            for (int o = lane; o < A.nout; o += NT) {
+            for (int o = lane; o < A.nout; o += nt) {
                 const double v = H[A.outslot[o]] * A.outscale[o];
                 if (MODE == kModeStore64) out0[(int64_t)o * total + q] = v;
                 else reinterpret_cast<float *>(out0)[(int64_t)o * total + q] = (float)v;
             }
         } else if (MODE == kModeDense) {
             const int64_t NN = N;
-            for (int o = lane; o < A.nout; o += NT) {
+            double part = 1.0;
+            if (bra.sa == bra.sb) part *= 0.5;
+            if (ket.sa == ket.sb) part *= 0.5;
+            if (same_class && i == j) part *= 0.5;
+            for (int o = lane; o < A.nout; o += nt) {
                 const int d = o % ND, cc = (o / ND) % NC, b = (o / (ND * NC)) % NB, a = o / (ND * NC * NB);
                 const double v = H[A.outslot[o]] * A.outscale[o];
                 const int64_t ia = bra.bfa + a, ib = bra.bfb + b, ic = ket.bfa + cc, id = ket.bfb + d;
-                out0[((ia * NN + ib) * NN + ic) * NN + id] = v;
-                out0[((ib * NN + ia) * NN + ic) * NN + id] = v;
-                out0[((ia * NN + ib) * NN + id) * NN + ic] = v;
-                out0[((ib * NN + ia) * NN + id) * NN + ic] = v;
-                out0[((ic * NN + id) * NN + ia) * NN + ib] = v;
-                out0[((id * NN + ic) * NN + ia) * NN + ib] = v;
-                out0[((ic * NN + id) * NN + ib) * NN + ia] = v;
-                out0[((id * NN + ic) * NN + ib) * NN + ia] = v;
+                auto put = [&](int64_t p, int64_t r, int64_t u, int64_t w) {
+                    double *e = out0 + ((p * NN + r) * NN + u) * NN + w;
+                    if (add) unsafeAtomicAdd(e, part * v);
+                    else *e = v;
+                };
+                put(ia, ib, ic, id);
+                put(ib, ia, ic, id);
+                put(ia, ib, id, ic);
+                put(ib, ia, id, ic);
+                put(ic, id, ia, ib);
+                put(id, ic, ia, ib);
+                put(ic, id, ib, ia);
+                put(id, ic, ib, ia);
             }
         } else {
             double fac = 1.0;
             if (bra.sa == bra.sb) fac *= 0.5;
             if (ket.sa == ket.sb) fac *= 0.5;
             if (same_class && i == j) fac *= 0.5;
-            wave_digest<NT>(lane, NA, NB, NC, ND, fac, bra.bfa, bra.bfb, ket.bfa, ket.bfb, O, D + bra.moff, bra.mN,
+            wave_digest(lane, nt, NA, NB, NC, ND, fac, bra.bfa, bra.bfb, ket.bfa, ket.bfb, O, D + bra.moff, bra.mN,
                             out0 ? out0 + bra.moff : nullptr, out1 ? out1 + bra.moff : nullptr);
         }
 }
 
 
 // Wave-per-primitive-quartet launch of one class in one precision
-// (wave.hip, compiled once per class and precision).  With lds_out != NULL
-// only reports the dynamic LDS bytes the launch needs.
+// (wave.hip, compiled once per class and precision) with nw waves a block
+// and nshare blocks a quartet.
+// With lds_out != NULL only reports the dynamic LDS bytes the launch needs.
 template <int CB, int CK, typename Real>
 struct WaveOps {
-    static void launch(int mode, const CoopArgs &A, const ClassLaunch &L, int64_t total, unsigned g,
+    static void launch(int mode, const CoopArgs &A, const ClassLaunch &L, int64_t total, unsigned g, int nw, int nshare,
                        const double *D, double *out0, double *out1, size_t *lds_out);
 };
 
 // Primitive-lane launch of one class in one precision (plane.hip, compiled
-// once per class and precision).
+// once per class and precision) with nw waves a block.
 template <int CB, int CK, typename Real>
 struct PlaneOps {
-    static void launch(int mode, const CoopArgs &A, const ClassLaunch &L, int64_t total, unsigned g, size_t lds,
+    static void launch(int mode, const CoopArgs &A, const ClassLaunch &L, int64_t total, unsigned g, int nw, size_t lds,
                        const double *D, double *out0, double *out1);
 };
 

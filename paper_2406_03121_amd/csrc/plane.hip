@@ -83,7 +83,7 @@ inline constexpr int kPlanePasses = MESS_PLANE_PASSES;
 #endif
 
 template <class Dm, int MODE, typename Real>
-__global__ void __launch_bounds__(64) MESS_PLANE_OCC k_plane(CoopArgs A, const PairInfo *__restrict__ pairs, int bra_off,
+__global__ void __launch_bounds__(sizeof(Real) == 8 ? 256 : 64) MESS_PLANE_OCC k_plane(CoopArgs A, const PairInfo *__restrict__ pairs, int bra_off,
                                               int ket_off, int nbra, int same_class,
                                               const int64_t *__restrict__ rowstart, const int2 *__restrict__ rowmap, int64_t total,
                                               const PrimPairT<Real> *__restrict__ pp, BoysTabs bt,
@@ -102,10 +102,15 @@ __global__ void __launch_bounds__(64) MESS_PLANE_OCC k_plane(CoopArgs A, const P
     extern __shared__ double lds[];
     double *H = lds;
     double *hc = lds + A.nH;
-    const int lane = threadIdx.x;
+    // FP64: one wave or four a block (blockDim), which take the rounds of 64
+    // primitive quartets in turn; FP32 sums keep the order of one wave
+    constexpr bool MW = sizeof(Real) == 8;
+    const int lane = threadIdx.x & 63, wave = MW ? threadIdx.x >> 6 : 0, nt = MW ? (int)blockDim.x : 64;
     // base values [00|00]^(m) of this lane's primitive quartet, element m at
     // bfl[64 m], shared by the recursion passes (one Boys evaluation)
-    Real *bfl = reinterpret_cast<Real *>(lds + A.nH + kNHCoef) + lane;
+    double *bw = lds + A.nH + kNHCoef;
+    Real *bfl = reinterpret_cast<Real *>(bw + wave * 64 * (Dm::L + 1)) + lane;
+    static_assert(NACC <= 64 * (Dm::L + 1), "a wave's sums fit its base values' place");
     for (int64_t q = blockIdx.x; q < total; q += gridDim.x) {
         int i, j;
         if (MODE == kModeSchwarz) {
@@ -123,7 +128,7 @@ __global__ void __launch_bounds__(64) MESS_PLANE_OCC k_plane(CoopArgs A, const P
         Real part[NPER];
         static_for<0, NPER>([&](auto I) { part[I] = Real(0); });
         const int nprim = bra.npp * ket.npp;
-        for (int k0 = 0; k0 < nprim; k0 += 64) {
+        for (int k0 = 64 * wave; k0 < nprim; k0 += nt) {
             const int k = k0 + lane;
             // lanes past the end evaluate primitive quartet 0 with zero
             // weight, so the recursion and the reductions stay one
@@ -195,17 +200,33 @@ __global__ void __launch_bounds__(64) MESS_PLANE_OCC k_plane(CoopArgs A, const P
                 run(std::integral_constant<int, 63>{});
             }
         }
-        static_for<0, NPER>([&](auto I) {
-            const int ps = BS * decltype(I)::value + lane;
-            if (lane < BS && ps < NACC) {
-                const int x = kPlaneBlocksDev<Dr, NACC>.xof[ps];
-                // swapped: x = (e - E0) NFA + (f - F0) holds [e0|f0]
-                const int h = SW ? (x % Dm::NFA) * Dm::NEA + x / Dm::NFA : x;
-                H[h] = (double)part[I];
+        // entry of the class's own order for position ps of the recursion's
+        auto slot = [&](int ps) {
+            const int x = kPlaneBlocksDev<Dr, NACC>.xof[ps];
+            // swapped: x = (e - E0) NFA + (f - F0) holds [e0|f0]
+            return SW ? (x % Dm::NFA) * Dm::NEA + x / Dm::NFA : x;
+        };
+        if (MW && nt > 64) {
+            // the waves' sums, added in wave order
+            __builtin_amdgcn_wave_barrier();
+            static_for<0, NPER>([&](auto I) {
+                const int ps = BS * decltype(I)::value + lane;
+                if (lane < BS && ps < NACC) bw[wave * 64 * (Dm::L + 1) + ps] = (double)part[I];
+            });
+            __syncthreads();
+            for (int ps = threadIdx.x; ps < NACC; ps += nt) {
+                double s = bw[ps];
+                for (int w = 1; w < nt / 64; ++w) s += bw[w * 64 * (Dm::L + 1) + ps];
+                H[slot(ps)] = s;
             }
-        });
+        } else {
+            static_for<0, NPER>([&](auto I) {
+                const int ps = BS * decltype(I)::value + lane;
+                if (lane < BS && ps < NACC) H[slot(ps)] = (double)part[I];
+            });
+        }
         __syncthreads();
-        coop_finish<MODE>(A, H, hc, lane, bra, ket, i, j, bra_off, same_class, D, N, out0, out1, q, total);
+        coop_finish<MODE>(A, H, hc, threadIdx.x, nt, bra, ket, i, j, bra_off, same_class, D, N, out0, out1, q, total);
         __syncthreads();
     }
 }
@@ -213,7 +234,7 @@ __global__ void __launch_bounds__(64) MESS_PLANE_OCC k_plane(CoopArgs A, const P
 
 template <>
 void PlaneOps<MESS_PCB, MESS_PCK, MESS_PREAL>::launch(int mode, const CoopArgs &A, const ClassLaunch &L,
-                                                      int64_t total, unsigned g, size_t lds, const double *D,
+                                                      int64_t total, unsigned g, int nw, size_t lds, const double *D,
                                                       double *out0, double *out1) {
     using Dm = ClassOf<MESS_PCB, MESS_PCK>;
     using R = MESS_PREAL;
@@ -222,23 +243,23 @@ void PlaneOps<MESS_PCB, MESS_PCK, MESS_PREAL>::launch(int mode, const CoopArgs &
     pp = reinterpret_cast<const PrimPairT<R> *>(sizeof(R) == 8 ? (const void *)L.pp : (const void *)L.ppf);
     switch (mode) {
         case kModeSchwarz:
-            hipLaunchKernelGGL((k_plane<Dm, kModeSchwarz, R>), dim3(g), dim3(64), lds, L.stream, A, L.pairs, L.bra_off,
+            hipLaunchKernelGGL((k_plane<Dm, kModeSchwarz, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
                                L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
             break;
         case kModeDense:
-            hipLaunchKernelGGL((k_plane<Dm, kModeDense, R>), dim3(g), dim3(64), lds, L.stream, A, L.pairs, L.bra_off,
+            hipLaunchKernelGGL((k_plane<Dm, kModeDense, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
                                L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
             break;
         case kModeStore64:
-            hipLaunchKernelGGL((k_plane<Dm, kModeStore64, R>), dim3(g), dim3(64), lds, L.stream, A, L.pairs, L.bra_off,
+            hipLaunchKernelGGL((k_plane<Dm, kModeStore64, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
                                L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
             break;
         case kModeStore32:
-            hipLaunchKernelGGL((k_plane<Dm, kModeStore32, R>), dim3(g), dim3(64), lds, L.stream, A, L.pairs, L.bra_off,
+            hipLaunchKernelGGL((k_plane<Dm, kModeStore32, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
                                L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
             break;
         default:
-            hipLaunchKernelGGL((k_plane<Dm, kModeJK, R>), dim3(g), dim3(64), lds, L.stream, A, L.pairs, L.bra_off,
+            hipLaunchKernelGGL((k_plane<Dm, kModeJK, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
                                L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
     }
 }

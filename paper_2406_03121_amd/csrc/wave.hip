@@ -2,8 +2,9 @@
 // precision (compiled once per class and precision with -DMESS_WCB,
 // -DMESS_WCK, -DMESS_WREAL).
 //
-// A 256-thread block takes one shell quartet; each of its four waves runs
-// the Obara-Saika vertical recursion of every fourth primitive quartet.
+// A block of four waves (twelve for short lists) takes one shell quartet;
+// each wave runs the Obara-Saika vertical recursion of every fourth
+// (twelfth) primitive quartet.
 // Inside a wave the lanes share the recursion of one primitive quartet:
 // lane slot p owns the intermediate pair (e, m) for the whole kernel, so a
 // step of component f reads the parent's (e, m), (e, m+1) and
@@ -15,7 +16,7 @@
 // (numbered by the deepest level that uses them), and the lanes owning an
 // output pair [e0|f0]^(0) accumulate it over the wave's primitive quartets
 // in registers: no reduction across lanes until the quartet is done.  The
-// four waves' sums then meet in LDS, and the horizontal recursion and output
+// waves' sums then meet in LDS, and the horizontal recursion and output
 // run table-driven as in k_coop.
 #include "coop.hpp"
 
@@ -169,16 +170,23 @@ struct WaveLds {
     static constexpr int LP = Dr::L + 1;
     static constexpr int BLOCK = Dr::NE * LP;                  // one level
     static constexpr int PER_WAVE = (Dr::LCD + 1) * BLOCK;     // Real elements per wave
-    static constexpr int VRR_DOUBLES = (4 * PER_WAVE * (int)sizeof(Real) + 7) / 8;
+    static constexpr int vrr_doubles(int nw) { return (nw * PER_WAVE * (int)sizeof(Real) + 7) / 8; }
 };
 
-template <class Dm, int MODE, typename Real>
-__global__ void __launch_bounds__(256) k_wave(CoopArgs A, int region, const PairInfo *__restrict__ pairs,
+// NW waves a block: 4, or for short lists of Schwarz factors and stored
+// blocks 12 (FP64 (dd|dd): their recursion levels take 151 of the 160 KB of
+// LDS; FP32 sums keep the order of four).  nshare: blocks that share a
+// quartet's primitive quartets, each with its own horizontal recursion and
+// output (J/K and the dense tensor, whose outputs then add up).
+constexpr bool kManyWaves = MESS_WCB == 5 && MESS_WCK == 5 && sizeof(MESS_WREAL) == 8;
+
+template <class Dm, int MODE, typename Real, int NW>
+__global__ void __launch_bounds__(64 * NW) k_wave(CoopArgs A, int region, const PairInfo *__restrict__ pairs,
                                               int bra_off, int ket_off, int nbra, int same_class,
                                               const int64_t *__restrict__ rowstart, const int2 *__restrict__ rowmap,
-                                              int64_t total, const PrimPairT<Real> *__restrict__ pp, BoysTabs bt,
-                                              const double *__restrict__ D, int N, double *__restrict__ out0,
-                                              double *__restrict__ out1) {
+                                              int64_t total, int nshare, const PrimPairT<Real> *__restrict__ pp,
+                                              BoysTabs bt, const double *__restrict__ D, int N,
+                                              double *__restrict__ out0, double *__restrict__ out1) {
     using WO = WaveOrient<Dm>;
     using Dr = typename WO::Dr;
     constexpr bool SW = WO::swap;
@@ -192,6 +200,7 @@ __global__ void __launch_bounds__(256) k_wave(CoopArgs A, int region, const Pair
     extern __shared__ double lds[];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
+    constexpr int nt = 64 * NW;
     Real *R = reinterpret_cast<Real *>(lds) + wave * Lds::PER_WAVE;
     double *H = lds;                 // after the primitive loop: accumulators and HRR slots
     double *hc = lds + region;       // HRR coefficients
@@ -214,7 +223,9 @@ __global__ void __launch_bounds__(256) k_wave(CoopArgs A, int region, const Pair
     });
     const bool out_lane = lane < kWaveMap<Dr>.nout;
 
-    for (int64_t q = blockIdx.x; q < total; q += gridDim.x) {
+    for (int64_t item = blockIdx.x; item < total * nshare; item += gridDim.x) {
+        const int64_t q = item / nshare;
+        const int share = (int)(item - q * nshare);
         int i, j;
         if (MODE == kModeSchwarz) {
             i = j = (int)q;
@@ -233,7 +244,7 @@ __global__ void __launch_bounds__(256) k_wave(CoopArgs A, int region, const Pair
         static_for<0, NFO>([&](auto F) { acc[decltype(F)::value] = Real(0); });
         const int npe = pe.npp, npf = pf.npp;
         const int npq = npe * npf;
-        for (int k = wave; k < npq; k += 4) {
+        for (int k = share * NW + wave; k < npq; k += NW * nshare) {
             const PrimPairT<Real> P = pp[pe.pp0 + k / npf];
             const PrimPairT<Real> Q = pp[pf.pp0 + k % npf];
             const Real p = P.p, qq = Q.p, pq = p + qq, spq = rsqrt_nr(pq), rpq = spq * spq;
@@ -304,7 +315,7 @@ __global__ void __launch_bounds__(256) k_wave(CoopArgs A, int region, const Pair
                 }
             });
         }
-        // the four waves' sums into H[(f - F0) NEA + (e - E0)] in the class's
+        // the waves' sums into H[(f - F0) NEA + (e - E0)] in the class's
         // own orientation: each wave writes its own copy (after H), then the
         // copies are added in wave order, so the result does not depend on
         // timing (the deterministic J/K mode relies on reproducible blocks)
@@ -319,24 +330,28 @@ __global__ void __launch_bounds__(256) k_wave(CoopArgs A, int region, const Pair
             });
         }
         __syncthreads();
-        for (int s = tid; s < A.nacc; s += 256)
-            H[s] = ((Hw[s] + Hw[A.nacc + s]) + Hw[2 * A.nacc + s]) + Hw[3 * A.nacc + s];
+        for (int s = tid; s < A.nacc; s += nt) {
+            double v = Hw[s];
+            for (int w = 1; w < NW; ++w) v += Hw[w * A.nacc + s];
+            H[s] = v;
+        }
         __syncthreads();
-        coop_finish<MODE, 256>(A, H, hc, tid, bra, ket, i, j, bra_off, same_class, D, N, out0, out1, q, total);
+        coop_finish<MODE>(A, H, hc, tid, nt, bra, ket, i, j, bra_off, same_class, D, N, out0, out1, q, total, nshare > 1);
         __syncthreads();
     }
 }
 
 template <>
 void WaveOps<MESS_WCB, MESS_WCK, MESS_WREAL>::launch(int mode, const CoopArgs &A, const ClassLaunch &L,
-                                                     int64_t total, unsigned g, const double *D, double *out0,
-                                                     double *out1, size_t *lds_out) {
+                                                     int64_t total, unsigned g, int nw, int nshare, const double *D,
+                                                     double *out0, double *out1, size_t *lds_out) {
     using Dm = ClassOf<MESS_WCB, MESS_WCK>;
     using R = MESS_WREAL;
     using Lds = WaveLds<Dm, R>;
-    // VRR blocks during the primitive loop; then the accumulators, the four
+    // VRR blocks during the primitive loop; then the accumulators, the
     // waves' copies of them, and the HRR slots
-    const int region = std::max(std::max(Lds::VRR_DOUBLES, A.nH), 5 * A.nacc);
+    nw = kManyWaves && nw == 12 ? 12 : 4;
+    const int region = std::max(std::max(Lds::vrr_doubles(nw), A.nH), (nw + 1) * A.nacc);
     const size_t lds = sizeof(double) * ((size_t)region + kNHCoef);
     if (lds_out) {
         *lds_out = lds;
@@ -345,9 +360,21 @@ void WaveOps<MESS_WCB, MESS_WCK, MESS_WREAL>::launch(int mode, const CoopArgs &A
     const BoysTabs bt{L.tab, L.etab, L.tabf, L.etabf, L.tabt};
     const PrimPairT<R> *pp =
         reinterpret_cast<const PrimPairT<R> *>(sizeof(R) == 8 ? (const void *)L.pp : (const void *)L.ppf);
-#define MESS_WAVE_GO(MODE)                                                                                       \
-    hipLaunchKernelGGL((k_wave<Dm, MODE, R>), dim3(g), dim3(256), lds, L.stream, A, region, L.pairs, L.bra_off,  \
-                       L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1)
+#define MESS_WAVE_GO(MODE)                                                                                         \
+    do {                                                                                                           \
+        if constexpr (kManyWaves && MODE != kModeJK && MODE != kModeDense)                                         \
+            if (nw == 12) {                                                                                        \
+                (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_wave<Dm, MODE, R, 12>),                \
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
+                hipLaunchKernelGGL((k_wave<Dm, MODE, R, 12>), dim3(g), dim3(768), lds, L.stream, A, region,        \
+                                   L.pairs, L.bra_off, L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap,      \
+                                   total, 1, pp, bt, D, L.N, out0, out1);                                          \
+                break;                                                                                             \
+            }                                                                                                      \
+        hipLaunchKernelGGL((k_wave<Dm, MODE, R, 4>), dim3(g), dim3(256), lds, L.stream, A, region, L.pairs,        \
+                           L.bra_off, L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, nshare, pp, bt, \
+                           D, L.N, out0, out1);                                                                         \
+    } while (0)
     switch (mode) {
         case kModeSchwarz: MESS_WAVE_GO(kModeSchwarz); break;
         case kModeDense: MESS_WAVE_GO(kModeDense); break;
