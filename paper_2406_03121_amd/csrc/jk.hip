@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <vector>
 
 namespace mess {
 
@@ -63,6 +64,120 @@ int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s) {
     return MESS_OK;
 }
 
+// ------------------------------------------------------- class streams
+//
+// The classes of a build are independent (they meet in atomics), and most
+// leave part of the chip idle: short lists, a long last wave, or a form
+// bound by latency.  They run on the caller's stream and kSideStreams
+// others between a fork and a join (events on the caller's stream), the
+// costliest first, each on the stream with the least work so far.  Sets of
+// side streams are kept in a pool: at most kMaxSets, each used by one call
+// at a time while it enqueues (a later call's work queues behind, so a set is
+// free again at once); with none left, and under capture, the classes run one
+// after another on the caller's stream.
+
+constexpr int kSideStreams = 3, kMaxSets = 8;
+
+struct SideSet {
+    int device = -1;
+    hipStream_t s[kSideStreams] = {};
+    hipEvent_t fork = nullptr, done[kSideStreams] = {};
+};
+
+static std::mutex g_side_mutex;
+static std::vector<SideSet *> g_side_free;
+static int g_side_made = 0;
+
+static SideSet *side_acquire(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    int dev = 0;
+    if (cap != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess) return nullptr;
+    std::lock_guard<std::mutex> lk(g_side_mutex);
+    for (size_t i = 0; i < g_side_free.size(); ++i)
+        if (g_side_free[i]->device == dev) {
+            SideSet *set = g_side_free[i];
+            g_side_free.erase(g_side_free.begin() + i);
+            return set;
+        }
+    if (g_side_made >= kMaxSets) return nullptr;
+    auto *set = new SideSet();
+    set->device = dev;
+    bool ok = hipEventCreateWithFlags(&set->fork, hipEventDisableTiming) == hipSuccess;
+    for (int i = 0; i < kSideStreams; ++i)
+        ok = ok && hipStreamCreateWithFlags(&set->s[i], hipStreamNonBlocking) == hipSuccess &&
+             hipEventCreateWithFlags(&set->done[i], hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        for (int i = 0; i < kSideStreams; ++i) {
+            if (set->s[i]) (void)hipStreamDestroy(set->s[i]);
+            if (set->done[i]) (void)hipEventDestroy(set->done[i]);
+        }
+        if (set->fork) (void)hipEventDestroy(set->fork);
+        delete set;
+        return nullptr;
+    }
+    ++g_side_made;
+    return set;
+}
+
+static void side_release(SideSet *set) {
+    std::lock_guard<std::mutex> lk(g_side_mutex);
+    g_side_free.push_back(set);
+}
+
+// Launches work(i, stream) for every i < cost.size() on s and the side
+// streams; all of it is complete before what s runs next.
+template <typename F>
+static int run_forked(hipStream_t s, const std::vector<double> &cost, F &&work) {
+    // few classes with little work each (s and p shells of a small molecule: up
+    // to six of 15-25 us) end sooner one after another than the fork and the
+    // join take (30-function J/K 109 and 151 us, its tensor 75 and 151); with
+    // all 21 classes the fork pays from the smallest molecule on (one water
+    // 544 -> 226 us, 3 waters 1190 -> 560, 13 waters 11.5 -> 9.0 ms and 17.2
+    // -> 8.0 in FP32, 20 waters 31.8 -> 27.7), as it does for few but long ones
+    const int n = (int)cost.size();
+    double all = 0.0;
+    for (double c : cost) all += c;
+    SideSet *set = (n >= 8 || (n > 1 && all >= 1e9)) && !prof_on() ? side_acquire(s) : nullptr;
+    if (!set) {
+        for (int i = 0; i < n; ++i) MESS_TRY(work(i, s));
+        return MESS_OK;
+    }
+    std::vector<int> order(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+    const int ns = std::min(n, kSideStreams + 1);
+    double load[kSideStreams + 1] = {};
+    int rc = MESS_OK;
+    hipError_t e = hipEventRecord(set->fork, s);
+    for (int i = 0; i + 1 < ns && e == hipSuccess; ++i) e = hipStreamWaitEvent(set->s[i], set->fork, 0);
+    if (e == hipSuccess)
+        for (int i = 0; i < n && rc == MESS_OK; ++i) {
+            int k = 0;
+            for (int j = 1; j < ns; ++j)
+                if (load[j] < load[k]) k = j;
+            load[k] += cost[order[i]];
+            rc = work(order[i], k == 0 ? s : set->s[k - 1]);
+        }
+    // join, also after an error: nothing of this call may outlast it
+    for (int i = 0; i + 1 < ns; ++i) {
+        hipError_t d = hipEventRecord(set->done[i], set->s[i]);
+        if (d == hipSuccess) d = hipStreamWaitEvent(s, set->done[i], 0);
+        if (d != hipSuccess) (void)hipStreamSynchronize(set->s[i]);
+        if (e == hipSuccess) e = d;
+    }
+    side_release(set);
+    if (rc == MESS_OK && e != hipSuccess) {
+        set_error("class streams: %s", hipGetErrorString(e));
+        rc = MESS_E_DEVICE;
+    }
+    return rc;
+}
+
 // Gj, Gk (device, packed block-diagonal, may be NULL) <- half-matrices of J and K.
 int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau,
                    hipStream_t s) {
@@ -70,10 +185,19 @@ int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int p
     MESS_TRY(get_work_lists(B, tau, s, &W));
     MESS_TRY(zero_halves(B, Gj, Gk, s));
     const bool prof = prof_on();
+    std::vector<const ClassList *> act;
+    std::vector<double> cost;
     for (const ClassList &cl : W->classes) {
         if (cl.total == 0) continue;
+        double fp = 0.0, fq = 0.0;
+        class_flops(cl.cb, cl.ck, &fp, &fq);
+        act.push_back(&cl);
+        cost.push_back(fp * (double)cl.prim_quartets + fq * (double)cl.total);
+    }
+    return run_forked(s, cost, [&](int i, hipStream_t st) {
+        const ClassList &cl = *act[i];
         ClassLaunch L;
-        fill_class_launch(B, cl, s, L);
+        fill_class_launch(B, cl, st, L);
         // arithmetic of this class: a build asked for in FP32 runs a class in
         // FP64 where the FP32 form table says its FP64 kernel is faster
         const int cp = (prec == MESS_FP32 && class_form(cl.cb, cl.ck, MESS_FP32) == kFormFp64) ? MESS_FP64 : prec;
@@ -81,16 +205,16 @@ int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int p
             double fp = 0.0, fq = 0.0;
             class_flops(cl.cb, cl.ck, &fp, &fq, cp);
             // FP32 launches are recorded under class index + 64
-            prof_record(s, class_index(cl.cb, cl.ck) + (cp == MESS_FP32 ? 64 : 0), true, cl.total,
+            prof_record(st, class_index(cl.cb, cl.ck) + (cp == MESS_FP32 ? 64 : 0), true, cl.total,
                         cl.prim_quartets,
                         fp * (double)cl.prim_quartets + fq * (double)cl.total);
         }
         MESS_TRY(dispatch_class(cl.cb, cl.ck, [&](auto CB, auto CK) {
             return ClassOps<decltype(CB)::value, decltype(CK)::value>::jk(L, D, Gj, Gk, cp);
         }));
-        if (prof) prof_record(s, 0, false, 0, 0, 0.0);
-    }
-    return MESS_OK;
+        if (prof) prof_record(st, 0, false, 0, 0, 0.0);
+        return (int)MESS_OK;
+    });
 }
 
 int jk_full(mess_basis *B, const double *D, double *J, double *K, int mode, int prec, double tau,
@@ -177,15 +301,22 @@ int mess_eri(const mess_basis *basis, int32_t layout, int32_t prec, double schwa
     WorkLists *W = nullptr;
     MESS_TRY(get_work_lists(B, schwarz_tol, s, &W));
     MESS_TRY(zero_async(static_cast<double *>(out), N * N * N * N, s));
+    std::vector<const ClassList *> act;
+    std::vector<double> cost;
     for (const ClassList &cl : W->classes) {
         if (cl.total == 0) continue;
-        ClassLaunch L;
-        fill_class_launch(B, cl, s, L);
-        MESS_TRY(dispatch_class(cl.cb, cl.ck, [&](auto CB, auto CK) {
-            return ClassOps<decltype(CB)::value, decltype(CK)::value>::dense(L, static_cast<double *>(out), prec);
-        }));
+        double fp = 0.0, fq = 0.0;
+        class_flops(cl.cb, cl.ck, &fp, &fq);
+        act.push_back(&cl);
+        cost.push_back(fp * (double)cl.prim_quartets + fq * (double)cl.total);
     }
-    return MESS_OK;
+    return run_forked(s, cost, [&](int i, hipStream_t st) {
+        ClassLaunch L;
+        fill_class_launch(B, *act[i], st, L);
+        return dispatch_class(act[i]->cb, act[i]->ck, [&](auto CB, auto CK) {
+            return ClassOps<decltype(CB)::value, decltype(CK)::value>::dense(L, static_cast<double *>(out), prec);
+        });
+    });
 }
 
 int mess_jk(const mess_basis *basis, const double *D, double *J, double *K, int32_t mode, int32_t prec,
