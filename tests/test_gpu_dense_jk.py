@@ -86,3 +86,40 @@ def test_dense_jk_forms_agree_and_edges(case):
     assert np.max(np.abs(host(J1)[0] - Jo[0])) <= 1e-11 * max(1.0, np.abs(Jo[0]).max())
     with pytest.raises(mess.MessError):
         mess.mess_jk_dense(eri64, N, D, J1, None, form=7)
+
+
+@pytest.mark.parametrize("n,nd,offset", [(1, 1, 0), (2, 3, 1), (3, 16, 0), (4, 17, 1), (7, 32, 1), (8, 33, 0),
+                                         (15, 65, 0), (16, 64, 1), (17, 16, 0), (18, 130, 1), (40, 200, 1)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_dense_jk_tile_edges(n, nd, offset, prec):
+    """Matrix-core form at the edges of its tiles (16 columns, 32 and 48 rows,
+    16/32/64 densities), operands an element off 16-byte alignment, no
+    symmetry in either operand.  Bar: n^2 roundings of the sums of
+    magnitudes."""
+    mess = need_gpu()
+    torch = pytest.importorskip("torch")
+    announce(f"dense J/K n={n} nd={nd} offset={offset} {prec}")
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    p = mess.MESS_FP64 if prec == "fp64" else mess.MESS_FP32
+    gen = torch.Generator().manual_seed(n * 1000 + nd)
+    Eh = torch.randn(n, n, n, n, dtype=dt, generator=gen)
+    Dh = torch.randn(nd, n, n, dtype=dt, generator=gen)
+
+    def put(x):
+        flat = torch.empty(x.numel() + offset, dtype=dt, device="cuda")
+        flat[offset:] = x.flatten().cuda()
+        return flat[offset:].view(x.shape)
+
+    E, D = put(Eh), put(Dh)
+    A64 = Eh.double().reshape(n * n, n * n), Eh.double().permute(0, 2, 1, 3).reshape(n * n, n * n)
+    D64 = Dh.double().reshape(nd, n * n)
+    for which in ("JK", "J", "K"):
+        J = torch.full((nd, n, n), 7.0, dtype=dt, device="cuda") if "J" in which else None
+        K = torch.full((nd, n, n), 7.0, dtype=dt, device="cuda") if "K" in which else None
+        mess.mess_jk_dense(E, n, D, J, K, prec=p, form=mess.MESS_DENSE_MFMA)
+        for X, A in ((J, A64[0]), (K, A64[1])):
+            if X is None:
+                continue
+            err = (X.cpu().double().reshape(nd, n * n) - D64 @ A.T).abs()
+            bar = n * n * torch.finfo(dt).eps * (D64.abs() @ A.abs().T)
+            assert bool((err <= bar).all()), (which, float((err / bar).max()))
