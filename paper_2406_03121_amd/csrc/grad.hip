@@ -346,14 +346,23 @@ extern "C" int mess_hf_gradient(const mess_basis *basis, const double *D, const 
     one(k_grad_1e<2, 1>, 4);
     one(k_grad_1e<2, 2>, 5);
     MESS_LAUNCH_CHECK();
+    std::vector<const ClassList *> act;
+    std::vector<double> cost;
     for (const ClassList &cl : W->classes) {
         if (cl.total == 0) continue;
-        ClassLaunch L;
-        MESS_TRY(fill_class_launch(B, cl, s, L));
-        MESS_TRY(dispatch_class(cl.cb, cl.ck, [&](auto CB, auto CK) {
-            return GradOps<decltype(CB)::value, decltype(CK)::value>::run(G, L);
-        }));
+        double fp = 0.0, fq = 0.0;
+        class_flops(cl.cb, cl.ck, &fp, &fq);
+        act.push_back(&cl);
+        cost.push_back(fp * (double)cl.prim_quartets + fq * (double)cl.total);
     }
+    MESS_TRY(run_forked(s, cost, [&](int i, hipStream_t st) {
+        const ClassList &cl = *act[i];
+        ClassLaunch L;
+        MESS_TRY(fill_class_launch(B, cl, st, L));
+        return dispatch_class(cl.cb, cl.ck, [&](auto CB, auto CK) {
+            return GradOps<decltype(CB)::value, decltype(CK)::value>::run(G, L);
+        });
+    }));
     hipLaunchKernelGGL(k_grad_finish, dim3((unsigned)((3 * nat + 63) / 64)), dim3(64), 0, s, nat, B->d_xyz, B->d_Zd,
                        copies, d_g);
     MESS_LAUNCH_CHECK();

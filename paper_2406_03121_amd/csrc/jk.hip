@@ -129,10 +129,7 @@ static void side_release(SideSet *set) {
     g_side_free.push_back(set);
 }
 
-// Launches work(i, stream) for every i < cost.size() on s and the side
-// streams; all of it is complete before what s runs next.
-template <typename F>
-static int run_forked(hipStream_t s, const std::vector<double> &cost, F &&work) {
+int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work) {
     // few classes with little work each (s and p shells of a small molecule: up
     // to six of 15-25 us) end sooner one after another than the fork and the
     // join take (30-function J/K 109 and 151 us, its tensor 75 and 151); with

@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <functional>
 #include <map>
 #include <string>
 #include <utility>
@@ -228,6 +229,12 @@ bool rows_compiled(int cb, int ck);   // bra-segment kernel built for the class
 
 // Profiling of class launches (HIP events on the launch stream).
 bool prof_on();
+
+// Launches work(i, stream) for every i < cost.size() on s and side streams
+// (jk.hip), the costliest first; all of it is complete before what s runs
+// next.  One after another on s for few or short launches (all the costs, in
+// operations or bytes, below 1e9), under capture and while profiling.
+int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work);
 void prof_record(hipStream_t s, int cls, bool begin, int64_t quartets, int64_t prims, double flops);
 
 struct WorkLists {

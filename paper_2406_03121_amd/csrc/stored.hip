@@ -112,20 +112,27 @@ int jk_stored(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, 
     MESS_TRY(get_stored(B, prec, tau, s, &W, &E));
     MESS_TRY(zero_halves(B, Gj, Gk, s));
     const bool prof = prof_on();
-    for (size_t c = 0; c < W->classes.size(); ++c) {
+    std::vector<size_t> act;
+    std::vector<double> cost;
+    for (size_t c = 0; c < W->classes.size(); ++c)
+        if (W->classes[c].total > 0) {
+            act.push_back(c);
+            cost.push_back((double)E->bytes[c]);
+        }
+    return run_forked(s, cost, [&](int i, hipStream_t st) {
+        const size_t c = act[i];
         const ClassList &cl = W->classes[c];
-        if (cl.total == 0) continue;
         ClassLaunch L;
-        fill_class_launch(B, cl, s, L);
+        fill_class_launch(B, cl, st, L);
         // recorded under class index + 32, with the bytes streamed in the
         // operation-count field
-        if (prof) prof_record(s, 32 + class_index(cl.cb, cl.ck), true, cl.total, cl.prim_quartets, (double)E->bytes[c]);
+        if (prof) prof_record(st, 32 + class_index(cl.cb, cl.ck), true, cl.total, cl.prim_quartets, (double)E->bytes[c]);
         MESS_TRY(dispatch_class(cl.cb, cl.ck, [&](auto CB, auto CK) {
             return ClassOps<decltype(CB)::value, decltype(CK)::value>::jk_stored(L, E->base[c], prec, D, Gj, Gk);
         }));
-        if (prof) prof_record(s, 0, false, 0, 0, 0.0);
-    }
-    return MESS_OK;
+        if (prof) prof_record(st, 0, false, 0, 0, 0.0);
+        return (int)MESS_OK;
+    });
 }
 
 // ------------------------------------------------------------ ERI blocks

@@ -133,13 +133,15 @@ def test_shared_quartets_match_single_lanes(waters):
     B.close()
 
 
-def test_class_streams_order_and_capture():
+@pytest.mark.parametrize("mode", ["direct", "stored"])
+def test_class_streams_order_and_capture(mode):
     """The classes of a build run on several streams between a fork and a
     join: calls on two streams at once, buffers overwritten right after a call
     on its stream, and a captured call (one stream) all give the eager result
     (same terms, order of the atomics aside: 1e-12 * max(1, |x|))."""
     import torch
     mess = need_gpu()
+    mode = mess.MESS_JK_STORED if mode == "stored" else mess.MESS_JK_DIRECT
     mols = [G.water_cluster(k, n_waters=2, box=8.0) for k in (1, 2)]
     Bs = [mess.basis_from_molecule(m) for m in mols]
     N = mols[0].n_bf
@@ -147,7 +149,7 @@ def test_class_streams_order_and_capture():
     ref = []
     for B, D in zip(Bs, Ds):
         J, K = zeros(N, N), zeros(N, N)
-        mess.mess_jk(B, D, J, K, schwarz_tol=1e-10)
+        mess.mess_jk(B, D, J, K, schwarz_tol=1e-10, mode=mode)
         ref.append((host(J), host(K)))
     bar = [tuple(1e-12 * max(1.0, np.abs(x).max()) for x in r) for r in ref]
     streams = [torch.cuda.Stream() for _ in Bs]
@@ -157,7 +159,7 @@ def test_class_streams_order_and_capture():
         for k, st in enumerate(streams):
             with torch.cuda.stream(st):
                 D = Ds[k].clone()
-                mess.mess_jk(Bs[k], D, *out[k], schwarz_tol=1e-10)
+                mess.mess_jk(Bs[k], D, *out[k], schwarz_tol=1e-10, mode=mode)
                 D.fill_(float("nan"))  # ordered after the call on its stream
         torch.cuda.synchronize()
         for k in range(2):
@@ -165,12 +167,12 @@ def test_class_streams_order_and_capture():
                 assert np.abs(host(a) - b).max() <= t
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
-        mess.mess_jk(Bs[0], Ds[0], *out[0], schwarz_tol=1e-10)
+        mess.mess_jk(Bs[0], Ds[0], *out[0], schwarz_tol=1e-10, mode=mode)
     for _ in range(3):
         for x in out[0]:
             x.zero_()
         g.replay()
-        mess.mess_jk(Bs[1], Ds[1], *out[1], schwarz_tol=1e-10)  # eager work between the replays
+        mess.mess_jk(Bs[1], Ds[1], *out[1], schwarz_tol=1e-10, mode=mode)  # eager work between the replays
         torch.cuda.synchronize()
         for k in range(2):
             for a, b, t in zip(out[k], ref[k], bar[k]):
