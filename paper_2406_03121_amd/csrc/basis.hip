@@ -31,33 +31,66 @@ void set_error(const char *fmt, ...) {
 // (all terms positive), lower orders by the stable downward recurrence
 //   F_n = (2T F_{n+1} + e^{-T}) / (2n+1).
 
-static void build_boys_table(std::vector<double> &tab, std::vector<double> &etab, std::vector<double> &tabt) {
-    tab.assign((size_t)kBoysRows * kBoysN, 0.0);
-    etab.assign(kBoysRows, 0.0);
-    tabt.assign((size_t)kBoysTL * kBoysRows * 8, 0.0);
-    for (int k = 0; k < kBoysRows; ++k) {
-        const long double T = (long double)k / (long double)kBoysInvStep;
-        const long double eT = expl(-T);
-        const int n = kBoysN - 1;
-        long double term = 1.0L / (2 * n + 1), sum = term;
-        for (int i = 1; i < 4000; ++i) {
-            term *= 2.0L * T / (long double)(2 * n + 2 * i + 1);
-            sum += term;
-            if (term < 1e-22L * sum) break;
-        }
+// tabt: per order L < 9 and quarter-wide interval the polynomial of degree 8
+// through F_L at the interval's nine Chebyshev nodes, in powers of u in
+// [-1, 1], and exp(-T_k) of the middle.  Built once per process.
+
+static void boys_ld(long double T, long double (&F)[kBoysN]) {
+    const long double eT = expl(-T);
+    const int n = kBoysN - 1;
+    long double term = 1.0L / (2 * n + 1), sum = term;
+    for (int i = 1; i < 4000; ++i) {
+        term *= 2.0L * T / (long double)(2 * n + 2 * i + 1);
+        sum += term;
+        if (term < 1e-22L * sum) break;
+    }
+    F[n] = eT * sum;
+    for (int m = n - 1; m >= 0; --m) F[m] = (2.0L * T * F[m + 1] + eT) / (long double)(2 * m + 1);
+}
+
+struct BoysTables {
+    std::vector<double> tab, etab, tabt;
+    BoysTables() : tab((size_t)kBoysRows * kBoysN), etab(kBoysRows), tabt((size_t)kBoysTL * kBoysPRows * kBoysPW) {
         long double F[kBoysN];
-        F[n] = eT * sum;
-        for (int m = n - 1; m >= 0; --m) F[m] = (2.0L * T * F[m + 1] + eT) / (long double)(2 * m + 1);
-        for (int m = 0; m < kBoysN; ++m) tab[(size_t)k * kBoysN + m] = (double)F[m];
-        etab[k] = (double)eT;
-        for (int L = 0; L < kBoysTL; ++L) {
-            long double fact = 1.0L;
-            for (int i = 0; i < 8; ++i) {
-                if (i > 0) fact *= (long double)i;
-                tabt[((size_t)L * kBoysRows + k) * 8 + i] = (double)(F[L + i] / fact);
+        for (int k = 0; k < kBoysRows; ++k) {
+            const long double T = (long double)k / (long double)kBoysInvStep;
+            boys_ld(T, F);
+            for (int m = 0; m < kBoysN; ++m) tab[(size_t)k * kBoysN + m] = (double)F[m];
+            etab[k] = (double)expl(-T);
+        }
+        constexpr int NC = kBoysPW - 1;
+        const long double pi = acosl(-1.0L);
+        long double node[NC], c[NC][NC], P[NC][NC] = {};  // nodes, T_n(node_j), T_n's coefficients
+        for (int j = 0; j < NC; ++j) {
+            node[j] = cosl(pi * (j + 0.5L) / NC);
+            for (int n = 0; n < NC; ++n) c[n][j] = cosl(pi * n * (j + 0.5L) / NC);
+        }
+        P[0][0] = P[1][1] = 1.0L;
+        for (int n = 2; n < NC; ++n)
+            for (int i = 0; i < NC; ++i) P[n][i] = (i > 0 ? 2.0L * P[n - 1][i - 1] : 0.0L) - P[n - 2][i];
+        for (int k = 0; k < kBoysPRows; ++k) {
+            const long double mid = (k + 0.5L) / 4.0L;
+            long double f[NC][kBoysN];
+            for (int j = 0; j < NC; ++j) boys_ld(mid + node[j] / 8.0L, f[j]);
+            for (int L = 0; L < kBoysTL; ++L) {
+                long double a[NC] = {};
+                for (int n = 0; n < NC; ++n) {
+                    long double s = 0.0L;
+                    for (int j = 0; j < NC; ++j) s += f[j][L] * c[n][j];
+                    s *= (n > 0 ? 2.0L : 1.0L) / NC;
+                    for (int i = 0; i <= n; ++i) a[i] += s * P[n][i];
+                }
+                double *row = tabt.data() + ((size_t)L * kBoysPRows + k) * kBoysPW;
+                for (int i = 0; i < NC; ++i) row[i] = (double)a[i];
+                row[NC] = (double)expl(-mid);
             }
         }
     }
+};
+
+static const BoysTables &boys_tables() {
+    static const BoysTables t;
+    return t;
 }
 
 // ------------------------------------------------ normalisation (host)
@@ -736,9 +769,7 @@ static int create_impl(int n_mol, const int32_t *mol_natom, const int32_t *mol_n
     MESS_HIP(hipGetDevice(&B->device));
 
     // Boys tables
-    std::vector<double> tab, etab;
-    std::vector<double> tabt;
-    build_boys_table(tab, etab, tabt);
+    const std::vector<double> &tab = boys_tables().tab, &etab = boys_tables().etab, &tabt = boys_tables().tabt;
     std::vector<float> tabf(tab.begin(), tab.end()), etabf(etab.begin(), etab.end());
     MESS_HIP(hipMalloc(&B->d_boys, sizeof(double) * tab.size()));
     MESS_HIP(hipMalloc(&B->d_boys_exp, sizeof(double) * etab.size()));

@@ -2,9 +2,9 @@
 // closed-form electron repulsion integrals reduce to it), evaluated by the
 // device routines that the integral kernels call, so that they can be checked
 // on their own:
-//   form 0: F_0..F_m together, as the recursion kernels take them: Taylor
-//           sum of F_m about the nearest grid point T_k = k/16 (T < 60),
-//           downward recurrence F_j = (2T F_{j+1} + exp(-T)) / (2j+1), and
+//   form 0: F_0..F_m together, as the recursion kernels take them: F_m by
+//           its polynomial of the quarter-wide interval (T < 60; FP32 by the
+//           Taylor sum about the nearest grid point T_k = k/16), downward recurrence F_j = (2T F_{j+1} + exp(-T)) / (2j+1), and
 //           the large-T form (2j-1)!!/(2T)^j sqrt(pi/T)/2 for T >= 60;
 //   form 1: each F_j on its own (Taylor sum of order j, no recurrence), as
 //           the table-driven kernel takes them.

@@ -117,10 +117,16 @@ int ClassOps<MESS_CB, MESS_CK>::jk(const ClassLaunch &L, const double *D, double
                 hipLaunchKernelGGL((k_jk_rows<Dm, float, true>), dim3(g), dim3(256), lds, L.stream, L.pairs,
                                    L.bra_off, L.ket_off, L.same_class, L.rowstart, L.rowmap, L.segs, L.nseg,
                                    (const float *)nullptr, L.total, D, Gj, Gk, L.ppf, bt);
-            else
+            else {
+                // 19 KB of Boys rows beside the K rows: together beyond the
+                // 64 KB that a launch may take unasked
+                if (lds > 44 * 1024)
+                    MESS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_jk_rows<Dm, double, true>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 48 * 1024));
                 hipLaunchKernelGGL((k_jk_rows<Dm, double, true>), dim3(g), dim3(256), lds, L.stream, L.pairs,
                                    L.bra_off, L.ket_off, L.same_class, L.rowstart, L.rowmap, L.segs, L.nseg,
                                    (const double *)nullptr, L.total, D, Gj, Gk, L.pp, bt);
+            }
             MESS_LAUNCH_CHECK();
             return MESS_OK;
         }

@@ -87,38 +87,40 @@ __device__ __forceinline__ void boys_f64(double T, const double *__restrict__ ta
 struct BoysTabs {
     const double *tab, *etab;
     const float *tabf, *etabf;
-    const double *tabt;  // F_{L+i}(T_k) / i! per order L (FP64 Taylor with no per-term scaling)
+    const double *tabt;  // polynomial rows per order L
 };
 
-// FP64 F_0..F_L as boys_f64, the Taylor sums in Horner form on the
-// prescaled table (F_{L+i}(T_k)/i!) and the constants 1/i! for exp(-T):
-// seven FMAs each.
+// FP64 F_0..F_L as boys_f64 from rows = the polynomial table of order L:
+// intervals four times as wide as the Taylor grid's spacing and one
+// coefficient more keep the order's rows in 19 KB, so that they fit a CU's
+// first cache or its LDS (the lanes of a wave read as many different rows,
+// which bounds the low classes: (ss|ss) of 20 waters 2.0 ms from the Taylor
+// table's 62 KB an order, see k_jk_rows).  Truncation below 1e-17 relative
+// (Chebyshev interpolation in each interval).
+// exp(-T) = exp(-T_k) exp(-u/8), degree 9, constants from the same
+// interpolation.  Largest relative errors over 30000 arguments as those of
+// the Taylor sums (2.1e-16 for F_L, 7.8e-16 for F_0 after eight steps down).
 template <int L>
-__device__ __forceinline__ void boys_f64t(double T, const double *__restrict__ tabt, const double *__restrict__ etab,
-                                          double (&F)[L + 1]) {
+__device__ __forceinline__ void boys_poly(double T, const double *__restrict__ rows, double (&F)[L + 1]) {
     if (T < kBoysTmax) {
-        const int k = __double2int_rn(T * kBoysInvStep);
-        const double md = static_cast<double>(k) * (1.0 / kBoysInvStep) - T;  // -(T - T_k), exact
-        const double *row = tabt + ((size_t)L * kBoysRows + k) * 8;
-        double f = row[7];
-        f = row[6] + md * f;
-        f = row[5] + md * f;
-        f = row[4] + md * f;
-        f = row[3] + md * f;
-        f = row[2] + md * f;
-        f = row[1] + md * f;
-        f = row[0] + md * f;
+        const int k = (int)(T * 4.0);
+        const double u = fma(T, 8.0, -(double)(2 * k + 1));
+        const double *row = rows + k * kBoysPW;
+        double f = row[8];
+        static_for<0, 8>([&](auto I) { f = fma(u, f, row[7 - decltype(I)::value]); });
         F[L] = f;
         if constexpr (L > 0) {
-            double e = 1.0 / 5040.0;
-            e = 1.0 / 720.0 + md * e;
-            e = 1.0 / 120.0 + md * e;
-            e = 1.0 / 24.0 + md * e;
-            e = 1.0 / 6.0 + md * e;
-            e = 0.5 + md * e;
-            e = 1.0 + md * e;
-            e = 1.0 + md * e;
-            e *= etab[k];
+            double e = -2.0605739337042904759e-14;
+            e = fma(u, e, 1.478975969471107947e-12);
+            e = fma(u, e, -9.4610406314865613808e-11);
+            e = fma(u, e, 5.2981899881232587524e-09);
+            e = fma(u, e, -2.5431315112608985466e-07);
+            e = fma(u, e, 1.0172526041935751529e-05);
+            e = fma(u, e, -0.00032552083333332014221);
+            e = fma(u, e, 0.0078124999999999583666);
+            e = fma(u, e, -0.125);
+            e = fma(u, e, 1.0);
+            e *= row[9];
             const double t2 = 2.0 * T;
             static_for<0, L>([&](auto I) {
                 constexpr int m = L - 1 - decltype(I)::value;
@@ -133,6 +135,11 @@ __device__ __forceinline__ void boys_f64t(double T, const double *__restrict__ t
             F[m + 1] = F[m] * ((2 * m + 1) * 0.5) * rT;
         });
     }
+}
+
+template <int L>
+__device__ __forceinline__ void boys_f64t(double T, const double *__restrict__ tabt, double (&F)[L + 1]) {
+    boys_poly<L>(T, tabt + (size_t)L * (kBoysPRows * kBoysPW), F);
 }
 
 template <int L>
@@ -171,9 +178,19 @@ __device__ __forceinline__ void boys_f32(float T, const BoysTabs &bt, float (&F)
 template <int L, typename Real>
 __device__ __forceinline__ void boys_eval(Real T, const BoysTabs &bt, Real (&F)[L + 1]) {
     if constexpr (sizeof(Real) == 8)
-        boys_f64t<L>(T, bt.tabt, bt.etab, F);
+        boys_f64t<L>(T, bt.tabt, F);
     else
         boys_f32<L>(T, bt, F);
+}
+
+// The polynomial rows of a kernel's own order, staged in LDS.
+struct BoysLds {
+    const double *rows;
+};
+
+template <int L, typename Real>
+__device__ __forceinline__ void boys_eval(Real T, const BoysLds &bt, Real (&F)[L + 1]) {
+    boys_poly<L>(T, bt.rows, F);
 }
 
 template <typename Real> struct PrimPairOf;
@@ -299,9 +316,9 @@ __host__ __device__ constexpr int ket_group_mask(const Cart c) {
 //
 // prim_base: the base values [00|00]^(m) = 2 pi^{5/2} K_P K_Q /
 // (p q sqrt(p+q)) F_m(T), m = 0..L, of one primitive quartet.
-template <int L, typename Real>
+template <int L, typename Real, class BT>
 __device__ __forceinline__ void prim_base(const PrimPairT<Real> &P, const PrimPairT<Real> &Q, const Real (&AC)[3],
-                                          const BoysTabs &bt, Real (&V0)[L + 1]) {
+                                          const BT &bt, Real (&V0)[L + 1]) {
     const Real p = P.p, q = Q.p;
     const Real spq = rsqrt_nr(p + q);
     const Real rho = p * q * (spq * spq);
@@ -313,9 +330,9 @@ __device__ __forceinline__ void prim_base(const PrimPairT<Real> &P, const PrimPa
     static_for<0, L + 1>([&](auto M) { V0[decltype(M)::value] = pref * F[decltype(M)::value]; });
 }
 
-template <class Dm, typename Real, int SUB = 63, bool PRE = false, class Out>
+template <class Dm, typename Real, int SUB = 63, bool PRE = false, class BT, class Out>
 __device__ __forceinline__ void prim_quartet(const PrimPairT<Real> &P, const PrimPairT<Real> &Q,
-                                                 const Real (&AC)[3], const BoysTabs &bt, Out &&out,
+                                                 const Real (&AC)[3], const BT &bt, Out &&out,
                                                  const Real *pre = nullptr) {
     constexpr int L = Dm::L, NE = Dm::NE, NF = Dm::NF, LA = Dm::LA, LC = Dm::LC, LCD = Dm::LCD;
     const Real p = P.p, q = Q.p;
@@ -460,9 +477,9 @@ __device__ constexpr double comp_scale(int local) {
 // P > 1: a group of P consecutive lanes shares the quartet; lane sub of the
 // group takes every P-th primitive quartet, the contracted intermediates are
 // summed over the group, and every lane of it returns the whole block.
-template <class Dm, typename Real, int P = 1>
+template <class Dm, typename Real, int P = 1, class BT>
 __device__ __forceinline__ void eri_quartet(const PairInfo &bra, const PairInfo &ket,
-                                            const PrimPairT<Real> *__restrict__ pp, const BoysTabs &bt,
+                                            const PrimPairT<Real> *__restrict__ pp, const BT &bt,
                                             Real (&out)[Dm::NOUT], int sub = 0) {
     // acc[f - F0][e - E0] = contracted [e0|f0], e on the bra side.  The
     // per-lane kernels keep the bra on the e side in every class: their

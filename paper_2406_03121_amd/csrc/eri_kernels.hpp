@@ -241,7 +241,8 @@ __global__ void __launch_bounds__(128) k_jk_stored(const PairInfo *__restrict__ 
 // per quartet.  This cuts the FP64 global atomics, which bound the
 // streaming digestion and much of the direct one for the low classes, by a
 // factor of up to six.  DIRECT: each quartet's block is computed by the
-// recursion instead of read from the store (base unused).
+// recursion instead of read from the store (base unused), in FP64 with the
+// Boys rows of the class's order in LDS (static, beside the dynamic K rows).
 template <class Dm, typename Real, bool DIRECT = false>
 __global__ void __launch_bounds__(256) k_jk_rows(const PairInfo *__restrict__ pairs, int bra_off, int ket_off,
                                                         int same_class, const int64_t *__restrict__ rowstart,
@@ -252,7 +253,13 @@ __global__ void __launch_bounds__(256) k_jk_rows(const PairInfo *__restrict__ pa
                                                         const PrimPairT<Real> *__restrict__ pp = nullptr,
                                                         BoysTabs bt = BoysTabs{}) {
     constexpr int NA = Dm::NA, NB = Dm::NB, NC = Dm::NC, ND = Dm::ND;
+    constexpr bool STAGE = DIRECT && sizeof(Real) == 8;
     extern __shared__ double lds[];
+    __shared__ __align__(16) double btab[STAGE ? kBoysPRows * kBoysPW : 1];
+    if constexpr (STAGE) {
+        const double2 *src = reinterpret_cast<const double2 *>(bt.tabt + (size_t)Dm::L * (kBoysPRows * kBoysPW));
+        for (int e = threadIdx.x; e < kBoysPRows * kBoysPW / 2; e += 256) reinterpret_cast<double2 *>(btab)[e] = src[e];
+    }
     for (int sidx = blockIdx.x; sidx < nseg; sidx += gridDim.x) {
         const int4 sg = segs[sidx];
         const int i = rowmap[sg.x].x;
@@ -277,7 +284,9 @@ __global__ void __launch_bounds__(256) k_jk_rows(const PairInfo *__restrict__ pa
             const PairInfo ket = pairs[ket_off + j];
             const int c0 = ket.bfa, d0 = ket.bfb;
             Real out[Dm::NOUT];
-            if constexpr (DIRECT)
+            if constexpr (STAGE)
+                eri_quartet<Dm, Real>(bra, ket, pp, BoysLds{btab}, out);
+            else if constexpr (DIRECT)
                 eri_quartet<Dm, Real>(bra, ket, pp, bt, out);
             else
                 static_for<0, Dm::NOUT>([&](auto I) { out[I] = base[(int64_t)decltype(I)::value * total + q]; });

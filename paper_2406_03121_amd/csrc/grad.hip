@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(64) k_grad_1e(GradLists G, int off, const doub
                 const double PA[3] = {P.PAx, P.PAy, P.PAz}, X[3] = {A0 + PA[0], A1 + PA[1], A2 + PA[2]};
                 const double rp = 1.0 / P.p, pref = z * rp * P.K;
                 double F[LAB + 2], R[cart_off(LAB + 2)];
-                boys_f64t<LAB + 1>(P.p * (X[0] * X[0] + X[1] * X[1] + X[2] * X[2]), G.tabt, G.etab, F);
+                boys_f64t<LAB + 1>(P.p * (X[0] * X[0] + X[1] * X[1] + X[2] * X[2]), G.tabt, F);
                 hermite_r<LAB + 1>(P.p, X, F, R);
                 using H = Herm1<LA, LB>;
                 H E[3];

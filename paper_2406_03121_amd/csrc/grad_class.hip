@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(256) k_grad_lane(GradLists G, int bra_off, int
             const double spq = rsqrt_nr(P.p + Q.p), alpha = P.p * Q.p * spq * spq;
             const double X[3] = {AC[0] + (P.PAx - Q.PAx), AC[1] + (P.PAy - Q.PAy), AC[2] + (P.PAz - Q.PAz)};
             double F[N1 + 1], R[cart_off(N1 + 1)];
-            boys_f64t<N1>(alpha * (X[0] * X[0] + X[1] * X[1] + X[2] * X[2]), G.tabt, G.etab, F);
+            boys_f64t<N1>(alpha * (X[0] * X[0] + X[1] * X[1] + X[2] * X[2]), G.tabt, F);
             hermite_r<N1>(alpha, X, F, R);
             const double rp = 1.0 / P.p, rq = 1.0 / Q.p;
             const double pref = k2Pi52 * rp * rq * spq * P.K * Q.K;
