@@ -31,9 +31,9 @@ void set_error(const char *fmt, ...) {
 // (all terms positive), lower orders by the stable downward recurrence
 //   F_n = (2T F_{n+1} + e^{-T}) / (2n+1).
 
-// tabt: per order L < 9 and quarter-wide interval the polynomial of degree 8
-// through F_L at the interval's nine Chebyshev nodes, in powers of u in
-// [-1, 1], and exp(-T_k) of the middle.  Built once per process.
+// tabt: per order L < 9 and quarter-wide interval about T_k = k/4 the
+// polynomial of degree 8 through F_L at the interval's nine Chebyshev nodes,
+// in powers of u = 4 T - k, and exp(-T_k).  Built once per process.
 
 static void boys_ld(long double T, long double (&F)[kBoysN]) {
     const long double eT = expl(-T);
@@ -69,7 +69,7 @@ struct BoysTables {
         for (int n = 2; n < NC; ++n)
             for (int i = 0; i < NC; ++i) P[n][i] = (i > 0 ? 2.0L * P[n - 1][i - 1] : 0.0L) - P[n - 2][i];
         for (int k = 0; k < kBoysPRows; ++k) {
-            const long double mid = (k + 0.5L) / 4.0L;
+            const long double mid = k / 4.0L;
             long double f[NC][kBoysN];
             for (int j = 0; j < NC; ++j) boys_ld(mid + node[j] / 8.0L, f[j]);
             for (int L = 0; L < kBoysTL; ++L) {
@@ -81,7 +81,7 @@ struct BoysTables {
                     for (int i = 0; i <= n; ++i) a[i] += s * P[n][i];
                 }
                 double *row = tabt.data() + ((size_t)L * kBoysPRows + k) * kBoysPW;
-                for (int i = 0; i < NC; ++i) row[i] = (double)a[i];
+                for (int i = 0; i < NC; ++i) row[i] = (double)(a[i] * (1 << i));  // nodes in 2 u
                 row[NC] = (double)expl(-mid);
             }
         }

@@ -16,7 +16,8 @@ namespace mess {
 // ------------------------------------------------------------------ Boys
 //
 // F_n(T) = int_0^1 t^{2n} exp(-T t^2) dt.
-// T < 60: the highest order needed, F_L, from an 8-term Taylor expansion
+// (boys_f64; the FP64 recursion kernels take F_L and exp(-T) from boys_poly
+// below.)  T < 60: the highest order needed, F_L, from an 8-term Taylor expansion
 // about the nearest grid point T_k = k/16 (|T - T_k| <= 1/32, truncation
 // below 3e-17 relative) using dF_n/dT = -F_{n+1}; exp(-T) the same way from
 // exp(-T_k); then the downward recurrence F_n = (2T F_{n+1} + e^{-T})/(2n+1),
@@ -37,6 +38,15 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 __device__ __forceinline__ float rsqrt_nr(float x) {
     const float y = __builtin_amdgcn_rsqf(x);
     return y * fmaf(-0.5f * x * y, y, 1.5f);
+}
+
+// The same in one step of third order, y (1 + e/2 + 3 e^2/8) with e = 1 - x
+// y^2 (the estimate's e <= 2^-22 leaves e^3 5/16 < 2^-67): five operations
+// for seven.
+__device__ __forceinline__ double rsqrt_3(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
 template <int L>
@@ -88,37 +98,44 @@ struct BoysTabs {
     const double *tab, *etab;
     const float *tabf, *etabf;
     const double *tabt;  // polynomial rows per order L
+    static constexpr bool kFromQ = false;
 };
 
 // FP64 F_0..F_L as boys_f64 from rows = the polynomial table of order L:
 // intervals four times as wide as the Taylor grid's spacing and one
 // coefficient more keep the order's rows in 19 KB, so that they fit a CU's
-// first cache or its LDS (the lanes of a wave read as many different rows,
-// which bounds the low classes: (ss|ss) of 20 waters 2.0 ms from the Taylor
-// table's 62 KB an order, see k_jk_rows).  Truncation below 1e-17 relative
-// (Chebyshev interpolation in each interval).
-// exp(-T) = exp(-T_k) exp(-u/8), degree 9, constants from the same
-// interpolation.  Largest relative errors over 30000 arguments as those of
-// the Taylor sums (2.1e-16 for F_L, 7.8e-16 for F_0 after eight steps down).
-template <int L>
+// first cache or its LDS.  The lanes of a wave read as many different rows,
+// and from the Taylor table's 62 KB an order that gather bounded the low
+// classes: (ss|ss) of 20 waters 2.01 ms, 1.30 with these rows in LDS, and
+// 1.14 with BARE, which also takes the conversions out of the row's number
+// and uses rsqrt_3; (ps|ss) 1.85, 1.63, 1.51; they are now bound by vector
+// instruction issue (72 % of the cycles).  Truncation below 1e-17 relative
+// (Chebyshev interpolation in each interval); exp(-T) = exp(-T_k) exp(-u/4),
+// degree 9, constants from the same interpolation.  Largest relative errors
+// over 30000 arguments as those of the Taylor sums (2.1e-16 for F_L, 7.8e-16
+// for F_0 after eight steps down).
+template <int L, bool BARE = false>
 __device__ __forceinline__ void boys_poly(double T, const double *__restrict__ rows, double (&F)[L + 1]) {
     if (T < kBoysTmax) {
-        const int k = (int)(T * 4.0);
-        const double u = fma(T, 8.0, -(double)(2 * k + 1));
+        // nearest row; BARE without conversions: 1.5 2^52 puts the integer
+        // in the low word
+        const double t = fma(T, 4.0, 6755399441055744.0);
+        const int k = BARE ? __double2loint(t) : __double2int_rn(T * 4.0);
+        const double u = fma(T, 4.0, BARE ? 6755399441055744.0 - t : -(double)k);
         const double *row = rows + k * kBoysPW;
         double f = row[8];
         static_for<0, 8>([&](auto I) { f = fma(u, f, row[7 - decltype(I)::value]); });
         F[L] = f;
         if constexpr (L > 0) {
-            double e = -2.0605739337042904759e-14;
-            e = fma(u, e, 1.478975969471107947e-12);
-            e = fma(u, e, -9.4610406314865613808e-11);
-            e = fma(u, e, 5.2981899881232587524e-09);
-            e = fma(u, e, -2.5431315112608985466e-07);
-            e = fma(u, e, 1.0172526041935751529e-05);
-            e = fma(u, e, -0.00032552083333332014221);
-            e = fma(u, e, 0.0078124999999999583666);
-            e = fma(u, e, -0.125);
+            double e = -1.0550138540565967e-11;
+            e = fma(u, e, 3.7861784818460363e-10);
+            e = fma(u, e, -1.2110132008302799e-08);
+            e = fma(u, e, 3.3908415923988856e-07);
+            e = fma(u, e, -8.138020836034875e-06);
+            e = fma(u, e, 0.00016276041667097202);
+            e = fma(u, e, -0.002604166666666561);
+            e = fma(u, e, 0.031249999999999833);
+            e = fma(u, e, -0.25);
             e = fma(u, e, 1.0);
             e *= row[9];
             const double t2 = 2.0 * T;
@@ -128,7 +145,7 @@ __device__ __forceinline__ void boys_poly(double T, const double *__restrict__ r
             });
         }
     } else {
-        const double sT = rsqrt_nr(T), rT = sT * sT;
+        const double sT = BARE ? rsqrt_3(T) : rsqrt_nr(T), rT = sT * sT;
         F[0] = 0.88622692545275801365 * sT;  // sqrt(pi) / 2
         static_for<0, L>([&](auto I) {
             constexpr int m = decltype(I)::value;
@@ -183,14 +200,29 @@ __device__ __forceinline__ void boys_eval(Real T, const BoysTabs &bt, Real (&F)[
         boys_f32<L>(T, bt, F);
 }
 
-// The polynomial rows of a kernel's own order, staged in LDS.
+// The polynomial rows of a kernel's own order, staged in LDS.  Its callers
+// hand the recursion A - C - (Q - C) in place of A - C: three subtractions
+// fewer in the inner loop, whose Q is fixed (kFromQ).
 struct BoysLds {
     const double *rows;
+    static constexpr bool kFromQ = true;
 };
+
+// The recursion's 1/sqrt(p + q): rsqrt_3 in the segment kernels; the others
+// keep the two steps (with it, or with BARE rows, the compiler takes one to
+// eight registers too many for two waves a SIMD in the primitive-lane
+// (dd|ps): 2.15 -> 3.64 ms).
+template <class BT, typename Real>
+__device__ __forceinline__ Real rsqrt_pq(Real x) {
+    if constexpr (BT::kFromQ)
+        return rsqrt_3(x);
+    else
+        return rsqrt_nr(x);
+}
 
 template <int L, typename Real>
 __device__ __forceinline__ void boys_eval(Real T, const BoysLds &bt, Real (&F)[L + 1]) {
-    boys_poly<L>(T, bt.rows, F);
+    boys_poly<L, true>(T, bt.rows, F);
 }
 
 template <typename Real> struct PrimPairOf;
@@ -320,9 +352,11 @@ template <int L, typename Real, class BT>
 __device__ __forceinline__ void prim_base(const PrimPairT<Real> &P, const PrimPairT<Real> &Q, const Real (&AC)[3],
                                           const BT &bt, Real (&V0)[L + 1]) {
     const Real p = P.p, q = Q.p;
-    const Real spq = rsqrt_nr(p + q);
+    const Real spq = rsqrt_pq<BT>(p + q);
     const Real rho = p * q * (spq * spq);
-    const Real PQx = AC[0] + (P.PAx - Q.PAx), PQy = AC[1] + (P.PAy - Q.PAy), PQz = AC[2] + (P.PAz - Q.PAz);
+    const Real PQx = BT::kFromQ ? AC[0] + P.PAx : AC[0] + (P.PAx - Q.PAx),
+               PQy = BT::kFromQ ? AC[1] + P.PAy : AC[1] + (P.PAy - Q.PAy),
+               PQz = BT::kFromQ ? AC[2] + P.PAz : AC[2] + (P.PAz - Q.PAz);
     const Real T = rho * (PQx * PQx + PQy * PQy + PQz * PQz);
     const Real pref = P.Kr * Q.Kr * spq;  // 2 pi^{5/2} K_P K_Q / (p q sqrt(p+q))
     Real F[L + 1];
@@ -337,9 +371,11 @@ __device__ __forceinline__ void prim_quartet(const PrimPairT<Real> &P, const Pri
     constexpr int L = Dm::L, NE = Dm::NE, NF = Dm::NF, LA = Dm::LA, LC = Dm::LC, LCD = Dm::LCD;
     const Real p = P.p, q = Q.p;
     const Real pq = p + q;
-    const Real spq = rsqrt_nr(pq);
+    const Real spq = rsqrt_pq<BT>(pq);
     const Real rpq = spq * spq;
-    const Real PQx = AC[0] + (P.PAx - Q.PAx), PQy = AC[1] + (P.PAy - Q.PAy), PQz = AC[2] + (P.PAz - Q.PAz);
+    const Real PQx = BT::kFromQ ? AC[0] + P.PAx : AC[0] + (P.PAx - Q.PAx),
+               PQy = BT::kFromQ ? AC[1] + P.PAy : AC[1] + (P.PAy - Q.PAy),
+               PQz = BT::kFromQ ? AC[2] + P.PAz : AC[2] + (P.PAz - Q.PAz);
 
     Real V[NF][NE][L + 1];
     if constexpr (PRE) {
@@ -500,6 +536,10 @@ __device__ __forceinline__ void eri_quartet(const PairInfo &bra, const PairInfo 
         constexpr int x = decltype(X)::value;
         acc[x / Dm::NEA][x % Dm::NEA] += v;
     };
+    auto from = [&](const PrimPairT<Real> &Q, int d) {
+        return BT::kFromQ ? AC[d] - (d == 0 ? Q.PAx : (d == 1 ? Q.PAy : Q.PAz)) : AC[d];
+    };
+    static_assert(P == 1 || !BT::kFromQ, "shared quartets take A - C");
     if constexpr (P > 1) {
         // primitive quartets numbered ket-major, k = sub, sub + P, ...
         const int nb = bra.npp, n = nb * ket.npp, dk = P / nb, db = P - dk * nb;
@@ -526,12 +566,14 @@ __device__ __forceinline__ void eri_quartet(const PairInfo &bra, const PairInfo 
         const PrimPairT<Real> *__restrict__ pb = pp + pbu;
         for (int ik = 0; ik < ket.npp; ++ik) {
             const PrimPairT<Real> Q = pp[ket.pp0 + ik];
-            for (int ib = 0; ib < nbu; ++ib) prim_quartet<Dm, Real>(pb[ib], Q, AC, bt, add);
+            const Real X[3] = {from(Q, 0), from(Q, 1), from(Q, 2)};
+            for (int ib = 0; ib < nbu; ++ib) prim_quartet<Dm, Real>(pb[ib], Q, X, bt, add);
         }
     } else {
         for (int ik = 0; ik < ket.npp; ++ik) {
             const PrimPairT<Real> Q = pp[ket.pp0 + ik];
-            for (int ib = 0; ib < bra.npp; ++ib) prim_quartet<Dm, Real>(pp[bra.pp0 + ib], Q, AC, bt, add);
+            const Real X[3] = {from(Q, 0), from(Q, 1), from(Q, 2)};
+            for (int ib = 0; ib < bra.npp; ++ib) prim_quartet<Dm, Real>(pp[bra.pp0 + ib], Q, X, bt, add);
         }
     }
     // bra HRR for every ket index f

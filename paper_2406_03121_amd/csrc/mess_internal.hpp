@@ -137,10 +137,10 @@ constexpr int kBoysN = 16;
 constexpr double kBoysInvStep = 16.0;
 constexpr double kBoysTmax = 60.0;
 constexpr int kBoysRows = 961;  // kBoysTmax * kBoysInvStep + 1
-// Polynomial table per order L = 0..kBoysTL-1: row k serves T in [k/4, (k+1)/4)
-// with the nine coefficients of F_L in u = 8 (T - T_k), |u| <= 1 about the
-// middle T_k, lowest first, and exp(-T_k).
-constexpr int kBoysTL = 9, kBoysPRows = 240, kBoysPW = 10;
+// Polynomial table per order L = 0..kBoysTL-1: row k serves |T - k/4| <= 1/8
+// with the nine coefficients of F_L in u = 4 T - k, lowest first, and
+// exp(-k/4).
+constexpr int kBoysTL = 9, kBoysPRows = 241, kBoysPW = 10;
 
 // Pair classes (l_a, l_b), l_a >= l_b: ss ps pp ds dp dd.
 constexpr int kNumPairClasses = 6;
