@@ -943,6 +943,7 @@ int mess_batch_scf_step(mess_batch_scf *st, mess_stream stream) {
             set_error("mess_batch_scf_step: class profiling cannot be recorded inside a graph");
             return MESS_E_ARG;
         }
+        const ForkCapture streams;
         MESS_HIP(hipStreamBeginCapture(st->cap, hipStreamCaptureModeThreadLocal));
         int rc = enqueue_step(st, st->cap, kind);
         hipGraph_t g = nullptr;

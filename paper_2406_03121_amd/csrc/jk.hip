@@ -73,8 +73,9 @@ int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s) {
 // costliest first, each on the stream with the least work so far.  Sets of
 // side streams are kept in a pool: at most kMaxSets, each used by one call
 // at a time while it enqueues (a later call's work queues behind, so a set is
-// free again at once); with none left, and under capture, the classes run one
-// after another on the caller's stream.
+// free again at once); with none left, and under a caller's capture, the
+// classes run one after another on the caller's stream.  The batch's own
+// captures are lent a set until they end.
 
 constexpr int kSideStreams = 3, kMaxSets = 8;
 
@@ -88,14 +89,11 @@ static std::mutex g_side_mutex;
 static std::vector<SideSet *> g_side_free;
 static int g_side_made = 0;
 
-static SideSet *side_acquire(hipStream_t s) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
+static thread_local SideSet *t_capture_set = nullptr;  // lent to this thread's captures
+
+static SideSet *side_acquire() {
     int dev = 0;
-    if (cap != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess) return nullptr;
+    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     std::lock_guard<std::mutex> lk(g_side_mutex);
     for (size_t i = 0; i < g_side_free.size(); ++i)
         if (g_side_free[i]->device == dev) {
@@ -129,6 +127,15 @@ static void side_release(SideSet *set) {
     g_side_free.push_back(set);
 }
 
+ForkCapture::ForkCapture() {
+    if (!t_capture_set) t_capture_set = side_acquire();
+}
+
+ForkCapture::~ForkCapture() {
+    if (t_capture_set) side_release(t_capture_set);
+    t_capture_set = nullptr;
+}
+
 int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work) {
     // few classes with little work each (s and p shells of a small molecule: up
     // to six of 15-25 us) end sooner one after another than the fork and the
@@ -139,7 +146,17 @@ int run_forked(hipStream_t s, const std::vector<double> &cost, const std::functi
     const int n = (int)cost.size();
     double all = 0.0;
     for (double c : cost) all += c;
-    SideSet *set = (n >= 8 || (n > 1 && all >= 1e9)) && !prof_on() ? side_acquire(s) : nullptr;
+    SideSet *set = nullptr;
+    bool lent = false;
+    if ((n >= 8 || (n > 1 && all >= 1e9)) && !prof_on()) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+        } else {
+            lent = cap != hipStreamCaptureStatusNone;
+            set = lent ? t_capture_set : side_acquire();
+        }
+    }
     if (!set) {
         for (int i = 0; i < n; ++i) MESS_TRY(work(i, s));
         return MESS_OK;
@@ -164,10 +181,10 @@ int run_forked(hipStream_t s, const std::vector<double> &cost, const std::functi
     for (int i = 0; i + 1 < ns; ++i) {
         hipError_t d = hipEventRecord(set->done[i], set->s[i]);
         if (d == hipSuccess) d = hipStreamWaitEvent(s, set->done[i], 0);
-        if (d != hipSuccess) (void)hipStreamSynchronize(set->s[i]);
+        if (d != hipSuccess && !lent) (void)hipStreamSynchronize(set->s[i]);
         if (e == hipSuccess) e = d;
     }
-    side_release(set);
+    if (!lent) side_release(set);
     if (rc == MESS_OK && e != hipSuccess) {
         set_error("class streams: %s", hipGetErrorString(e));
         rc = MESS_E_DEVICE;

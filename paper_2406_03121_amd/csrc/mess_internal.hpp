@@ -232,10 +232,21 @@ bool rows_compiled(int cb, int ck);   // bra-segment kernel built for the class
 // Profiling of class launches (HIP events on the launch stream).
 bool prof_on();
 
+// Side streams lent to this thread's stream captures while the object lives.
+// Taken before a capture begins and given back after it ends, since the
+// streams that a capture forks to stay in it until then.
+struct ForkCapture {
+    ForkCapture();
+    ~ForkCapture();
+    ForkCapture(const ForkCapture &) = delete;
+    ForkCapture &operator=(const ForkCapture &) = delete;
+};
+
 // Launches work(i, stream) for every i < cost.size() on s and side streams
 // (jk.hip), the costliest first; all of it is complete before what s runs
 // next.  One after another on s for few or short launches (all the costs, in
-// operations or bytes, below 1e9), under capture and while profiling.
+// operations or bytes, below 1e9), while profiling, and under a capture that
+// has been lent no streams.
 int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work);
 void prof_record(hipStream_t s, int cls, bool begin, int64_t quartets, int64_t prims, double flops);
 
