@@ -56,8 +56,30 @@ __global__ void __launch_bounds__(64) k_schwarz(const PairInfo *__restrict__ pai
     if (threadIdx.x % 16 == 0) Q[off + i] = sqrt(m);
 }
 
-// Dense N^4 store: every unique quartet writes its block to all eight
-// index permutations (P lanes a quartet, which share the stores).
+// One quartet's block to all eight index permutations of the dense tensor
+// (P lanes hold it and share the stores).
+template <class Dm, typename Real, int P>
+__device__ __forceinline__ void dense_block(const Real (&out)[Dm::NOUT], const PairInfo &bra, const PairInfo &ket, int sub,
+                                            int64_t N, double *__restrict__ eri) {
+    static_for<0, Dm::NOUT>([&](auto I) {
+        constexpr int k = decltype(I)::value;
+        if (P > 1 && k % P != sub) return;
+        constexpr int a = k / (Dm::NB * Dm::NCD), b = (k / Dm::NCD) % Dm::NB;
+        constexpr int c = (k / Dm::ND) % Dm::NC, d = k % Dm::ND;
+        const int64_t ia = bra.bfa + a, ib = bra.bfb + b, ic = ket.bfa + c, id = ket.bfb + d;
+        const double v = (double)out[k];
+        eri[((ia * N + ib) * N + ic) * N + id] = v;
+        eri[((ib * N + ia) * N + ic) * N + id] = v;
+        eri[((ia * N + ib) * N + id) * N + ic] = v;
+        eri[((ib * N + ia) * N + id) * N + ic] = v;
+        eri[((ic * N + id) * N + ia) * N + ib] = v;
+        eri[((id * N + ic) * N + ia) * N + ib] = v;
+        eri[((ic * N + id) * N + ib) * N + ia] = v;
+        eri[((id * N + ic) * N + ib) * N + ia] = v;
+    });
+}
+
+// Dense N^4 store, P lanes a quartet.
 template <class Dm, typename Real, int P = 1>
 __global__ void __launch_bounds__(128) k_eri_dense(const PairInfo *__restrict__ pairs, int bra_off,
                                                    int ket_off, int nbra,
@@ -74,22 +96,7 @@ __global__ void __launch_bounds__(128) k_eri_dense(const PairInfo *__restrict__ 
         const PairInfo ket = pairs[ket_off + j];
         Real out[Dm::NOUT];
         eri_quartet<Dm, Real, P>(bra, ket, pp, bt, out, sub);
-        static_for<0, Dm::NOUT>([&](auto I) {
-            constexpr int k = decltype(I)::value;
-            if (P > 1 && k % P != sub) return;
-            constexpr int a = k / (Dm::NB * Dm::NCD), b = (k / Dm::NCD) % Dm::NB;
-            constexpr int c = (k / Dm::ND) % Dm::NC, d = k % Dm::ND;
-            const int64_t ia = bra.bfa + a, ib = bra.bfb + b, ic = ket.bfa + c, id = ket.bfb + d;
-            const double v = (double)out[k];
-            eri[((ia * N + ib) * N + ic) * N + id] = v;
-            eri[((ib * N + ia) * N + ic) * N + id] = v;
-            eri[((ia * N + ib) * N + id) * N + ic] = v;
-            eri[((ib * N + ia) * N + id) * N + ic] = v;
-            eri[((ic * N + id) * N + ia) * N + ib] = v;
-            eri[((id * N + ic) * N + ia) * N + ib] = v;
-            eri[((ic * N + id) * N + ib) * N + ia] = v;
-            eri[((id * N + ic) * N + ib) * N + ia] = v;
-        });
+        dense_block<Dm, Real, P>(out, bra, ket, sub, N, eri);
     }
 }
 
@@ -180,6 +187,15 @@ __device__ __forceinline__ void digest_jk(const Real (&out)[Dm::NOUT], double fa
     }
 }
 
+// Weight of a unique quartet in the digestion.
+__device__ __forceinline__ double quartet_factor(const PairInfo &bra, const PairInfo &ket, bool same) {
+    double fac = 1.0;
+    if (bra.sa == bra.sb) fac *= 0.5;
+    if (ket.sa == ket.sb) fac *= 0.5;
+    if (same) fac *= 0.5;
+    return fac;
+}
+
 // Direct J/K, one lane (or P, see kSplits) per quartet.
 template <class Dm, typename Real, int P = 1>
 __global__ void __launch_bounds__(128) k_jk_direct(const PairInfo *__restrict__ pairs, int bra_off,
@@ -199,10 +215,7 @@ __global__ void __launch_bounds__(128) k_jk_direct(const PairInfo *__restrict__ 
         Real out[Dm::NOUT];
         eri_quartet<Dm, Real, P>(bra, ket, pp, bt, out, sub);
         if (P > 1 && sub != 0) continue;
-        double fac = 1.0;
-        if (bra.sa == bra.sb) fac *= 0.5;
-        if (ket.sa == ket.sb) fac *= 0.5;
-        if (same_class && i == j) fac *= 0.5;
+        const double fac = quartet_factor(bra, ket, same_class && i == j);
         digest_jk<Dm, Real>(out, fac, bra.bfa, bra.bfb, ket.bfa, ket.bfb, D + bra.moff, bra.mN,
                             Gj ? Gj + bra.moff : nullptr, Gk ? Gk + bra.moff : nullptr);
     }
@@ -223,10 +236,7 @@ __global__ void __launch_bounds__(128) k_jk_stored(const PairInfo *__restrict__ 
         const PairInfo ket = pairs[ket_off + j];
         Real out[Dm::NOUT];
         static_for<0, Dm::NOUT>([&](auto I) { out[I] = base[(int64_t)decltype(I)::value * total + t]; });
-        double fac = 1.0;
-        if (bra.sa == bra.sb) fac *= 0.5;
-        if (ket.sa == ket.sb) fac *= 0.5;
-        if (same_class && i == j) fac *= 0.5;
+        const double fac = quartet_factor(bra, ket, same_class && i == j);
         digest_jk<Dm, Real>(out, fac, bra.bfa, bra.bfb, ket.bfa, ket.bfb, D + bra.moff, bra.mN,
                             Gj ? Gj + bra.moff : nullptr, Gk ? Gk + bra.moff : nullptr);
     }

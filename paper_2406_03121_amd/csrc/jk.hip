@@ -192,6 +192,27 @@ int run_forked(hipStream_t s, const std::vector<double> &cost, const std::functi
     return rc;
 }
 
+// The classes with quartets, and their operation counts.
+static std::vector<const ClassList *> active_classes(const WorkLists *W) {
+    std::vector<const ClassList *> act;
+    for (const ClassList &cl : W->classes)
+        if (cl.total > 0) act.push_back(&cl);
+    return act;
+}
+
+static std::vector<double> class_costs(const std::vector<const ClassList *> &act) {
+    std::vector<double> cost;
+    for (const ClassList *cl : act) {
+        double fp = 0.0, fq = 0.0;
+        class_flops(cl->cb, cl->ck, &fp, &fq);
+        cost.push_back(fp * (double)cl->prim_quartets + fq * (double)cl->total);
+    }
+    return cost;
+}
+
+int short_launch(const mess_basis *B, std::vector<const ClassList *> &act, bool dense, const double *D, double *out0,
+                 double *out1, hipStream_t s);  // short.hip
+
 // Gj, Gk (device, packed block-diagonal, may be NULL) <- half-matrices of J and K.
 int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau,
                    hipStream_t s) {
@@ -199,15 +220,9 @@ int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int p
     MESS_TRY(get_work_lists(B, tau, s, &W));
     MESS_TRY(zero_halves(B, Gj, Gk, s));
     const bool prof = prof_on();
-    std::vector<const ClassList *> act;
-    std::vector<double> cost;
-    for (const ClassList &cl : W->classes) {
-        if (cl.total == 0) continue;
-        double fp = 0.0, fq = 0.0;
-        class_flops(cl.cb, cl.ck, &fp, &fq);
-        act.push_back(&cl);
-        cost.push_back(fp * (double)cl.prim_quartets + fq * (double)cl.total);
-    }
+    std::vector<const ClassList *> act = active_classes(W);
+    if (prec == MESS_FP64) MESS_TRY(short_launch(B, act, false, D, Gj, Gk, s));
+    const std::vector<double> cost = class_costs(act);
     return run_forked(s, cost, [&](int i, hipStream_t st) {
         const ClassList &cl = *act[i];
         ClassLaunch L;
@@ -315,15 +330,9 @@ int mess_eri(const mess_basis *basis, int32_t layout, int32_t prec, double schwa
     WorkLists *W = nullptr;
     MESS_TRY(get_work_lists(B, schwarz_tol, s, &W));
     MESS_TRY(zero_async(static_cast<double *>(out), N * N * N * N, s));
-    std::vector<const ClassList *> act;
-    std::vector<double> cost;
-    for (const ClassList &cl : W->classes) {
-        if (cl.total == 0) continue;
-        double fp = 0.0, fq = 0.0;
-        class_flops(cl.cb, cl.ck, &fp, &fq);
-        act.push_back(&cl);
-        cost.push_back(fp * (double)cl.prim_quartets + fq * (double)cl.total);
-    }
+    std::vector<const ClassList *> act = active_classes(W);
+    if (prec == MESS_FP64) MESS_TRY(short_launch(B, act, true, nullptr, static_cast<double *>(out), nullptr, s));
+    const std::vector<double> cost = class_costs(act);
     return run_forked(s, cost, [&](int i, hipStream_t st) {
         ClassLaunch L;
         fill_class_launch(B, *act[i], st, L);

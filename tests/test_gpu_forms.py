@@ -133,6 +133,40 @@ def test_shared_quartets_match_single_lanes(waters):
     B.close()
 
 
+@pytest.mark.parametrize("atoms,half", [(2, None), (4, None), (6, None), (6, "J"), (6, "K"), (9, None), (15, None)])
+def test_small_molecules_in_one_launch(atoms, half):
+    """s and p molecules whose lists take 64 (2 and 4 atoms) or 16 lanes a
+    quartet (6, 9) run their classes in one launch, longer ones (15) in one each:
+    J, K (or one of them) and the dense tensor against the same builds with a
+    form asked for, which keeps the separate launches.  Sums of the same terms
+    in another order: 1e-12 * max(1, |x|)."""
+    mess = need_gpu()
+    mol = G.random_small_molecule(3, n_atoms=atoms, box=6.0 * (atoms / 6) ** (1 / 3) + 1.0)
+    announce(f"one launch, {atoms} atoms, {mol.n_bf} functions, {half}")
+    B = mess.basis_from_molecule(mol)
+    N = mol.n_bf
+    D = dev(random_density(N, seed=9))
+
+    def builds():
+        J, K = (None if half == "K" else zeros(N, N)), (None if half == "J" else zeros(N, N))
+        mess.mess_jk(B, D, J, K, schwarz_tol=0.0)
+        out = [x for x in (J, K) if x is not None]
+        if half is None and N <= 50:
+            out.append(zeros(N, N, N, N))
+            mess.mess_eri(B, out[-1], schwarz_tol=0.0)
+        return [host(x) for x in out]
+
+    got = builds()
+    try:
+        assert mess.lib().mess_kernel_form(mess.MESS_FP64, 0, mess.MESS_FORM_LANE, None) == mess.MESS_OK
+        ref = builds()
+    finally:
+        mess.mess_kernel_form(0, mess.MESS_FORM_AUTO)
+    for a, b in zip(got, ref):
+        assert np.all(np.abs(a - b) <= 1e-12 * np.maximum(1.0, np.abs(b)).max())
+    B.close()
+
+
 @pytest.mark.parametrize("mode", ["direct", "stored"])
 def test_class_streams_order_and_capture(mode):
     """The classes of a build run on several streams between a fork and a
