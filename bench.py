@@ -10,8 +10,9 @@ orthogonaliser, core-Hamiltonian guess, then Fock builds with direct J/K
 
 Prints one JSON line (stdout).  value = shell quartets evaluated per second
 over the timed steps (all Fock builds); the roofline block is for the
-dominant ERI class kernel, from HIP events recorded on the launch stream
-around every class launch inside the timed region.
+dominant ERI class kernel, from HIP events recorded around every class launch
+of as many further SCFs after the timed ones (with the events on, the classes
+run one after another instead of on several streams).
 """
 from __future__ import annotations
 
@@ -45,6 +46,22 @@ def make_workload(name, seed):
     if name == "hco6_sp":
         return G.random_small_molecule(seed)
     raise SystemExit(f"unknown workload {name}")
+
+
+def timed_then_profiled(mess, torch, steps, run):
+    """Results and seconds of steps timed runs, and seconds of as many again
+    with the class events on (to be read, then switched off, by the caller)."""
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    results = [run() for _ in range(steps)]
+    torch.cuda.synchronize()
+    t1 = time.perf_counter()
+    mess.mess_prof_enable(True)
+    t2 = time.perf_counter()
+    for _ in range(steps):
+        run()
+    torch.cuda.synchronize()
+    return results, t1 - t0, time.perf_counter() - t2
 
 
 def scf_once(mess, mol, tau, conv_tol, max_iter=100, verbose=True, prec=0, jk_mode=0):
@@ -508,16 +525,9 @@ def main():
         e, it, conv = scf_once(mess, mol, a.tau, a.conv)
         log(f"warmup {w}: E={e:.10f} iterations={it} converged={conv}")
 
-    torch.cuda.synchronize()
-    mess.mess_prof_enable(True)
-    t0 = time.perf_counter()
-    results = []
-    for k in range(a.steps):
-        results.append(scf_once(mess, mol, a.tau, a.conv))
-        log(f"step {k}: E={results[-1][0]:.10f} iterations={results[-1][1]}")
-    torch.cuda.synchronize()
-    t1 = time.perf_counter()
-    elapsed = t1 - t0
+    results, elapsed, profiled = timed_then_profiled(mess, torch, a.steps, lambda: scf_once(mess, mol, a.tau, a.conv, verbose=False))
+    for k, r in enumerate(results):
+        log(f"step {k}: E={r[0]:.10f} iterations={r[1]}")
     tot = mess.mess_prof_read(-1)
     per = {}
     for c in range(21):
@@ -554,7 +564,7 @@ def main():
         "jk_gbps": None,
         "primitive_quartets_per_s": tot["prim_quartets"] / elapsed,
         "eri_kernels": {"ms": tot["ms"], "alg_tflops": eri_tf, "frac_of_fp64_peak": eri_tf / FP64_VALU_PEAK_TFLOPS,
-                        "share_of_step": tot["ms"] * 1e-3 / elapsed},
+                        "share_of_step": tot["ms"] * 1e-3 / profiled},
         "per_class": {CLASS_NAMES[c]: {"ms": round(per[c]["ms"], 3), "quartets": per[c]["quartets"],
                                        "prim_quartets": per[c]["prim_quartets"],
                                        "tflops": round(per[c]["alg_flops"] / (per[c]["ms"] * 1e-3) / 1e12, 3)}
@@ -572,15 +582,11 @@ def main():
         ref = json.load(open(golden))["energy"]
         line["delta_e_vs_oracle_hartree"] = energies[-1] - ref
     if not a.no_fp32:
-        # same molecule, mixed precision, timed like the FP64 run (class
-        # events on), per-class kernel times in both arithmetics
+        # same molecule, mixed precision, timed like the FP64 run, per-class
+        # kernel times in both arithmetics
         scf_once(mess, mol, a.tau, a.conv, verbose=False, prec=mess.MESS_FP32)
-        torch.cuda.synchronize()
-        mess.mess_prof_enable(True)
-        t2 = time.perf_counter()
-        r32 = [scf_once(mess, mol, a.tau, a.conv, verbose=False, prec=mess.MESS_FP32) for _ in range(a.steps)]
-        torch.cuda.synchronize()
-        t3 = time.perf_counter()
+        r32, e32, _ = timed_then_profiled(
+            mess, torch, a.steps, lambda: scf_once(mess, mol, a.tau, a.conv, verbose=False, prec=mess.MESS_FP32))
         pc32 = {}
         for c in range(21):
             r64, r32c = mess.mess_prof_read(c), mess.mess_prof_read(64 + c)
@@ -589,7 +595,7 @@ def main():
                 "fp64_ms_per_launch": round(per[c]["ms"] / per[c]["launches"], 4) if c in per else None,
                 "fp32_launches": r32c["launches"], "fp64_launches": r64["launches"]}
         mess.mess_prof_enable(False)
-        fp32 = {"ms_per_step": (t3 - t2) / a.steps * 1e3, "molecules_per_s": a.steps / (t3 - t2),
+        fp32 = {"ms_per_step": e32 / a.steps * 1e3, "molecules_per_s": a.steps / e32,
                 "scf_iterations": r32[-1][1], "energy_hartree": r32[-1][0],
                 "delta_e_vs_fp64_hartree": r32[-1][0] - energies[-1], "per_class": pc32}
         fp32["speedup_vs_fp64"] = fp32["molecules_per_s"] / line["molecules_per_s"]
@@ -602,13 +608,8 @@ def main():
         # same molecule, stored J/K: blocks computed once per SCF (first
         # Fock build), streamed from HBM by the later builds
         scf_once(mess, mol, a.tau, a.conv, verbose=False, jk_mode=mess.MESS_JK_STORED)
-        torch.cuda.synchronize()
-        mess.mess_prof_enable(True)
-        t4 = time.perf_counter()
-        rst = [scf_once(mess, mol, a.tau, a.conv, verbose=False, jk_mode=mess.MESS_JK_STORED)
-               for _ in range(a.steps)]
-        torch.cuda.synchronize()
-        t5 = time.perf_counter()
+        rst, est, _ = timed_then_profiled(
+            mess, torch, a.steps, lambda: scf_once(mess, mol, a.tau, a.conv, verbose=False, jk_mode=mess.MESS_JK_STORED))
         sb, sms = 0.0, 0.0
         spc = {}
         nb = max(1, a.steps * (rst[-1][1] - 1))
@@ -620,13 +621,13 @@ def main():
                 spc[CLASS_NAMES[c]] = {"ms_per_build": round(r["ms"] / nb, 3),
                                        "gbps": round(r["alg_flops"] / (r["ms"] * 1e-3) / 1e9, 1)}
         mess.mess_prof_enable(False)
-        stored = {"ms_per_step": (t5 - t4) / a.steps * 1e3, "molecules_per_s": a.steps / (t5 - t4),
+        stored = {"ms_per_step": est / a.steps * 1e3, "molecules_per_s": a.steps / est,
                   "scf_iterations": rst[-1][1], "energy_hartree": rst[-1][0],
                   "delta_e_vs_direct_hartree": rst[-1][0] - energies[-1],
                   "jk_stream_bytes_per_build": sb / max(1, a.steps * (rst[-1][1] - 1)),
                   "jk_stream_ms_per_build": sms / max(1, a.steps * (rst[-1][1] - 1)),
                   "jk_gbps": sb / (sms * 1e-3) / 1e9 if sms > 0 else None,
-                  "speedup_vs_direct": (a.steps / (t5 - t4)) / line["molecules_per_s"],
+                  "speedup_vs_direct": (a.steps / est) / line["molecules_per_s"],
                   "per_class_stream": spc}
         line["stored_jk"] = stored
         line["jk_gbps"] = stored["jk_gbps"]
