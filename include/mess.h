@@ -178,7 +178,8 @@ int mess_jk_dense(const void *eri, int32_t n, int32_t ndens, const void *D, void
 /* Boys function F_j(T) = int_0^1 u^(2j) exp(-T u^2) du, j = 0..m (section 3:
  * every closed-form repulsion integral is a sum over it), by the device
  * routines of the integral kernels, using the basis handle's tables:
- *   form 0  F_0..F_m together (Taylor sum of F_m about T_k = k/16, downward
+ *   form 0  F_0..F_m together (F_m by a polynomial on quarter-wide
+ *           intervals, in FP32 by its Taylor sum about T_k = k/16, downward
  *           recurrence; (2j-1)!!/(2T)^j sqrt(pi/T)/2 for T >= 60), the
  *           recursion kernels' form;
  *   form 1  each F_j by its own Taylor sum, the table-driven kernel's form.

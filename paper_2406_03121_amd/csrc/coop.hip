@@ -491,6 +491,15 @@ static const CoopProgram *coop_program(int cb, int ck) {
     return raw;
 }
 
+// Builds the class's tables if its kernels of this precision read them and
+// they are not there.
+int coop_prepare(int cb, int ck, int prec) {
+    if (!coop_class(cb, ck) && !(plane_compiled(cb, ck) && class_form(cb, ck, prec) == kFormPlane)) return MESS_OK;
+    if (coop_program(cb, ck)) return MESS_OK;
+    set_error("internal: cooperative program for class (%d,%d) could not be built", cb, ck);
+    return MESS_E_DEVICE;
+}
+
 // ------------------------------------------------------------ device
 
 // Per-primitive-quartet coefficients of the vertical recursion, in registers.

@@ -213,6 +213,19 @@ static std::vector<double> class_costs(const std::vector<const ClassList *> &act
 int short_launch(const mess_basis *B, std::vector<const ClassList *> &act, bool dense, const double *D, double *out0,
                  double *out1, hipStream_t s);  // short.hip
 
+int coop_prepare(int cb, int ck, int prec);                              // coop.hip
+int stored_prepare(mess_basis *B, int prec, double tau, hipStream_t s);  // stored.hip
+
+// Everything that a build of this mode, precision and tolerance allocates, so
+// that later ones allocate nothing and can be captured: the work lists, step
+// tables and stored blocks.
+int jk_prepare(mess_basis *B, int mode, int prec, double tau, hipStream_t s) {
+    WorkLists *W = nullptr;
+    MESS_TRY(get_work_lists(B, tau, s, &W));
+    for (const ClassList *cl : active_classes(W)) MESS_TRY(coop_prepare(cl->cb, cl->ck, prec));
+    return mode == MESS_JK_DIRECT ? (int)MESS_OK : stored_prepare(B, prec, tau, s);
+}
+
 // Gj, Gk (device, packed block-diagonal, may be NULL) <- half-matrices of J and K.
 int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau,
                    hipStream_t s) {

@@ -104,6 +104,13 @@ static int get_stored(mess_basis *B, int prec, double tau, hipStream_t s, WorkLi
     return MESS_OK;
 }
 
+// The stored blocks of (prec, tau) that jk_stored streams.
+int stored_prepare(mess_basis *B, int prec, double tau, hipStream_t s) {
+    WorkLists *W = nullptr;
+    StoredEri *E = nullptr;
+    return get_stored(B, prec, tau, s, &W, &E);
+}
+
 int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s);
 
 int jk_stored(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau, hipStream_t s) {

@@ -213,3 +213,43 @@ def test_class_streams_order_and_capture(mode):
                 assert np.abs(host(a) - b).max() <= t
     for B in Bs:
         B.close()
+
+
+def test_wide_exchange_rows():
+    """480 functions: the exchange rows of a dd bra take 46 KB of LDS beside
+    the Boys rows of the segment kernels, together beyond 64 KB.  Eager and
+    captured builds against the d-bra classes forced to one lane per quartet:
+    sums of the same terms in another order, 1e-12 * max(1, |x|)."""
+    import torch
+    mess = need_gpu()
+    mol = G.water_cluster(5, n_waters=32, box=26.0)
+    assert mol.n_bf == 480
+    announce("wide exchange rows, 480 functions")
+    B = mess.basis_from_molecule(mol)
+    N = mol.n_bf
+    D = dev(random_density(N, seed=11))
+    J, K, Jc, Kc = (zeros(N, N) for _ in range(4))
+    tau = 1e-7
+    g = torch.cuda.CUDAGraph()
+    mess.mess_jk(B, D, J, K, schwarz_tol=tau)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        mess.mess_jk(B, D, Jc, Kc, schwarz_tol=tau)
+    forced = [mess.class_index(5, 0), mess.class_index(3, 0)]
+    Jr, Kr = zeros(N, N), zeros(N, N)
+    try:
+        for c in forced:
+            assert mess.lib().mess_kernel_form(mess.MESS_FP64, c, mess.MESS_FORM_LANE, None) == mess.MESS_OK
+        mess.mess_jk(B, D, Jr, Kr, schwarz_tol=tau)
+    finally:
+        for c in forced:
+            mess.mess_kernel_form(c, mess.MESS_FORM_AUTO)
+    for _ in range(2):
+        Jc.zero_()
+        Kc.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for a, b in ((J, Jr), (K, Kr), (Jc, Jr), (Kc, Kr)):
+            a, b = host(a), host(b)
+            assert np.abs(a - b).max() <= 1e-12 * max(1.0, np.abs(b).max())
+    B.close()
