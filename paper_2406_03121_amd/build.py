@@ -31,7 +31,7 @@ CLASSES = [(cb, ck) for cb in range(6) for ck in range(cb + 1)]
 # classes evaluated by the wave-cooperative kernel (coop.hip) instead
 COOP_CLASSES = {(2, 2), (4, 2), (4, 4), (5, 2), (5, 3), (5, 4), (5, 5)}
 UNROLLED_CLASSES = [c for c in CLASSES if c not in COOP_CLASSES]
-# primitive-lane kernels (plane.hip), one object per class and precision
+# primitive-lane kernels (plane.hip), one object per class, precision and waves a block
 PLANE_CLASSES = [(5, 4), (5, 3), (5, 2), (5, 1), (4, 4), (4, 2), (2, 2)]
 # recursion passes over ket subtrees (fewer live values for the largest;
 # measured per build on the 60-atom cluster, one pass -> three (x | y | z)
@@ -81,10 +81,11 @@ def _units():
                                   [f"-DMESS_WCB={cb}", f"-DMESS_WCK={ck}", f"-DMESS_WREAL={real}"]))
         elif name == "plane":
             for cb, ck in PLANE_CLASSES:
-                for real in ("double", "float"):
+                # FP64: one wave a block, and four for short lists
+                for real, nw in (("double", 1), ("double", 4), ("float", 1)):
                     waves = {**PLANE_WAVES, **PLANE_WAVES_F32} if real == "float" else PLANE_WAVES
-                    units.append((src, os.path.join(OBJ, f"plane_{cb}{ck}_{real}.o"),
-                                  [f"-DMESS_PCB={cb}", f"-DMESS_PCK={ck}", f"-DMESS_PREAL={real}",
+                    units.append((src, os.path.join(OBJ, f"plane_{cb}{ck}_{real}_{nw}.o"),
+                                  [f"-DMESS_PCB={cb}", f"-DMESS_PCK={ck}", f"-DMESS_PREAL={real}", f"-DMESS_PLANE_NW={nw}",
                                    f"-DMESS_PLANE_PASSES={PLANE_PASSES.get((cb, ck), 1)}"] +
                                   ([f"-DMESS_PLANE_WAVES={waves[(cb, ck)]}"] if (cb, ck) in waves else []) +
                                   (["-DMESS_PLANE_SHARE=0"] if real == "float" and (cb, ck) in PLANE_NO_SHARE_F32

@@ -645,8 +645,9 @@ static void launch_plane(int mode, int cb, int ck, int prec, const CoopArgs &A, 
                          unsigned g, int nw, size_t lds, const double *D, double *out0, double *out1) {
 #define MESS_PL(B, K)                                                                                  \
     if (cb == B && ck == K) {                                                                          \
-        if (prec == MESS_FP32) PlaneOps<B, K, float>::launch(mode, A, L, total, g, nw, lds, D, out0, out1);  \
-        else PlaneOps<B, K, double>::launch(mode, A, L, total, g, nw, lds, D, out0, out1);                   \
+        if (prec == MESS_FP32) PlaneOps<B, K, float, 1>::launch(mode, A, L, total, g, lds, D, out0, out1);   \
+        else if (nw == 4) PlaneOps<B, K, double, 4>::launch(mode, A, L, total, g, lds, D, out0, out1);       \
+        else PlaneOps<B, K, double, 1>::launch(mode, A, L, total, g, lds, D, out0, out1);                    \
     }
     MESS_PL(5, 4)
     MESS_PL(5, 3)

@@ -248,11 +248,11 @@ struct WaveOps {
                        const double *D, double *out0, double *out1, size_t *lds_out);
 };
 
-// Primitive-lane launch of one class in one precision (plane.hip, compiled
-// once per class and precision) with nw waves a block.
-template <int CB, int CK, typename Real>
+// Primitive-lane launch of one class in one precision with NW waves a block
+// (plane.hip, compiled once per class, precision and NW).
+template <int CB, int CK, typename Real, int NW>
 struct PlaneOps {
-    static void launch(int mode, const CoopArgs &A, const ClassLaunch &L, int64_t total, unsigned g, int nw, size_t lds,
+    static void launch(int mode, const CoopArgs &A, const ClassLaunch &L, int64_t total, unsigned g, size_t lds,
                        const double *D, double *out0, double *out1);
 };
 

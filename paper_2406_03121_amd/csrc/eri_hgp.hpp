@@ -114,7 +114,28 @@ struct BoysTabs {
 // degree 9, constants from the same interpolation.  Largest relative errors
 // over 30000 arguments as those of the Taylor sums (2.1e-16 for F_L, 7.8e-16
 // for F_0 after eight steps down).
-template <int L, bool BARE = false>
+//
+// MEM: the ten constants of exp(-u/4) are read on each evaluation, into
+// scalar registers, by a pointer that the compiler cannot see through.  As
+// literals it keeps them in vector registers around the primitive loop, which
+// the primitive-lane kernels in passes, whose recursion fills the registers,
+// pay for in spills (scratch a lane, literals -> MEM: (dd|ds) 204 -> 124 B,
+// (dp|dp) 296 -> 188, (dd|pp) 280 -> 164; per build of 20 waters (dd|ds) 3.75
+// -> 3.63 ms, (dd|pp) 0.67 -> 0.63, (dp|dp) 1.04 -> 0.96).  The others keep
+// the literals: the reads' latency costs the segment and lane kernels 5-10 %
+// ((ps|ss) 1.47 -> 1.64 ms, (pp|ss) 0.68 -> 1.24).
+static __constant__ const double kBoysExp[10] = {1.0,
+                                                 -0.25,
+                                                 0.031249999999999833,
+                                                 -0.002604166666666561,
+                                                 0.00016276041667097202,
+                                                 -8.138020836034875e-06,
+                                                 3.3908415923988856e-07,
+                                                 -1.2110132008302799e-08,
+                                                 3.7861784818460363e-10,
+                                                 -1.0550138540565967e-11};
+
+template <int L, bool BARE = false, bool MEM = false>
 __device__ __forceinline__ void boys_poly(double T, const double *__restrict__ rows, double (&F)[L + 1]) {
     if (T < kBoysTmax) {
         // nearest row; BARE without conversions: 1.5 2^52 puts the integer
@@ -127,16 +148,10 @@ __device__ __forceinline__ void boys_poly(double T, const double *__restrict__ r
         static_for<0, 8>([&](auto I) { f = fma(u, f, row[7 - decltype(I)::value]); });
         F[L] = f;
         if constexpr (L > 0) {
-            double e = -1.0550138540565967e-11;
-            e = fma(u, e, 3.7861784818460363e-10);
-            e = fma(u, e, -1.2110132008302799e-08);
-            e = fma(u, e, 3.3908415923988856e-07);
-            e = fma(u, e, -8.138020836034875e-06);
-            e = fma(u, e, 0.00016276041667097202);
-            e = fma(u, e, -0.002604166666666561);
-            e = fma(u, e, 0.031249999999999833);
-            e = fma(u, e, -0.25);
-            e = fma(u, e, 1.0);
+            const double *c = kBoysExp;
+            if constexpr (MEM) asm volatile("" : "+s"(c));
+            double e = c[9];
+            static_for<0, 9>([&](auto I) { e = fma(u, e, c[8 - decltype(I)::value]); });
             e *= row[9];
             const double t2 = 2.0 * T;
             static_for<0, L>([&](auto I) {
@@ -154,9 +169,9 @@ __device__ __forceinline__ void boys_poly(double T, const double *__restrict__ r
     }
 }
 
-template <int L>
+template <int L, bool MEM = false>
 __device__ __forceinline__ void boys_f64t(double T, const double *__restrict__ tabt, double (&F)[L + 1]) {
-    boys_poly<L>(T, tabt + (size_t)L * (kBoysPRows * kBoysPW), F);
+    boys_poly<L, false, MEM>(T, tabt + (size_t)L * (kBoysPRows * kBoysPW), F);
 }
 
 template <int L>
@@ -196,6 +211,19 @@ template <int L, typename Real>
 __device__ __forceinline__ void boys_eval(Real T, const BoysTabs &bt, Real (&F)[L + 1]) {
     if constexpr (sizeof(Real) == 8)
         boys_f64t<L>(T, bt.tabt, F);
+    else
+        boys_f32<L>(T, bt, F);
+}
+
+// The tables for kernels that read the constants of exp(-u/4) (MEM).
+struct BoysMem : BoysTabs {
+    __device__ __forceinline__ explicit BoysMem(const BoysTabs &t) : BoysTabs(t) {}
+};
+
+template <int L, typename Real>
+__device__ __forceinline__ void boys_eval(Real T, const BoysMem &bt, Real (&F)[L + 1]) {
+    if constexpr (sizeof(Real) == 8)
+        boys_f64t<L, true>(T, bt.tabt, F);
     else
         boys_f32<L>(T, bt, F);
 }

@@ -1,10 +1,11 @@
 // Primitive-lane kernel of one high angular class in one precision.  This
-// file is compiled once per (class, precision) with -DMESS_PCB=<bra pair
-// class> -DMESS_PCK=<ket pair class> -DMESS_PREAL=<double|float>.
+// file is compiled once per (class, precision, waves a block) with
+// -DMESS_PCB=<bra pair class> -DMESS_PCK=<ket pair class>
+// -DMESS_PREAL=<double|float> -DMESS_PLANE_NW=<1|4>.
 #include "coop.hpp"
 
 #ifndef MESS_PCB
-#error "compile with -DMESS_PCB, -DMESS_PCK, -DMESS_PREAL"
+#error "compile with -DMESS_PCB, -DMESS_PCK, -DMESS_PREAL, -DMESS_PLANE_NW"
 #endif
 
 namespace mess {
@@ -82,8 +83,13 @@ inline constexpr int kPlanePasses = MESS_PLANE_PASSES;
 #define MESS_PLANE_OCC
 #endif
 
-template <class Dm, int MODE, typename Real>
-__global__ void __launch_bounds__(sizeof(Real) == 8 ? 256 : 64) MESS_PLANE_OCC k_plane(CoopArgs A, const PairInfo *__restrict__ pairs, int bra_off,
+// NW: waves a block, one or (FP64) four, which take the rounds of 64 primitive
+// quartets in turn; FP32 sums keep the order of one wave.  A kernel of its own
+// each: with the count at run time, the long lists' one-wave blocks spilled
+// 232 B a lane for 204 in (dd|ds), and took 3.87 ms a build of 20 waters for
+// 3.75.
+template <class Dm, int MODE, typename Real, int NW>
+__global__ void __launch_bounds__(64 * NW) MESS_PLANE_OCC k_plane(CoopArgs A, const PairInfo *__restrict__ pairs, int bra_off,
                                               int ket_off, int nbra, int same_class,
                                               const int64_t *__restrict__ rowstart, const int2 *__restrict__ rowmap, int64_t total,
                                               const PrimPairT<Real> *__restrict__ pp, BoysTabs bt,
@@ -102,10 +108,8 @@ __global__ void __launch_bounds__(sizeof(Real) == 8 ? 256 : 64) MESS_PLANE_OCC k
     extern __shared__ double lds[];
     double *H = lds;
     double *hc = lds + A.nH;
-    // FP64: one wave or four a block (blockDim), which take the rounds of 64
-    // primitive quartets in turn; FP32 sums keep the order of one wave
-    constexpr bool MW = sizeof(Real) == 8;
-    const int lane = threadIdx.x & 63, wave = MW ? threadIdx.x >> 6 : 0, nt = MW ? (int)blockDim.x : 64;
+    constexpr int nt = 64 * NW;
+    const int lane = NW > 1 ? threadIdx.x & 63 : threadIdx.x, wave = NW > 1 ? threadIdx.x >> 6 : 0;
     // base values [00|00]^(m) of this lane's primitive quartet, element m at
     // bfl[64 m], shared by the recursion passes (one Boys evaluation)
     double *bw = lds + A.nH + kNHCoef;
@@ -167,11 +171,13 @@ __global__ void __launch_bounds__(sizeof(Real) == 8 ? 256 : 64) MESS_PLANE_OCC k
             // order, so the reduction blocks are unchanged)
             constexpr bool PRE = MESS_PLANE_SHARE && kPlanePasses<Dm> > 1;
             if constexpr (PRE) {
+                // (four waves: literals, with which (dp|dp) spills 320 B, 440 so)
+                const std::conditional_t<NW == 1, BoysMem, BoysTabs> bq(bt);
                 Real V0[Dr::L + 1];
                 if constexpr (SW)
-                    prim_base<Dr::L, Real>(Q, P, AC, bt, V0);
+                    prim_base<Dr::L, Real>(Q, P, AC, bq, V0);
                 else
-                    prim_base<Dr::L, Real>(P, Q, AC, bt, V0);
+                    prim_base<Dr::L, Real>(P, Q, AC, bq, V0);
                 static_for<0, Dr::L + 1>([&](auto M) { bfl[64 * decltype(M)::value] = V0[decltype(M)::value]; });
             }
             auto run = [&](auto SUBC) {
@@ -206,7 +212,7 @@ __global__ void __launch_bounds__(sizeof(Real) == 8 ? 256 : 64) MESS_PLANE_OCC k
             // swapped: x = (e - E0) NFA + (f - F0) holds [e0|f0]
             return SW ? (x % Dm::NFA) * Dm::NEA + x / Dm::NFA : x;
         };
-        if (MW && nt > 64) {
+        if constexpr (NW > 1) {
             // the waves' sums, added in wave order
             __builtin_amdgcn_wave_barrier();
             static_for<0, NPER>([&](auto I) {
@@ -216,7 +222,7 @@ __global__ void __launch_bounds__(sizeof(Real) == 8 ? 256 : 64) MESS_PLANE_OCC k
             __syncthreads();
             for (int ps = threadIdx.x; ps < NACC; ps += nt) {
                 double s = bw[ps];
-                for (int w = 1; w < nt / 64; ++w) s += bw[w * 64 * (Dm::L + 1) + ps];
+                for (int w = 1; w < NW; ++w) s += bw[w * 64 * (Dm::L + 1) + ps];
                 H[slot(ps)] = s;
             }
         } else {
@@ -233,35 +239,26 @@ __global__ void __launch_bounds__(sizeof(Real) == 8 ? 256 : 64) MESS_PLANE_OCC k
 
 
 template <>
-void PlaneOps<MESS_PCB, MESS_PCK, MESS_PREAL>::launch(int mode, const CoopArgs &A, const ClassLaunch &L,
-                                                      int64_t total, unsigned g, int nw, size_t lds, const double *D,
-                                                      double *out0, double *out1) {
+void PlaneOps<MESS_PCB, MESS_PCK, MESS_PREAL, MESS_PLANE_NW>::launch(int mode, const CoopArgs &A, const ClassLaunch &L,
+                                                                     int64_t total, unsigned g, size_t lds,
+                                                                     const double *D, double *out0, double *out1) {
+    constexpr int NW = MESS_PLANE_NW;
     using Dm = ClassOf<MESS_PCB, MESS_PCK>;
     using R = MESS_PREAL;
     const BoysTabs bt{L.tab, L.etab, L.tabf, L.etabf, L.tabt};
     const PrimPairT<R> *pp;
     pp = reinterpret_cast<const PrimPairT<R> *>(sizeof(R) == 8 ? (const void *)L.pp : (const void *)L.ppf);
+#define MESS_PLANE_GO(MODE)                                                                                        \
+    hipLaunchKernelGGL((k_plane<Dm, MODE, R, NW>), dim3(g), dim3(64 * NW), lds, L.stream, A, L.pairs, L.bra_off,   \
+                       L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1)
     switch (mode) {
-        case kModeSchwarz:
-            hipLaunchKernelGGL((k_plane<Dm, kModeSchwarz, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
-                               L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
-            break;
-        case kModeDense:
-            hipLaunchKernelGGL((k_plane<Dm, kModeDense, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
-                               L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
-            break;
-        case kModeStore64:
-            hipLaunchKernelGGL((k_plane<Dm, kModeStore64, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
-                               L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
-            break;
-        case kModeStore32:
-            hipLaunchKernelGGL((k_plane<Dm, kModeStore32, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
-                               L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
-            break;
-        default:
-            hipLaunchKernelGGL((k_plane<Dm, kModeJK, R>), dim3(g), dim3(64 * nw), lds, L.stream, A, L.pairs, L.bra_off,
-                               L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, total, pp, bt, D, L.N, out0, out1);
+        case kModeSchwarz: MESS_PLANE_GO(kModeSchwarz); break;
+        case kModeDense: MESS_PLANE_GO(kModeDense); break;
+        case kModeStore64: MESS_PLANE_GO(kModeStore64); break;
+        case kModeStore32: MESS_PLANE_GO(kModeStore32); break;
+        default: MESS_PLANE_GO(kModeJK);
     }
+#undef MESS_PLANE_GO
 }
 
 }  // namespace mess
