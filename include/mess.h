@@ -545,13 +545,18 @@ int mess_prof_read(int32_t cls, int64_t *launches, double *ms, double *alg_flops
  * class, MESS_E_ARG for an unknown precision or class.
  *
  * mess_autotune: for every class with quartets in the basis's work list at
- * schwarz_tol, time each available form in precision prec on a direct J/K
- * pass with density D
+ * schwarz_tol, time the built-in choice and each available form in precision
+ * prec on a direct J/K pass with density D
  * (device N x N, or packed for a batch) as the best of reps runs after one
- * warm-up (HIP events on the stream), and keep the fastest.  forms[21]
- * (host, may be NULL) receives the chosen forms; ms[21 * 7] (host, may be
+ * warm-up (HIP events on the stream), and keep the fastest.  The built-in
+ * choice (MESS_FORM_AUTO) takes several lanes per quartet on short FP64 lists
+ * and the lists of small s and p molecules in one launch; a class that it
+ * serves fastest stays at MESS_FORM_AUTO.  forms[21]
+ * (host, may be NULL) receives the chosen forms (the built-in form where the
+ * class stays at AUTO); ms[21 * 7] (host, may be
  * NULL) the best time of form f for class c at ms[c * 7 + f] (-1 where not
- * run).  Synchronises the stream; uses the basis's own J/K work buffer. */
+ * run), the built-in choice at ms[c * 7].  Synchronises the stream; uses the
+ * basis's own J/K work buffer. */
 enum { MESS_FORM_AUTO = 0, MESS_FORM_LANE = 1, MESS_FORM_ROWS = 2, MESS_FORM_PLANE = 3, MESS_FORM_COOP = 4,
        MESS_FORM_WAVE = 5, MESS_FORM_FP64 = 6 };
 int mess_kernel_form(int32_t prec, int32_t cls, int32_t form, int32_t *active);

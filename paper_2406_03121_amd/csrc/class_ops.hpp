@@ -41,6 +41,34 @@ int coop_jk(int cb, int ck, const ClassLaunch &L, const double *D, double *Gj, d
 bool stored_aos_class(int cb, int ck);
 int to_aos(const void *soa, void *aos, int nout, int64_t total, int prec, hipStream_t s);
 
+// Lanes that share a shell quartet in the kernels with one lane per quartet
+// (FP64).  A lane's loop over the quartet's primitive quartets (up to 1296
+// of 6 x 6 x 6 x 6 primitives) is a serial chain, so a list that leaves the
+// chip's SIMDs with less than about two waves each is as slow as its longest
+// quartet: then P lanes take every P-th primitive quartet and sum the
+// contracted intermediates (log2 P exchanges each, a few hundred cycles
+// against the chain).  The sum's order depends on the list's size alone.
+// FP32 keeps one lane: its sums round where they are taken.
+constexpr int kSplits[3] = {64, 16, 4};
+
+// Lanes per quartet (1 or one of kSplits) for a list of total quartets with
+// prims primitive quartets in all: as many as 2^20 lanes allow (16 waves a
+// SIMD: enough of them that the longest does not end alone), 2^21 for the
+// classes without the segment form, with at least half a primitive quartet a
+// lane.  Measured on water clusters (n waters; us, one lane -> P): (ss|ss) of
+// n = 3 340 -> 52 (16 lanes), (dp|ds) 3214 -> 75 (64), n = 7 3051 -> 217 (16
+// lanes; 280 with 64), n = 20 3739 -> 1985 (4 lanes, 0.9e6 lanes; 2511 with
+// 16), (pp|ps) of n = 20 1051 -> 543 (4 lanes), but (dd|ss) of n = 20, which
+// would take 1.4e6 lanes, 1429 by segments and 2723 with 4 lanes: there the
+// global atomics that the segments save outweigh the chain.
+inline int split_lanes(int cb, int ck, int64_t total, int64_t prims) {
+    const bool segments = !(cb == 4 && ck == 3) && !(cb == 3 && ck == 2);
+    const int64_t lanes = segments ? int64_t(1) << 20 : int64_t(1) << 21;
+    for (int P : kSplits)
+        if (total * P <= lanes && prims >= total * P / 2) return P;
+    return 1;
+}
+
 template <int CB, int CK>
 struct ClassOps {
     // Q[off + i] for the n pairs of class CB (requires CB == CK).

@@ -20,24 +20,6 @@ inline unsigned grid_for(int64_t total, int block) {
     return static_cast<unsigned>(g);
 }
 
-// Lanes per quartet (1 or one of kSplits) for a list of total quartets with
-// prims primitive quartets in all: as many as 2^20 lanes allow (16 waves a
-// SIMD: enough of them that the longest does not end alone), 2^21 for the
-// classes without the segment form, with at least half a primitive quartet a
-// lane.  Measured on water clusters (n waters; us, one lane -> P): (ss|ss) of
-// n = 3 340 -> 52 (16 lanes), (dp|ds) 3214 -> 75 (64), n = 7 3051 -> 217 (16
-// lanes; 280 with 64), n = 20 3739 -> 1985 (4 lanes, 0.9e6 lanes; 2511 with
-// 16), (pp|ps) of n = 20 1051 -> 543 (4 lanes), but (dd|ss) of n = 20, which
-// would take 1.4e6 lanes, 1429 by segments and 2723 with 4 lanes: there the
-// global atomics that the segments save outweigh the chain.
-int split_lanes(int64_t total, int64_t prims) {
-    constexpr bool segments = !(MESS_CB == 4 && MESS_CK == 3) && !(MESS_CB == 3 && MESS_CK == 2);
-    constexpr int64_t lanes = segments ? int64_t(1) << 20 : int64_t(1) << 21;
-    for (int P : kSplits)
-        if (total * P <= lanes && prims >= total * P / 2) return P;
-    return 1;
-}
-
 // Calls f(integral_constant<P>) for P = 64, 16, 4 or 1.
 template <typename F>
 void with_split(int P, F &&f) {
@@ -73,7 +55,7 @@ int ClassOps<MESS_CB, MESS_CK>::dense(const ClassLaunch &L, double *eri, int pre
         hipLaunchKernelGGL((k_eri_dense<Dm, float>), dim3(grid_for(L.total, 128)), dim3(128), 0, L.stream,
                            L.pairs, L.bra_off, L.ket_off, L.nbra, L.rowstart, L.rowmap, L.ppf, bt, (int64_t)L.N, eri);
     else
-        with_split(split_lanes(L.total, L.prims), [&](auto Pc) {
+        with_split(split_lanes(MESS_CB, MESS_CK, L.total, L.prims), [&](auto Pc) {
             constexpr int P = decltype(Pc)::value;
             hipLaunchKernelGGL((k_eri_dense<Dm, double, P>), dim3(grid_for(L.total * P, 128)), dim3(128), 0, L.stream,
                                L.pairs, L.bra_off, L.ket_off, L.nbra, L.rowstart, L.rowmap, L.pp, bt, (int64_t)L.N, eri);
@@ -93,7 +75,7 @@ int ClassOps<MESS_CB, MESS_CK>::jk(const ClassLaunch &L, const double *D, double
     const BoysTabs bt{L.tab, L.etab, L.tabf, L.etabf, L.tabt};
     // short lists: several lanes per quartet, whatever the built-in form (a
     // form that was asked for is kept)
-    const int split = prec == MESS_FP64 && form_is_default(MESS_CB, MESS_CK, prec) ? split_lanes(L.total, L.prims) : 1;
+    const int split = prec == MESS_FP64 && form_is_default(MESS_CB, MESS_CK, prec) ? split_lanes(MESS_CB, MESS_CK, L.total, L.prims) : 1;
     if (split > 1) {
         with_split(split, [&](auto Pc) {
             constexpr int P = decltype(Pc)::value;
@@ -152,7 +134,7 @@ int ClassOps<MESS_CB, MESS_CK>::store(const ClassLaunch &L, void *base, int prec
         hipLaunchKernelGGL((k_eri_store<Dm, float>), dim3(grid_for(L.total, 128)), dim3(128), 0, L.stream, L.pairs,
                            L.bra_off, L.ket_off, L.nbra, L.rowstart, L.rowmap, L.ppf, bt, static_cast<float *>(base));
     else
-        with_split(split_lanes(L.total, L.prims), [&](auto Pc) {
+        with_split(split_lanes(MESS_CB, MESS_CK, L.total, L.prims), [&](auto Pc) {
             constexpr int P = decltype(Pc)::value;
             hipLaunchKernelGGL((k_eri_store<Dm, double, P>), dim3(grid_for(L.total * P, 128)), dim3(128), 0, L.stream,
                                L.pairs, L.bra_off, L.ket_off, L.nbra, L.rowstart, L.rowmap, L.pp, bt,

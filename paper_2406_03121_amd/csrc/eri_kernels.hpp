@@ -27,16 +27,6 @@ __device__ __forceinline__ int2 quartet_pairs(const int64_t *__restrict__ rowsta
     return make_int2(m.x, m.y + static_cast<int>(t - rowstart[r]));
 }
 
-// Lanes that share a shell quartet in the kernels with one lane per quartet
-// (FP64).  A lane's loop over the quartet's primitive quartets (up to 1296
-// of 6 x 6 x 6 x 6 primitives) is a serial chain, so a list that leaves the
-// chip's SIMDs with less than about two waves each is as slow as its longest
-// quartet: then P lanes take every P-th primitive quartet and sum the
-// contracted intermediates (log2 P exchanges each, a few hundred cycles
-// against the chain).  The sum's order depends on the list's size alone.
-// FP32 keeps one lane: its sums round where they are taken.
-constexpr int kSplits[3] = {64, 16, 4};
-
 // Q = sqrt(max_{a in sa, b in sb} |(ab|ab)|) for every pair of one class, 16
 // lanes a pair.
 template <class Dm>

@@ -234,7 +234,7 @@ int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int p
     MESS_TRY(zero_halves(B, Gj, Gk, s));
     const bool prof = prof_on();
     std::vector<const ClassList *> act = active_classes(W);
-    if (prec == MESS_FP64) MESS_TRY(short_launch(B, act, false, D, Gj, Gk, s));
+    if (prec == MESS_FP64 && !prof) MESS_TRY(short_launch(B, act, false, D, Gj, Gk, s));
     const std::vector<double> cost = class_costs(act);
     return run_forked(s, cost, [&](int i, hipStream_t st) {
         const ClassList &cl = *act[i];
@@ -344,7 +344,7 @@ int mess_eri(const mess_basis *basis, int32_t layout, int32_t prec, double schwa
     MESS_TRY(get_work_lists(B, schwarz_tol, s, &W));
     MESS_TRY(zero_async(static_cast<double *>(out), N * N * N * N, s));
     std::vector<const ClassList *> act = active_classes(W);
-    if (prec == MESS_FP64) MESS_TRY(short_launch(B, act, true, nullptr, static_cast<double *>(out), nullptr, s));
+    if (prec == MESS_FP64 && !prof_on()) MESS_TRY(short_launch(B, act, true, nullptr, static_cast<double *>(out), nullptr, s));
     const std::vector<double> cost = class_costs(act);
     return run_forked(s, cost, [&](int i, hipStream_t st) {
         ClassLaunch L;

@@ -70,7 +70,6 @@ __global__ void __launch_bounds__(128, 3) k_short(ShortArgs A, const PairInfo *_
 // all (60 functions, 3.7e6: 394 us in one launch, 386 in five).
 int short_launch(const mess_basis *B, std::vector<const ClassList *> &act, bool dense, const double *D, double *out0,
                  double *out1, hipStream_t s) {
-    if (prof_on()) return MESS_OK;
     ShortArgs A{};
     const ClassList *pick[kShort] = {};
     int P = 64, found = 0;

@@ -12,9 +12,12 @@
 //           asked for in FP32, where it is the faster one.
 // Which is fastest depends on the class (registers, primitive counts) and
 // on the workload, so the choice is a run-time table.  The built-in
-// defaults come from measurements on MI355X; mess_autotune times every
-// valid form of every class on a basis's own work lists and keeps the
-// fastest.
+// defaults come from measurements on MI355X; mess_autotune times the
+// built-in choice and every valid form of every class on a basis's own work
+// lists and keeps the fastest.  The built-in choice is more than its form:
+// FP64 lists too short to fill the chip take several lanes per quartet
+// (split_lanes), those of small s and p molecules in one launch (short.hip),
+// which a form that was asked for rules out.
 #include <algorithm>
 #include <mutex>
 #include <vector>
@@ -27,6 +30,8 @@ namespace mess {
 int get_work_lists(mess_basis *B, double tau, hipStream_t s, WorkLists **out);
 int fill_class_launch(const mess_basis *B, const ClassList &cl, hipStream_t s, ClassLaunch &L);
 int zero_async(double *p, int64_t n, hipStream_t s);
+int short_launch(const mess_basis *B, std::vector<const ClassList *> &act, bool dense, const double *D, double *out0,
+                 double *out1, hipStream_t s);  // short.hip
 
 namespace {
 std::mutex g_form_mutex;
@@ -150,48 +155,83 @@ int mess_autotune(const mess_basis *basis, int32_t prec, double schwarz_tol, con
     int rc = MESS_OK;
     if (ms)
         for (int k = 0; k < kNumClasses * kNumForms; ++k) ms[k] = -1.0;
+    // best of reps runs after a warm-up
+    auto time_of = [&](auto &&launch, double *tmin) {
+        *tmin = 1e300;
+        for (int r = 0; r <= reps; ++r) {
+            MESS_TRY(zero_async(Gj, 2 * B->packed, s));
+            if (hipEventRecord(e0, s) != hipSuccess) return (int)MESS_E_DEVICE;
+            MESS_TRY(launch());
+            float t = 0.0f;
+            if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                hipEventElapsedTime(&t, e0, e1) != hipSuccess)
+                return (int)MESS_E_DEVICE;
+            if (r > 0) *tmin = std::min(*tmin, (double)t);
+        }
+        return (int)MESS_OK;
+    };
+    int choice[kNumClasses] = {};          // kFormAuto: the built-in choice
+    double best_ms[kNumClasses] = {};
     for (const ClassList &cl : W->classes) {
         const int cls = class_index(cl.cb, cl.ck);
-        int best = kFormAuto;
-        double best_ms = 0.0;
         if (cl.total > 0) {
-            for (int form = 1; form < kNumForms && rc == MESS_OK; ++form) {
-                if (!form_valid(cl.cb, cl.ck, form, prec)) continue;
+            const int builtin = default_form(cl.cb, cl.ck, prec);
+            // where the built-in choice is its form and no more, that form is timed once
+            const bool shared = prec == MESS_FP64 && (builtin == kFormLane || builtin == kFormRows) &&
+                                split_lanes(cl.cb, cl.ck, cl.total, cl.prim_quartets) > 1;
+            for (int form = kFormAuto; form < kNumForms && rc == MESS_OK; ++form) {
+                if (!form_valid(cl.cb, cl.ck, form, prec) || (form == builtin && !shared)) continue;
                 set_form(prec, cls, form);
                 ClassLaunch L;
                 fill_class_launch(B, cl, s, L);
-                double tmin = 1e300;
-                for (int r = 0; r <= reps && rc == MESS_OK; ++r) {  // the first run is a warm-up
-                    rc = zero_async(Gj, 2 * B->packed, s);
-                    if (rc != MESS_OK) break;
-                    if (hipEventRecord(e0, s) != hipSuccess) rc = MESS_E_DEVICE;
-                    if (rc == MESS_OK)
-                        rc = dispatch_class(cl.cb, cl.ck, [&](auto CB, auto CK) {
-                            return ClassOps<decltype(CB)::value, decltype(CK)::value>::jk(
-                                L, D, Gj, Gk, form == kFormFp64 ? MESS_FP64 : prec);
+                const int cp = class_form(cl.cb, cl.ck, prec) == kFormFp64 ? MESS_FP64 : prec;
+                double t = 0.0;
+                rc = time_of(
+                    [&] {
+                        return dispatch_class(cl.cb, cl.ck, [&](auto CB, auto CK) {
+                            return ClassOps<decltype(CB)::value, decltype(CK)::value>::jk(L, D, Gj, Gk, cp);
                         });
-                    if (rc == MESS_OK && (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess))
-                        rc = MESS_E_DEVICE;
-                    float t = 0.0f;
-                    if (rc == MESS_OK && hipEventElapsedTime(&t, e0, e1) != hipSuccess) rc = MESS_E_DEVICE;
-                    if (rc == MESS_OK && r > 0) tmin = std::min(tmin, (double)t);
-                }
+                    },
+                    &t);
                 if (rc != MESS_OK) break;
-                if (ms) ms[cls * kNumForms + form] = tmin;
-                if (best == kFormAuto || tmin < best_ms) {
-                    best = form;
-                    best_ms = tmin;
+                if (ms) {
+                    ms[cls * kNumForms + form] = t;
+                    if (form == kFormAuto && !shared) ms[cls * kNumForms + builtin] = t;
+                }
+                if (form == kFormAuto || t < best_ms[cls]) {
+                    choice[cls] = form;
+                    best_ms[cls] = t;
                 }
             }
+            if (rc != MESS_OK) choice[cls] = kFormAuto;
         }
-        if (rc != MESS_OK) {
-            set_form(prec, cls, kFormAuto);
-            break;
-        }
-        // the built-in form stays the default, which short lists may leave for
-        // several lanes per quartet
-        set_form(prec, cls, best == default_form(cl.cb, cl.ck, prec) ? (int)kFormAuto : best);
-        if (forms) forms[cls] = best == kFormAuto ? class_form(cl.cb, cl.ck, prec) : best;
+        set_form(prec, cls, kFormAuto);
+        if (rc != MESS_OK) break;
+    }
+    if (rc == MESS_OK && prec == MESS_FP64) {
+        // the classes that one launch takes together stay so unless their
+        // best forms take less time one after another
+        std::vector<const ClassList *> act, rest;
+        for (const ClassList &cl : W->classes)
+            if (cl.total > 0) act.push_back(&cl);
+        double t = 0.0;
+        rc = time_of(
+            [&] {
+                rest = act;
+                return short_launch(B, rest, false, D, Gj, Gk, s);
+            },
+            &t);
+        double apart = 0.0;
+        for (const ClassList *cl : act)
+            if (std::find(rest.begin(), rest.end(), cl) == rest.end()) apart += best_ms[class_index(cl->cb, cl->ck)];
+        if (rc == MESS_OK && t <= apart)
+            for (const ClassList *cl : act)
+                if (std::find(rest.begin(), rest.end(), cl) == rest.end()) choice[class_index(cl->cb, cl->ck)] = kFormAuto;
+    }
+    for (const ClassList &cl : W->classes) {
+        const int cls = class_index(cl.cb, cl.ck);
+        set_form(prec, cls, choice[cls]);
+        if (forms) forms[cls] = class_form(cl.cb, cl.ck, prec);
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
