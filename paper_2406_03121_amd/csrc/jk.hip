@@ -73,9 +73,9 @@ int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s) {
 // costliest first, each on the stream with the least work so far.  Sets of
 // side streams are kept in a pool: at most kMaxSets, each used by one call
 // at a time while it enqueues (a later call's work queues behind, so a set is
-// free again at once); with none left, and under a caller's capture, the
-// classes run one after another on the caller's stream.  The batch's own
-// captures are lent a set until they end.
+// free again at once; a call that may not allocate makes none); with none
+// left, and under a caller's capture, the classes run one after another on
+// the caller's stream.  The batch's own captures are lent a set until they end.
 
 constexpr int kSideStreams = 3, kMaxSets = 8;
 
@@ -91,7 +91,7 @@ static int g_side_made = 0;
 
 static thread_local SideSet *t_capture_set = nullptr;  // lent to this thread's captures
 
-static SideSet *side_acquire() {
+static SideSet *side_acquire(bool create) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     std::lock_guard<std::mutex> lk(g_side_mutex);
@@ -101,7 +101,7 @@ static SideSet *side_acquire() {
             g_side_free.erase(g_side_free.begin() + i);
             return set;
         }
-    if (g_side_made >= kMaxSets) return nullptr;
+    if (!create || g_side_made >= kMaxSets) return nullptr;
     auto *set = new SideSet();
     set->device = dev;
     bool ok = hipEventCreateWithFlags(&set->fork, hipEventDisableTiming) == hipSuccess;
@@ -128,7 +128,7 @@ static void side_release(SideSet *set) {
 }
 
 ForkCapture::ForkCapture() {
-    if (!t_capture_set) t_capture_set = side_acquire();
+    if (!t_capture_set) t_capture_set = side_acquire(true);
 }
 
 ForkCapture::~ForkCapture() {
@@ -136,7 +136,8 @@ ForkCapture::~ForkCapture() {
     t_capture_set = nullptr;
 }
 
-int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work) {
+int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work,
+               bool create) {
     // few classes with little work each (s and p shells of a small molecule: up
     // to six of 15-25 us) end sooner one after another than the fork and the
     // join take (30-function J/K 109 and 151 us, its tensor 75 and 151); with
@@ -154,7 +155,7 @@ int run_forked(hipStream_t s, const std::vector<double> &cost, const std::functi
             (void)hipGetLastError();
         } else {
             lent = cap != hipStreamCaptureStatusNone;
-            set = lent ? t_capture_set : side_acquire();
+            set = lent ? t_capture_set : side_acquire(create);
         }
     }
     if (!set) {
@@ -227,8 +228,9 @@ int jk_prepare(mess_basis *B, int mode, int prec, double tau, hipStream_t s) {
 }
 
 // Gj, Gk (device, packed block-diagonal, may be NULL) <- half-matrices of J and K.
-int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau,
-                   hipStream_t s) {
+// create: class streams may be made where none are free.
+static int direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau, hipStream_t s,
+                       bool create) {
     WorkLists *W = nullptr;
     MESS_TRY(get_work_lists(B, tau, s, &W));
     MESS_TRY(zero_halves(B, Gj, Gk, s));
@@ -256,7 +258,12 @@ int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int p
         }));
         if (prof) prof_record(st, 0, false, 0, 0, 0.0);
         return (int)MESS_OK;
-    });
+    }, create);
+}
+
+int jk_direct_half(mess_basis *B, const double *D, double *Gj, double *Gk, int prec, double tau,
+                   hipStream_t s) {
+    return direct_half(B, D, Gj, Gk, prec, tau, s, true);
 }
 
 int jk_full(mess_basis *B, const double *D, double *J, double *K, int mode, int prec, double tau,
@@ -411,7 +418,7 @@ int mess_jk_noalloc(const mess_basis *basis, const double *D, double *J, double 
     hipStream_t s = static_cast<hipStream_t>(stream);
     double *Gj = J ? ws : nullptr;
     double *Gk = K ? ws + B->packed : nullptr;
-    MESS_TRY(jk_direct_half(B, D, Gj, Gk, prec, tau, s));
+    MESS_TRY(direct_half(B, D, Gj, Gk, prec, tau, s, false));
     return symmetrise_async(B, Gj, Gk, J, K, s);
 }
 

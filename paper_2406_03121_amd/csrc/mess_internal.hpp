@@ -245,9 +245,11 @@ struct ForkCapture {
 // Launches work(i, stream) for every i < cost.size() on s and side streams
 // (jk.hip), the costliest first; all of it is complete before what s runs
 // next.  One after another on s for few or short launches (all the costs, in
-// operations or bytes, below 1e9), while profiling, and under a capture that
-// has been lent no streams.
-int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work);
+// operations or bytes, below 1e9), while profiling, under a capture that has
+// been lent no streams, and where there are no side streams yet and create
+// does not allow them to be made.
+int run_forked(hipStream_t s, const std::vector<double> &cost, const std::function<int(int, hipStream_t)> &work,
+               bool create = true);
 void prof_record(hipStream_t s, int cls, bool begin, int64_t quartets, int64_t prims, double flops);
 
 struct WorkLists {

@@ -1,0 +1,62 @@
+"""Host-logic cases that test_host_logic.py runs in a process of its own, with
+fake_hip.c in place of the HIP runtime (argv: its library, the case)."""
+import ctypes
+import os
+import sys
+
+import numpy as np
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+
+from mess_inputs import generators as G  # noqa: E402
+from paper_2406_03121_amd import mess  # noqa: E402
+
+assert "torch" not in sys.modules
+CREATES = [b"hipMalloc", b"hipFree", b"hipStreamCreateWithFlags", b"hipEventCreate", b"hipEventCreateWithFlags"]
+
+
+def system():
+    """A basis with d shells (all 21 classes), and its density and outputs."""
+    B = mess.basis_from_molecule(G.water_cluster(0, n_waters=2, box=6.0))
+    D = np.eye(B.nbf)
+    return B, D, np.zeros_like(D), np.zeros_like(D)
+
+
+def p(a):
+    return None if a is None else a.ctypes.data_as(ctypes.c_void_p)
+
+
+def jk(s, stream=0):
+    B, D, J, K = s
+    rc = mess.lib().mess_jk(B.handle, p(D), p(J), p(K), 0, 0, 0.0, ctypes.c_void_p(stream))
+    assert rc == 0, mess.mess_last_error()
+
+
+def noalloc(s, stream=0):
+    B, D, J, K = s
+    rc = mess.lib().mess_jk_noalloc(B.handle, p(D), p(J), p(K), 0, 0.0, ctypes.c_void_p(stream))
+    assert rc == 0, mess.mess_last_error()
+
+
+def noalloc_creates_nothing():
+    s = system()
+    # lists and tables made by a build that forks no streams
+    mess.mess_prof_enable(True)
+    jk(s)
+    mess.mess_prof_enable(False)
+    before = [fake.fake_count(n) for n in CREATES]
+    noalloc(s)
+    assert [fake.fake_count(n) for n in CREATES] == before
+    # once another build has made them, it runs on the class streams too
+    jk(s)
+    waits = fake.fake_count(b"hipStreamWaitEvent")
+    before = [fake.fake_count(n) for n in CREATES]
+    noalloc(s)
+    assert [fake.fake_count(n) for n in CREATES] == before
+    assert fake.fake_count(b"hipStreamWaitEvent") > waits
+
+
+globals()[sys.argv[2]]()
+print("ok")
