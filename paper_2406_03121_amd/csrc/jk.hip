@@ -71,13 +71,13 @@ int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s) {
 // bound by latency.  They run on the caller's stream and kSideStreams
 // others between a fork and a join (events on the caller's stream), the
 // costliest first, each on the stream with the least work so far.  Sets of
-// side streams are kept in a pool: at most kMaxSets, each used by one call
+// side streams are kept in a pool: at most kMaxSets a device, each used by one call
 // at a time while it enqueues (a later call's work queues behind, so a set is
 // free again at once; a call that may not allocate makes none); with none
 // left, and under a caller's capture, the classes run one after another on
 // the caller's stream.  The batch's own captures are lent a set until they end.
 
-constexpr int kSideStreams = 3, kMaxSets = 8;
+constexpr int kSideStreams = 3, kMaxSets = 8, kMaxDevices = 64;
 
 struct SideSet {
     int device = -1;
@@ -87,13 +87,13 @@ struct SideSet {
 
 static std::mutex g_side_mutex;
 static std::vector<SideSet *> g_side_free;
-static int g_side_made = 0;
+static int g_side_made[kMaxDevices] = {};  // sets of each device
 
 static thread_local SideSet *t_capture_set = nullptr;  // lent to this thread's captures
 
 static SideSet *side_acquire(bool create) {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lk(g_side_mutex);
     for (size_t i = 0; i < g_side_free.size(); ++i)
         if (g_side_free[i]->device == dev) {
@@ -101,7 +101,7 @@ static SideSet *side_acquire(bool create) {
             g_side_free.erase(g_side_free.begin() + i);
             return set;
         }
-    if (!create || g_side_made >= kMaxSets) return nullptr;
+    if (!create || g_side_made[dev] >= kMaxSets) return nullptr;
     auto *set = new SideSet();
     set->device = dev;
     bool ok = hipEventCreateWithFlags(&set->fork, hipEventDisableTiming) == hipSuccess;
@@ -118,7 +118,7 @@ static SideSet *side_acquire(bool create) {
         delete set;
         return nullptr;
     }
-    ++g_side_made;
+    ++g_side_made[dev];
     return set;
 }
 
@@ -286,7 +286,6 @@ int jk_full(mess_basis *B, const double *D, double *J, double *K, int mode, int 
 constexpr int64_t kNoAllocMaxPacked = int64_t(1) << 19;
 static __device__ __align__(256) double scratch[2 * kNoAllocMaxPacked];
 
-constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mutex;
 static double *g_scratch_ptr[kMaxDevices] = {};
 

@@ -3,6 +3,7 @@ fake_hip.c in place of the HIP runtime (argv: its library, the case)."""
 import ctypes
 import os
 import sys
+import threading
 
 import numpy as np
 
@@ -15,6 +16,7 @@ from paper_2406_03121_amd import mess  # noqa: E402
 
 assert "torch" not in sys.modules
 CREATES = [b"hipMalloc", b"hipFree", b"hipStreamCreateWithFlags", b"hipEventCreate", b"hipEventCreateWithFlags"]
+STREAM = b"hipStreamCreateWithFlags"
 
 
 def system():
@@ -56,6 +58,24 @@ def noalloc_creates_nothing():
     noalloc(s)
     assert [fake.fake_count(n) for n in CREATES] == before
     assert fake.fake_count(b"hipStreamWaitEvent") > waits
+
+
+def streams_per_device():
+    n = 8
+    sets = [system() for _ in range(n)]
+    for s in sets:
+        mess.mess_work_stats(s[0], 0.0, 0)
+    fake.fake_gate(n)
+    th = [threading.Thread(target=jk, args=(s, 0x10 * (i + 1))) for i, s in enumerate(sets)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    fake.fake_gate(0)
+    assert fake.fake_count(STREAM) == 3 * n  # the first device has its eight
+    fake.fake_device(1)
+    jk(system())
+    assert fake.fake_count(STREAM) == 3 * n + 3
 
 
 globals()[sys.argv[2]]()

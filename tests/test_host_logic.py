@@ -28,3 +28,7 @@ def run(fake, case):
 
 def test_noalloc_creates_nothing(fake):
     run(fake, "noalloc_creates_nothing")
+
+
+def test_class_streams_per_device(fake):
+    run(fake, "streams_per_device")
