@@ -71,16 +71,20 @@ int zero_halves(const mess_basis *B, double *Gj, double *Gk, hipStream_t s) {
 // bound by latency.  They run on the caller's stream and kSideStreams
 // others between a fork and a join (events on the caller's stream), the
 // costliest first, each on the stream with the least work so far.  Sets of
-// side streams are kept in a pool: at most kMaxSets a device, each used by one call
-// at a time while it enqueues (a later call's work queues behind, so a set is
-// free again at once; a call that may not allocate makes none); with none
-// left, and under a caller's capture, the classes run one after another on
-// the caller's stream.  The batch's own captures are lent a set until they end.
+// side streams are kept in a pool, at most kMaxSets a device, each used by
+// one call at a time while it enqueues.  A call takes the set that its
+// stream's call before had (whose work it queues behind in any case), or a
+// new one, so that callers on different streams do not queue behind one
+// another; beyond kMaxSets callers it takes the set that was given back
+// longest ago.  With none left, and under a caller's capture, the classes run
+// one after another on the caller's stream.  The batch's own captures are
+// lent a set until they end.
 
 constexpr int kSideStreams = 3, kMaxSets = 8, kMaxDevices = 64;
 
 struct SideSet {
     int device = -1;
+    hipStream_t user = nullptr;  // stream of the last call
     hipStream_t s[kSideStreams] = {};
     hipEvent_t fork = nullptr, done[kSideStreams] = {};
 };
@@ -91,19 +95,30 @@ static int g_side_made[kMaxDevices] = {};  // sets of each device
 
 static thread_local SideSet *t_capture_set = nullptr;  // lent to this thread's captures
 
-static SideSet *side_acquire(bool create) {
+// A set for a call on s (for_capture: to be lent to a capture, which any free
+// one serves); a new one only if create.
+static SideSet *side_acquire(hipStream_t s, bool create, bool for_capture = false) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lk(g_side_mutex);
-    for (size_t i = 0; i < g_side_free.size(); ++i)
-        if (g_side_free[i]->device == dev) {
-            SideSet *set = g_side_free[i];
-            g_side_free.erase(g_side_free.begin() + i);
-            return set;
-        }
-    if (!create || g_side_made[dev] >= kMaxSets) return nullptr;
+    int pick = -1;
+    for (int i = 0; i < (int)g_side_free.size(); ++i) {
+        if (g_side_free[i]->device != dev) continue;
+        const bool own = g_side_free[i]->user == s;
+        if (pick < 0 || own) pick = i;
+        if (own) break;
+    }
+    const bool more = create && g_side_made[dev] < kMaxSets;
+    if (pick >= 0 && (for_capture || !more || g_side_free[pick]->user == s)) {
+        SideSet *set = g_side_free[pick];
+        g_side_free.erase(g_side_free.begin() + pick);
+        if (!for_capture) set->user = s;
+        return set;
+    }
+    if (!more) return nullptr;
     auto *set = new SideSet();
     set->device = dev;
+    set->user = s;
     bool ok = hipEventCreateWithFlags(&set->fork, hipEventDisableTiming) == hipSuccess;
     for (int i = 0; i < kSideStreams; ++i)
         ok = ok && hipStreamCreateWithFlags(&set->s[i], hipStreamNonBlocking) == hipSuccess &&
@@ -128,7 +143,7 @@ static void side_release(SideSet *set) {
 }
 
 ForkCapture::ForkCapture() {
-    if (!t_capture_set) t_capture_set = side_acquire(true);
+    if (!t_capture_set) t_capture_set = side_acquire(nullptr, true, true);
 }
 
 ForkCapture::~ForkCapture() {
@@ -155,7 +170,7 @@ int run_forked(hipStream_t s, const std::vector<double> &cost, const std::functi
             (void)hipGetLastError();
         } else {
             lent = cap != hipStreamCaptureStatusNone;
-            set = lent ? t_capture_set : side_acquire(create);
+            set = lent ? t_capture_set : side_acquire(s, create);
         }
     }
     if (!set) {

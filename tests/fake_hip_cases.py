@@ -60,6 +60,22 @@ def noalloc_creates_nothing():
     assert fake.fake_count(b"hipStreamWaitEvent") > waits
 
 
+def streams_per_caller():
+    s = system()
+    jk(s, 0x10)
+    assert fake.fake_count(STREAM) == 3
+    jk(s, 0x10)
+    assert fake.fake_count(STREAM) == 3      # the same caller again
+    jk(s, 0x20)
+    assert fake.fake_count(STREAM) == 6      # another caller's work queues behind neither
+    jk(s, 0x10)
+    jk(s, 0x20)
+    assert fake.fake_count(STREAM) == 6
+    for k in range(3, 40):                   # bounded
+        jk(s, 0x10 * k)
+    assert fake.fake_count(STREAM) == 24
+
+
 def streams_per_device():
     n = 8
     sets = [system() for _ in range(n)]

@@ -30,5 +30,9 @@ def test_noalloc_creates_nothing(fake):
     run(fake, "noalloc_creates_nothing")
 
 
+def test_class_streams_per_caller(fake):
+    run(fake, "streams_per_caller")
+
+
 def test_class_streams_per_device(fake):
     run(fake, "streams_per_device")
