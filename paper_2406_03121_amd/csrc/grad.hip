@@ -326,6 +326,11 @@ extern "C" int mess_hf_gradient(const mess_basis *basis, const double *D, const 
     auto *d_T = reinterpret_cast<double *>(prims + nprim), *d_W = d_T + (size_t)N * N;
     double *copies = d_W + (size_t)N * N, *d_g = copies + 3 * (size_t)nat * kGradCopies;
     int *cnt = reinterpret_cast<int *>(d_g + 3 * nat), *off = d_prim0 + 3 * nsh;
+    // however this returns, the stream is waited for first: the copy reads tab
+    struct Wait {
+        hipStream_t s;
+        ~Wait() { (void)hipStreamSynchronize(s); }
+    } wait{s};
     MESS_HIP(hipMemcpyAsync(ws, tab.data(), tab_bytes, hipMemcpyHostToDevice, s));
     MESS_TRY(zero_async(copies, 3 * (int64_t)nat * kGradCopies, s));
     hipLaunchKernelGGL(k_grad_prims, dim3((unsigned)((npair + 3) / 4)), dim3(256), 0, s, npair, B->d_pairs, d_prim0,

@@ -94,5 +94,29 @@ def streams_per_device():
     assert fake.fake_count(STREAM) == 3 * n + 3
 
 
+def gradient_waits_for_its_copy():
+    B, D, _, _ = system()
+    g = np.zeros(3 * B.n_atoms)
+    f = mess.lib().mess_hf_gradient
+
+    def run():
+        return f(B.handle, p(D), p(D), ctypes.c_double(0.0), p(g), None)
+
+    assert run() == 0, mess.mess_last_error()
+    assert fake.fake_pending_copies() == 0
+    # every launch of the call failing in turn
+    n0 = fake.fake_count(b"hipGetLastError")
+    assert run() == 0
+    checks = fake.fake_count(b"hipGetLastError") - n0
+    failed = 0
+    for k in range(1, checks + 1):
+        fake.fake_fail(b"hipGetLastError", k)
+        rc = run()
+        fake.fake_fail(None, 0)
+        failed += rc != 0
+        assert fake.fake_pending_copies() == 0, f"returned {rc} with its host table still being copied (launch {k})"
+    assert failed > 5
+
+
 globals()[sys.argv[2]]()
 print("ok")

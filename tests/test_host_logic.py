@@ -36,3 +36,7 @@ def test_class_streams_per_caller(fake):
 
 def test_class_streams_per_device(fake):
     run(fake, "streams_per_device")
+
+
+def test_gradient_waits_for_its_copy(fake):
+    run(fake, "gradient_waits_for_its_copy")
