@@ -200,6 +200,11 @@ int mess_boys(const mess_basis *basis, int32_t prec, int32_t form, int32_t m, co
  *     every element is written (screened quartets are zero).
  *     out_bytes must be >= 8 N^4.  Single molecules only.  prec MESS_FP32
  *     computes in FP32 and stores widened to FP64.
+ *     Every element has the same bits in all eight places that permutations
+ *     give it, in every call and in every replay of a captured call (a
+ *     captured call may differ from others in the last bits: others sum
+ *     short (dd|dd) lists by a workspace of up to 21 MB, which the handle
+ *     keeps and calls on different streams take in turn).
  *   layout MESS_ERI_BLOCKS: the unique shell quartets (ab|cd), pair (ab)
  *     >= pair (cd), that pass the Schwarz test, class by class in the order
  *     cls = cb (cb + 1) / 2 + ck (pair classes ss ps pp ds dp dd = 0..5);

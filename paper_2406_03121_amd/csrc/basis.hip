@@ -610,6 +610,8 @@ static void free_basis(mess_basis *B) {
     free_guess_tables(B);
     void free_grad(mess_basis *);
     free_grad(B);
+    hipFree(B->share_ws);
+    if (B->share_done) hipEventDestroy(B->share_done);
     hipFree(B->d_xyz);
     hipFree(B->d_Zd);
     hipFree(B->d_boys);

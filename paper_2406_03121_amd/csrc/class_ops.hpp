@@ -29,11 +29,17 @@ struct ClassLaunch {
     const int4 *groups = nullptr, *tiles = nullptr;
     const int *grows = nullptr;
     int ngroups = 0;
+    // dense mode: workspace for blocks that share a quartet (NULL: none do)
+    double *shares = nullptr;
 };
 
 // Direct J/K of class (cb, ck) through its cooperative tables (primitive-
 // lane, wave or table-driven kernel; coop.hip).
 int coop_jk(int cb, int ck, const ClassLaunch &L, const double *D, double *Gj, double *Gk, int prec);
+
+// Doubles of ClassLaunch::shares that the dense mode of class (cb, ck) takes
+// for a list of total quartets (0: its blocks do not share them).
+int64_t coop_share_doubles(int cb, int ck, int64_t total, int prec);
 
 // Stored-block layout (coop.hip): true when class (cb, ck) keeps its blocks
 // quartet-major for J/K streaming (element e of quartet t at t NOUT + e)

@@ -678,19 +678,68 @@ static void launch_wave(int mode, int cb, int ck, int prec, const CoopArgs &A, c
 // up to 2048 quartets, where the chip has room and the longest quartet (1296
 // primitive quartets of 6 x 6 x 6 x 6 primitives) sets the time.  The
 // primitive-lane form then has four waves take the rounds of 64 in turn; in
-// the wave form whole blocks share a quartet (J/K and the dense tensor, whose
-// outputs are sums) until about 2048 blocks, or 12 waves do.  Measured per
+// the wave form whole blocks share a quartet until about 2048 blocks (J/K,
+// whose outputs are sums, and the dense tensor, whose shares go through a
+// workspace), or 12 waves do.  Measured per
 // J/K build on water clusters, us: (dd|dd) of 3, 7 and 13 waters (21, 271,
 // 1458 quartets) 1757 -> 97, 1821 -> 325, 1949 -> 1084 (6489 quartets: 3150
 // as it is, 3860 with 12 waves a block); (dd|dp) of 3 and 7 waters 685 -> 210,
 // 702 -> 258, but of 13 (5420) 757 -> 1177; (dp|pp) of 1150 quartets 160 -> 81.
-static void quartet_waves(bool wave, int mode, int cb, int ck, int prec, int64_t total, int *nw, int *nshare) {
+static void quartet_waves(bool wave, int mode, int cb, int ck, int prec, int64_t total, bool ws, int *nw, int *nshare) {
     *nw = wave ? 4 : 1;
     *nshare = 1;
     if (prec != MESS_FP64 || total > 2048) return;
     if (!wave) *nw = 4;
-    else if (mode == kModeJK || mode == kModeDense) *nshare = (int)std::min<int64_t>(32, std::max<int64_t>(2, 2048 / total));
+    else if (mode == kModeJK || (mode == kModeDense && ws)) *nshare = (int)std::min<int64_t>(32, std::max<int64_t>(2, 2048 / total));
     else if (cb == 5 && ck == 5) *nw = 12;
+}
+
+// Doubles of workspace with which the dense mode's blocks share the quartets
+// of a list (0: they do not).
+int64_t coop_share_doubles(int cb, int ck, int64_t total, int prec) {
+    const bool wave = wave_compiled(cb, ck) && class_form(cb, ck, prec) == kFormWave;
+    int nw = 1, nshare = 1;
+    if (total > 0) quartet_waves(wave, kModeDense, cb, ck, prec, total, true, &nw, &nshare);
+    const CoopProgram *P = nshare > 1 ? coop_program(cb, ck) : nullptr;
+    return P ? total * nshare * P->nout : 0;
+}
+
+// The end of quartets that several blocks have worked at (kModeShare): a
+// block a quartet adds the shares in order and stores the sums, so that the
+// tensor has the same bits in every call and in all images of an element
+// (those that permutations of the shells' own indices give are averaged).
+// Each share adding its part to the tensor by atomics, to eight places apart,
+// took longer (tensor of 3 waters 656 us, 540 so).  Each share has done
+// its own horizontal recursion, whose rounding errors then average out: one
+// recursion of the sums left six times the error in elements that cancel.
+__global__ void __launch_bounds__(256) k_finish_shares(CoopArgs A, const PairInfo *__restrict__ pairs, int bra_off,
+                                                       int ket_off, int nbra, int same_class,
+                                                       const int64_t *__restrict__ rowstart,
+                                                       const int2 *__restrict__ rowmap, int nshare,
+                                                       const double *__restrict__ shares, int N,
+                                                       double *__restrict__ eri) {
+    extern __shared__ double sum[];
+    const int64_t q = blockIdx.x;
+    const int2 ij = quartet_pairs(rowstart, rowmap, nbra, q);
+    const PairInfo bra = pairs[bra_off + ij.x], ket = pairs[ket_off + ij.y];
+    for (int o = threadIdx.x; o < A.nout; o += 256) {
+        const double *p = shares + q * nshare * A.nout + o;
+        double v = p[0];
+        for (int k = 1; k < nshare; ++k) v += p[(int64_t)k * A.nout];
+        sum[o] = v;
+    }
+    __syncthreads();
+    const int NB = A.NB, NC = A.NC, ND = A.ND;
+    const bool sab = bra.sa == bra.sb, scd = ket.sa == ket.sb, same = same_class && ij.x == ij.y;
+    for (int o = threadIdx.x; o < A.nout; o += 256) {
+        const int d = o % ND, c = (o / ND) % NC, b = (o / (ND * NC)) % NB, a = o / (ND * NC * NB);
+        if ((sab && a < b) || (scd && c < d) || (same && a * NB + b < c * ND + d)) continue;
+        auto at = [&](int p, int r, int u, int w) { return sum[((p * NB + r) * NC + u) * ND + w]; };
+        auto bras = [&](int p, int r, int u, int w) { return sab ? 0.5 * (at(p, r, u, w) + at(r, p, u, w)) : at(p, r, u, w); };
+        auto both = [&](int p, int r, int u, int w) { return scd ? 0.5 * (bras(p, r, u, w) + bras(p, r, w, u)) : bras(p, r, u, w); };
+        const double v = same ? 0.5 * (both(a, b, c, d) + both(c, d, a, b)) : both(a, b, c, d);
+        put_images(eri, N, bra.bfa + a, bra.bfb + b, ket.bfa + c, ket.bfb + d, v);
+    }
 }
 
 static int coop_launch(int mode, int cb, int ck, const ClassLaunch &L, int64_t total, double *out0, double *out1,
@@ -712,7 +761,7 @@ static int coop_launch(int mode, int cb, int ck, const ClassLaunch &L, int64_t t
     if (g > (1 << 20)) g = 1 << 20;
     const bool wave = wave_compiled(cb, ck) && class_form(cb, ck, prec) == kFormWave;
     int nw = 1, nshare = 1;
-    quartet_waves(wave, mode, cb, ck, prec, total, &nw, &nshare);
+    quartet_waves(wave, mode, cb, ck, prec, total, L.shares != nullptr, &nw, &nshare);
     if (wave) {
         size_t lds = 0;
         launch_wave(mode, cb, ck, prec, A, L, total, (unsigned)g, nw, nshare, D, out0, out1, &lds);
@@ -720,8 +769,16 @@ static int coop_launch(int mode, int cb, int ck, const ClassLaunch &L, int64_t t
             set_error("internal: class (%d,%d) needs %zu bytes of LDS in the wave form", cb, ck, lds);
             return MESS_E_UNSUPPORTED;
         }
-        launch_wave(mode, cb, ck, prec, A, L, total, (unsigned)(g * nshare), nw, nshare, D, out0, out1, nullptr);
+        const bool finish = mode == kModeDense && nshare > 1;
+        launch_wave(finish ? (int)kModeShare : mode, cb, ck, prec, A, L, total, (unsigned)(g * nshare), nw, nshare, D,
+                    finish ? L.shares : out0, out1, nullptr);
         MESS_LAUNCH_CHECK();
+        if (finish) {
+            hipLaunchKernelGGL(k_finish_shares, dim3((unsigned)total), dim3(256), sizeof(double) * A.nout, L.stream, A,
+                               L.pairs, L.bra_off, L.ket_off, L.nbra, L.same_class, L.rowstart, L.rowmap, nshare,
+                               L.shares, L.N, out0);
+            MESS_LAUNCH_CHECK();
+        }
         return MESS_OK;
     }
     if (plane_class(cb, ck, prec)) {

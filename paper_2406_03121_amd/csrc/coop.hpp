@@ -38,7 +38,8 @@ struct CoopArgs {
     int NA, NB, NC, ND;
 };
 
-enum { kModeSchwarz = 0, kModeDense = 1, kModeJK = 2, kModeStore64 = 3, kModeStore32 = 4 };
+// kModeShare: a block's part of a quartet's elements, for k_finish_shares
+enum { kModeSchwarz = 0, kModeDense = 1, kModeJK = 2, kModeStore64 = 3, kModeStore32 = 4, kModeShare = 5 };
 
 __device__ __forceinline__ double coop_boys(int m, double T, const double *__restrict__ tab) {
     // F_m(T), m <= 8, directly (no recurrence): Taylor about the nearest grid
@@ -158,18 +159,29 @@ __device__ __forceinline__ void wave_digest(const int lane, const int nt, const 
     }
 }
 
+// An element of the dense tensor to its eight places.
+__device__ __forceinline__ void put_images(double *__restrict__ eri, const int64_t N, const int64_t a, const int64_t b,
+                                           const int64_t c, const int64_t d, const double v) {
+    auto put = [&](int64_t p, int64_t r, int64_t u, int64_t w) { eri[((p * N + r) * N + u) * N + w] = v; };
+    put(a, b, c, d);
+    put(b, a, c, d);
+    put(a, b, d, c);
+    put(b, a, d, c);
+    put(c, d, a, b);
+    put(d, c, a, b);
+    put(c, d, b, a);
+    put(d, c, b, a);
+}
+
 // Horizontal recursion of the accumulated [e0|f0] (in H[0, nacc)) and the
 // per-mode output of one quartet, shared by the nt threads of the block
-// (lane = thread index).  add: the block holds a part of the quartet's sum,
-// and dense elements are added to a cleared tensor (one that several
-// permutations reach, by as many equal parts).
+// (lane = thread index).
 template <int MODE>
 __device__ __forceinline__ void coop_finish(const CoopArgs &A, double *__restrict__ H, double *__restrict__ hc,
                                             const int lane, const int nt, const PairInfo &bra, const PairInfo &ket, const int i,
                                             const int j, const int bra_off, const int same_class,
                                             const double *__restrict__ D, const int N, double *__restrict__ out0,
-                                            double *__restrict__ out1, const int64_t q = 0, const int64_t total = 0,
-                                            const bool add = false) {
+                                            double *__restrict__ out1, const int64_t q = 0, const int64_t total = 0) {
         if (lane == 0) {
             hc[kH0] = 0.0; hc[kH1] = 1.0;
             hc[kHAB + 0] = bra.ABx; hc[kHAB + 1] = bra.ABy; hc[kHAB + 2] = bra.ABz;
@@ -203,29 +215,18 @@ __device__ __forceinline__ void coop_finish(const CoopArgs &A, double *__restric
                 if (MODE == kModeStore64) out0[(int64_t)o * total + q] = v;
                 else reinterpret_cast<float *>(out0)[(int64_t)o * total + q] = (float)v;
             }
+        } else if (MODE == kModeShare) {
+            for (int o = lane; o < A.nout; o += nt) out0[q * A.nout + o] = H[A.outslot[o]] * A.outscale[o];
         } else if (MODE == kModeDense) {
-            const int64_t NN = N;
-            double part = 1.0;
-            if (bra.sa == bra.sb) part *= 0.5;
-            if (ket.sa == ket.sb) part *= 0.5;
-            if (same_class && i == j) part *= 0.5;
+            // elements that permutations of the shells' own indices repeat are
+            // written once each, so every element has one value in every call
+            // and in all its places
+            const bool sab = bra.sa == bra.sb, scd = ket.sa == ket.sb, same = same_class && i == j;
             for (int o = lane; o < A.nout; o += nt) {
                 const int d = o % ND, cc = (o / ND) % NC, b = (o / (ND * NC)) % NB, a = o / (ND * NC * NB);
+                if ((sab && a < b) || (scd && cc < d) || (same && a * NB + b < cc * ND + d)) continue;
                 const double v = H[A.outslot[o]] * A.outscale[o];
-                const int64_t ia = bra.bfa + a, ib = bra.bfb + b, ic = ket.bfa + cc, id = ket.bfb + d;
-                auto put = [&](int64_t p, int64_t r, int64_t u, int64_t w) {
-                    double *e = out0 + ((p * NN + r) * NN + u) * NN + w;
-                    if (add) unsafeAtomicAdd(e, part * v);
-                    else *e = v;
-                };
-                put(ia, ib, ic, id);
-                put(ib, ia, ic, id);
-                put(ia, ib, id, ic);
-                put(ib, ia, id, ic);
-                put(ic, id, ia, ib);
-                put(id, ic, ia, ib);
-                put(ic, id, ib, ia);
-                put(id, ic, ib, ia);
+                put_images(out0, N, bra.bfa + a, bra.bfb + b, ket.bfa + cc, ket.bfb + d, v);
             }
         } else {
             double fac = 1.0;

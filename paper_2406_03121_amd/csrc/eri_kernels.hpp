@@ -51,11 +51,17 @@ __global__ void __launch_bounds__(64) k_schwarz(const PairInfo *__restrict__ pai
 template <class Dm, typename Real, int P>
 __device__ __forceinline__ void dense_block(const Real (&out)[Dm::NOUT], const PairInfo &bra, const PairInfo &ket, int sub,
                                             int64_t N, double *__restrict__ eri) {
+    // each element once, as in coop_finish
+    const bool sab = bra.sa == bra.sb, scd = ket.sa == ket.sb;
+    const bool same = bra.sa == ket.sa && bra.sb == ket.sb;
     static_for<0, Dm::NOUT>([&](auto I) {
         constexpr int k = decltype(I)::value;
         if (P > 1 && k % P != sub) return;
         constexpr int a = k / (Dm::NB * Dm::NCD), b = (k / Dm::NCD) % Dm::NB;
         constexpr int c = (k / Dm::ND) % Dm::NC, d = k % Dm::ND;
+        if constexpr (a < b) if (sab) return;
+        if constexpr (c < d) if (scd) return;
+        if constexpr (a * Dm::NB + b < c * Dm::ND + d) if (same) return;
         const int64_t ia = bra.bfa + a, ib = bra.bfb + b, ic = ket.bfa + c, id = ket.bfb + d;
         const double v = (double)out[k];
         eri[((ia * N + ib) * N + ic) * N + id] = v;

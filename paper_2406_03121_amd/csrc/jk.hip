@@ -294,6 +294,30 @@ int jk_full(mess_basis *B, const double *D, double *J, double *K, int mode, int 
     return symmetrise_async(B, Gj, Gk, J, K, s);
 }
 
+// Workspace of n doubles of the basis for a call on s, which waits for the
+// call before, on whatever stream that was; its user records share_done on s
+// when it has enqueued its work.  NULL under a caller's capture, whose replays
+// nothing could order, and where it cannot be had.
+static double *share_workspace(mess_basis *B, int64_t n, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    bool ok = hipStreamIsCapturing(s, &cap) == hipSuccess;
+    if (ok && cap != hipStreamCaptureStatusNone) return nullptr;
+    if (ok && !B->share_done) ok = hipEventCreateWithFlags(&B->share_done, hipEventDisableTiming) == hipSuccess;
+    if (ok && n > B->share_doubles) {
+        if (B->share_ws) (void)hipEventSynchronize(B->share_done);
+        hipFree(B->share_ws);
+        B->share_ws = nullptr;
+        B->share_doubles = 0;
+        ok = hipMalloc(&B->share_ws, sizeof(double) * n) == hipSuccess;
+        if (ok) B->share_doubles = n;
+        else B->share_ws = nullptr;
+    } else if (ok) {
+        ok = hipStreamWaitEvent(s, B->share_done, 0) == hipSuccess;
+    }
+    if (!ok) (void)hipGetLastError();
+    return ok ? B->share_ws : nullptr;
+}
+
 // Fixed device workspace of the allocation-free J/K entry point: the two
 // half matrices Gj, Gk of at most kNoAllocMaxPacked doubles each (8 MB in
 // all per device, held until the process ends).  Host code never passes the
@@ -366,14 +390,25 @@ int mess_eri(const mess_basis *basis, int32_t layout, int32_t prec, double schwa
     MESS_TRY(zero_async(static_cast<double *>(out), N * N * N * N, s));
     std::vector<const ClassList *> act = active_classes(W);
     if (prec == MESS_FP64 && !prof_on()) MESS_TRY(short_launch(B, act, true, nullptr, static_cast<double *>(out), nullptr, s));
+    // shares of quartets, a part of the workspace for each class that has them
+    std::vector<int64_t> off(act.size() + 1, 0);
+    for (size_t i = 0; i < act.size(); ++i)
+        off[i + 1] = off[i] + coop_share_doubles(act[i]->cb, act[i]->ck, act[i]->total, prec);
+    double *shares = off.back() ? share_workspace(B, off.back(), s) : nullptr;
     const std::vector<double> cost = class_costs(act);
-    return run_forked(s, cost, [&](int i, hipStream_t st) {
+    const int rc = run_forked(s, cost, [&](int i, hipStream_t st) {
         ClassLaunch L;
         fill_class_launch(B, *act[i], st, L);
+        if (shares && off[i + 1] > off[i]) L.shares = shares + off[i];
         return dispatch_class(act[i]->cb, act[i]->ck, [&](auto CB, auto CK) {
             return ClassOps<decltype(CB)::value, decltype(CK)::value>::dense(L, static_cast<double *>(out), prec);
         });
     });
+    if (shares && hipEventRecord(B->share_done, s) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipStreamSynchronize(s);
+    }
+    return rc;
 }
 
 int mess_jk(const mess_basis *basis, const double *D, double *J, double *K, int32_t mode, int32_t prec,

@@ -309,4 +309,7 @@ struct mess_basis {
     void *guess = nullptr;        // learned-guess pair tables (built on first use)
     void *grad_ws = nullptr;      // workspace of the nuclear gradient (built on first use)
     size_t grad_ws_bytes = 0;
+    double *share_ws = nullptr;   // dense tensor: shares of quartets (built on first use)
+    int64_t share_doubles = 0;
+    hipEvent_t share_done = nullptr;  // the last call that used share_ws
 };

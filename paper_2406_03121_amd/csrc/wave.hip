@@ -173,11 +173,12 @@ struct WaveLds {
     static constexpr int vrr_doubles(int nw) { return (nw * PER_WAVE * (int)sizeof(Real) + 7) / 8; }
 };
 
-// NW waves a block: 4, or for short lists of Schwarz factors and stored
-// blocks 12 (FP64 (dd|dd): their recursion levels take 151 of the 160 KB of
+// NW waves a block: 4, or for short lists of Schwarz factors, stored blocks
+// and (without a workspace) the dense tensor 12 (FP64 (dd|dd): their recursion levels take 151 of the 160 KB of
 // LDS; FP32 sums keep the order of four).  nshare: blocks that share a
 // quartet's primitive quartets, each with its own horizontal recursion and
-// output (J/K and the dense tensor, whose outputs then add up).
+// output: J/K, whose outputs then add up, and kModeShare, where share s of
+// quartet q writes its part of the block to out0[(q nshare + s) nout ..].
 constexpr bool kManyWaves = MESS_WCB == 5 && MESS_WCK == 5 && sizeof(MESS_WREAL) == 8;
 
 template <class Dm, int MODE, typename Real, int NW>
@@ -336,7 +337,8 @@ __global__ void __launch_bounds__(64 * NW) k_wave(CoopArgs A, int region, const 
             H[s] = v;
         }
         __syncthreads();
-        coop_finish<MODE>(A, H, hc, tid, nt, bra, ket, i, j, bra_off, same_class, D, N, out0, out1, q, total, nshare > 1);
+        coop_finish<MODE>(A, H, hc, tid, nt, bra, ket, i, j, bra_off, same_class, D, N, out0, out1,
+                          MODE == kModeShare ? item : q, total);
         __syncthreads();
     }
 }
@@ -362,7 +364,7 @@ void WaveOps<MESS_WCB, MESS_WCK, MESS_WREAL>::launch(int mode, const CoopArgs &A
         reinterpret_cast<const PrimPairT<R> *>(sizeof(R) == 8 ? (const void *)L.pp : (const void *)L.ppf);
 #define MESS_WAVE_GO(MODE)                                                                                         \
     do {                                                                                                           \
-        if constexpr (kManyWaves && MODE != kModeJK && MODE != kModeDense)                                         \
+        if constexpr (kManyWaves && MODE != kModeJK && MODE != kModeShare)                                         \
             if (nw == 12) {                                                                                        \
                 (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_wave<Dm, MODE, R, 12>),                \
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
@@ -380,6 +382,7 @@ void WaveOps<MESS_WCB, MESS_WCK, MESS_WREAL>::launch(int mode, const CoopArgs &A
         case kModeDense: MESS_WAVE_GO(kModeDense); break;
         case kModeStore64: MESS_WAVE_GO(kModeStore64); break;
         case kModeStore32: MESS_WAVE_GO(kModeStore32); break;
+        case kModeShare: MESS_WAVE_GO(kModeShare); break;
         default: MESS_WAVE_GO(kModeJK);
     }
 #undef MESS_WAVE_GO
