@@ -72,8 +72,7 @@ struct XcGrid {
     double *rho = nullptr;    // [G]
     double *epart = nullptr;  // [G / 16] partial sums of w_g e_x
     double *Dp = nullptr;     // D in fragment order
-    double *vpart = nullptr;  // partial sums of V_x tiles
-    size_t vpart_n = 0;       // doubles it holds
+    double *vpart[2] = {};    // partial sums of V_x tiles, LDA and PBE
     int4 *groups = nullptr;   // V_x tile groups (VGroup), LDA then PBE
     double *ex = nullptr;     // [1] E_x of the last build
     double *Vacc = nullptr;   // [nbf][nbf] accumulation of the upper block triangle
@@ -83,7 +82,7 @@ void free_xc(mess_basis *B) {
     XcGrid *X = static_cast<XcGrid *>(B->xc);
     if (!X) return;
     for (double *p : {X->xyzw, X->phiT, X->f, X->rho, X->epart, X->ex, X->Vacc, X->dphiT, X->grad, X->hv, X->Dp,
-                      X->vpart})
+                      X->vpart[0], X->vpart[1]})
         hipFree(p);
     hipFree(X->groups);
     delete X;
@@ -741,7 +740,8 @@ __global__ void k_gga_sym(int N, const double *__restrict__ Vacc, double *__rest
     }
 }
 
-int zero_async(double *p, int64_t n, hipStream_t s);
+template <bool GGA>
+static int v_prepare(XcGrid *X);
 
 // Grid and basis values, built once per basis (synchronous).
 static int get_xc(mess_basis *B, XcGrid **out) {
@@ -837,6 +837,11 @@ static int get_xc(mess_basis *B, XcGrid **out) {
         set_error("LDA grid construction failed: %s", hipGetErrorString(e));
         return MESS_E_DEVICE;
     }
+    const int rc = v_prepare<false>(X);
+    if (rc != MESS_OK) {
+        free_xc(B);
+        return rc;
+    }
     *out = X;
     return MESS_OK;
 }
@@ -845,6 +850,7 @@ static int get_xc(mess_basis *B, XcGrid **out) {
 // first PBE call (synchronous).
 static int ensure_gga(mess_basis *B, XcGrid *X) {
     if (X->dphiT) return MESS_OK;
+    MESS_TRY(v_prepare<true>(X));
     std::vector<XcShell> hs(B->nsh);
     for (int s = 0; s < B->nsh; ++s) {
         const int at = B->sh_atom[s];
@@ -948,56 +954,75 @@ static std::vector<VGroup> v_groups(int nblk, bool gga) {
     return out;
 }
 
-// Vacc <- sum over the grid (k_xc_v).
+// How the tiles of V are shared out.
 template <bool GGA>
-static int v_async(XcGrid *X, hipStream_t s) {
-    const int N = X->nbf, nblk = (N + kXT - 1) / kXT;
-    const int ntile = GGA ? nblk * nblk : nblk * (nblk + 1) / 2, ngroup = (ntile + 7) / 8;
+struct VPlan {
+    int nblk, ntile, ngroup, nw, KP;
+    int64_t chunk, nchunk;
+    explicit VPlan(const XcGrid *X) {
+        nblk = (X->nbf + kXT - 1) / kXT;
+        ntile = GGA ? nblk * nblk : nblk * (nblk + 1) / 2;
+        ngroup = (ntile + 7) / 8;
+        // chunks of points: two rounds of blocks where a block takes a CU's
+        // registers (8 waves), 2048 waves where it holds fewer
+        nw = std::min(8, (ntile + 1) / 2 * 2);
+        nchunk = std::max<int64_t>(1, nw > 4 ? 512 / ngroup : 2048 / ntile);
+        // a group reads at most 8 tiles' row blocks: all of them up to 5 blocks,
+        // at most 10 beyond (GGA: 3 left, 8 right); steps of 16 points where two
+        // buffers of their rows fit the LDS, of 8 else
+        KP = !GGA && nblk <= 5 ? 16 : 8;
+        chunk = ((X->G + nchunk - 1) / nchunk + KP - 1) / KP * KP;
+        nchunk = (X->G + chunk - 1) / chunk;
+    }
+};
+
+// The tile groups and the partial sums' place, made with the grid (PBE: with
+// the basis gradients) and kept as long: a call that was captured finds them
+// where they were.
+template <bool GGA>
+static int v_prepare(XcGrid *X) {
+    const VPlan<GGA> P(X);
+    hipError_t e = hipSuccess;
     if (!X->groups) {
-        const std::vector<VGroup> l = v_groups(nblk, false), g = v_groups(nblk, true);
+        const std::vector<VGroup> l = v_groups(P.nblk, false), g = v_groups(P.nblk, true);
         // what a group's threads load in a step (see kVLoadA) covers its rows
         bool fits = true;
-        for (const VGroup &q : l) fits &= 64 * q.na * (nblk <= 5 ? 8 : 4) <= kVLoadA<false> * 64 * std::min(8, ((int)l[0].nsup + 1) / 2 * 2);
+        for (const VGroup &q : l) fits &= 64 * q.na * (P.nblk <= 5 ? 8 : 4) <= kVLoadA<false> * 64 * std::min(8, ((int)l[0].nsup + 1) / 2 * 2);
         for (const VGroup &q : g) {
             const int thr = 64 * std::min(8, ((int)g[0].nsup + 1) / 2 * 2);
             fits &= 64 * q.na * 4 <= kVLoadA<true> * thr && 64 * q.nb * 4 <= kVLoadB * thr && q.na <= 3;
         }
         if (!fits) {
-            set_error("internal: exchange-correlation tile groups of %d row blocks", nblk);
+            set_error("internal: exchange-correlation tile groups of %d row blocks", P.nblk);
             return MESS_E_ARG;
         }
         std::vector<VGroup> all(l);
         all.insert(all.end(), g.begin(), g.end());
-        MESS_HIP(hipMalloc(&X->groups, sizeof(VGroup) * all.size()));
-        const hipError_t e = hipMemcpy(X->groups, all.data(), sizeof(VGroup) * all.size(), hipMemcpyHostToDevice);
+        e = hipMalloc(&X->groups, sizeof(VGroup) * all.size());
+        if (e == hipSuccess) e = hipMemcpy(X->groups, all.data(), sizeof(VGroup) * all.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             hipFree(X->groups);
             X->groups = nullptr;
-            set_error("exchange-correlation tile groups: %s", hipGetErrorString(e));
-            return MESS_E_DEVICE;
         }
     }
-    const VGroup *groups = reinterpret_cast<const VGroup *>(X->groups) + (GGA ? (nblk * (nblk + 1) / 2 + 7) / 8 : 0);
-    // chunks of points: two rounds of blocks where a block takes a CU's
-    // registers (8 waves), 2048 waves where it holds fewer
-    const int nw = std::min(8, (ntile + 1) / 2 * 2);
-    int64_t nchunk = std::max<int64_t>(1, nw > 4 ? 512 / ngroup : 2048 / ntile);
-    // a group reads at most 8 tiles' row blocks: all of them up to 5 blocks,
-    // at most 10 beyond (GGA: 3 left, 8 right); steps of 16 points where two
-    // buffers of their rows fit the LDS, of 8 else
-    const bool wide = !GGA && nblk <= 5;
-    const int KP = wide ? 16 : 8;
-    int64_t chunk = ((X->G + nchunk - 1) / nchunk + KP - 1) / KP * KP;
-    nchunk = (X->G + chunk - 1) / chunk;
-    const size_t need = (size_t)nchunk * ntile * kXT * kXT;
-    if (need > X->vpart_n) {
-        MESS_HIP(hipStreamSynchronize(s));
-        hipFree(X->vpart);
-        X->vpart = nullptr;
-        X->vpart_n = 0;
-        MESS_HIP(hipMalloc(&X->vpart, sizeof(double) * need));
-        X->vpart_n = need;
+    if (e == hipSuccess && !X->vpart[GGA]) {
+        e = hipMalloc(&X->vpart[GGA], sizeof(double) * P.nchunk * P.ntile * kXT * kXT);
+        if (e != hipSuccess) X->vpart[GGA] = nullptr;
     }
+    if (e != hipSuccess) {
+        set_error("exchange-correlation tiles: %s", hipGetErrorString(e));
+        return e == hipErrorOutOfMemory ? MESS_E_NOMEM : MESS_E_DEVICE;
+    }
+    return MESS_OK;
+}
+
+// Vacc <- sum over the grid (k_xc_v).
+template <bool GGA>
+static int v_async(XcGrid *X, hipStream_t s) {
+    const VPlan<GGA> P(X);
+    const int nblk = P.nblk, ntile = P.ntile, ngroup = P.ngroup, nw = P.nw, KP = P.KP, N = X->nbf;
+    const int64_t chunk = P.chunk, nchunk = P.nchunk;
+    const VGroup *groups = reinterpret_cast<const VGroup *>(X->groups) + (GGA ? (nblk * (nblk + 1) / 2 + 7) / 8 : 0);
     const int na = std::min(nblk, GGA ? 3 : 10), nb = GGA ? std::min(nblk, 8) : 0;
     const size_t lds = sizeof(double) * (2 * (size_t)64 * (na + nb) * KP + 2 * KP);
     auto go = [&](auto kernel) {
@@ -1005,15 +1030,15 @@ static int v_async(XcGrid *X, hipStream_t s) {
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) (void)hipGetLastError();
         hipLaunchKernelGGL(kernel, dim3((unsigned)nchunk, (unsigned)ngroup), dim3(64 * nw), lds, s, N, X->G, chunk, X->phiT,
-                           X->dphiT, X->f, X->hv, groups, ntile, X->vpart);
+                           X->dphiT, X->f, X->hv, groups, ntile, X->vpart[GGA]);
     };
     if constexpr (!GGA) {
-        if (wide) go(&k_xc_v<false, 16>);
+        if (KP == 16) go(&k_xc_v<false, 16>);
         else go(&k_xc_v<false, 8>);
     } else {
         go(&k_xc_v<true, 8>);
     }
-    hipLaunchKernelGGL(k_xc_v_sum<GGA>, dim3(64, (unsigned)ntile), dim3(256), 0, s, N, nblk, ntile, (int)nchunk, X->vpart,
+    hipLaunchKernelGGL(k_xc_v_sum<GGA>, dim3(64, (unsigned)ntile), dim3(256), 0, s, N, nblk, ntile, (int)nchunk, X->vpart[GGA],
                        X->Vacc);
     MESS_LAUNCH_CHECK();
     return MESS_OK;

@@ -18,6 +18,7 @@ static int counts[N_NAMES], n_names;
 static const char *fail_name;
 static int fail_at, pending_copies;
 static int gate_need, gate_seen;
+static int n_alloc, watch, freed_watched;
 static __thread int device, gate_passed;
 static intptr_t next_handle = 0x1000;
 static char symbol[2 * (1 << 19) * 8];
@@ -45,16 +46,31 @@ void fake_fail(const char *name, int after) {  /* the after-th call from now on 
     fail_at = name ? fake_count(name) + after : 0;
 }
 int fake_pending_copies(void) { return pending_copies; }
+void fake_watch(void) { watch = n_alloc; freed_watched = 0; }   /* from now on, count the frees */
+int fake_freed_watched(void) { return freed_watched; }        /* of what is allocated by now */
 void fake_device(int d) { device = d; }
 void fake_gate(int threads) { gate_need = threads; gate_seen = 0; }
 
 int hipGetDevice(int *d) { *d = device; return call("hipGetDevice"); }
+/* allocations are numbered in a header of 64 bytes */
 int hipMalloc(void **p, size_t n) {
     const int r = call("hipMalloc");
-    *p = r ? NULL : calloc(n ? n : 1, 1);
+    *p = NULL;
+    if (!r) {
+        char *q = calloc(n + 64, 1);
+        *(int *)q = __sync_add_and_fetch(&n_alloc, 1);
+        *p = q + 64;
+    }
     return r;
 }
-int hipFree(void *p) { free(p); return call("hipFree"); }
+int hipFree(void *p) {
+    if (p) {
+        char *q = (char *)p - 64;
+        if (*(int *)q <= watch) __sync_add_and_fetch(&freed_watched, 1);
+        free(q);
+    }
+    return call("hipFree");
+}
 int hipMemcpy(void *d, const void *s, size_t n, int kind) {
     (void)kind;
     memcpy(d, s, n);

@@ -118,5 +118,31 @@ def gradient_waits_for_its_copy():
     assert failed > 5
 
 
+def xc(s, pbe, V, E):
+    B, D, J, _ = s
+    v, e = p(J) if V else None, ctypes.byref(ctypes.c_double()) if E else None
+    if pbe:
+        rc = mess.lib().mess_pbe_xc(B.handle, p(D), v, e, None, None, None)
+    else:
+        rc = mess.lib().mess_lda_x(B.handle, p(D), v, e, None, None)
+    assert rc == 0, mess.mess_last_error()
+
+
+def xc_buffers_stay():
+    # what a captured call could hold is neither made by a later call of the
+    # same functional nor freed by any
+    for first in (0, 1):
+        s = system()
+        xc(s, first, False, True)
+        n = fake.fake_count(b"hipMalloc")
+        xc(s, first, True, False)
+        assert fake.fake_count(b"hipMalloc") == n
+        fake.fake_watch()
+        xc(s, 1 - first, True, True)
+        xc(s, first, True, True)
+        assert fake.fake_freed_watched() == 0
+        s[0].close()
+
+
 globals()[sys.argv[2]]()
 print("ok")

@@ -40,3 +40,7 @@ def test_class_streams_per_device(fake):
 
 def test_gradient_waits_for_its_copy(fake):
     run(fake, "gradient_waits_for_its_copy")
+
+
+def test_xc_buffers_stay(fake):
+    run(fake, "xc_buffers_stay")
