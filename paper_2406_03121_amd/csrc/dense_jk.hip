@@ -14,8 +14,8 @@
 //     block share the rows and take every eighth k; their sums meet in LDS in
 //     a fixed order.  J and K run in one launch, their blocks in turn, so that
 //     the second reader of a part of the tensor finds it in the last cache.
-//     Tensors of one to three functions, below a load's width, take the other
-//     form.
+//     Tensors narrower than a load (one function in FP64, three in FP32) take
+//     the other form.
 //   - VALU (k_dense_valu): 256-thread blocks own 64 rows x 64 densities, stage
 //     64 x 32 tensor and 32 x 64 density panels in LDS and accumulate 16
 //     densities a lane with FMAs; the column range is split over blockIdx.z
@@ -252,10 +252,11 @@ __global__ void k_dj_zero(int64_t n, Real *__restrict__ p) {
 // 64, 32 or 16 densities a wave: the fewest that hold them all, several tiles
 // of 64 beyond.  48 rows a wave with 64 densities where that leaves a block a
 // CU, since its 12 accumulators use each loaded element more often (105
-// functions, FP64: 801 us, 32 rows 901 us); 32 rows below (30 functions, 70
-// densities: 27 us, 48 rows 36 us).  Both: 105 functions 1651 -> 801 us with
-// 64 densities, 1364 -> 492 us with 16, 1297 -> 398 us with one (two reads of
-// the tensor at 4.9 TB/s); FP32 with 64 1315 -> 450 us.
+// functions, FP64, normally distributed operands: 801 us, 32 rows 901 us); 32
+// rows below (30 functions, 70 densities: 27 us, 48 rows 36 us).  Both: 105
+// functions 1651 -> 801 us with 64 densities, 1364 -> 490 us with 16, 1297 ->
+// 396 us with one (two reads of the tensor at 4.9 TB/s); FP32 with 64 1315 ->
+// 450 us.
 template <typename Real>
 static void launch_mfma(int N, int nd, const Real *eri, const Real *D, Real *J, Real *K, hipStream_t s) {
     auto tiles = [&](int rows) { return (int)(((int64_t)N * N + rows - 1) / rows) * ((J ? 1 : 0) + (K ? 1 : 0)); };

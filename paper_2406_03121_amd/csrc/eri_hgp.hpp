@@ -109,8 +109,9 @@ struct BoysTabs {
 // classes: (ss|ss) of 20 waters 2.01 ms, 1.30 with these rows in LDS, and
 // 1.14 with BARE, which also takes the conversions out of the row's number
 // and uses rsqrt_3; (ps|ss) 1.85, 1.63, 1.51; they are now bound by vector
-// instruction issue (72 % of the cycles).  Truncation below 1e-17 relative
-// (Chebyshev interpolation in each interval); exp(-T) = exp(-T_k) exp(-u/4),
+// instruction issue (61 to 71 % of the cycles).  Truncation 4e-18 relative at
+// order 0 to 4e-17 at order 8 ((2L + 1)/(2L + 19) / (2^35 9!), Chebyshev
+// interpolation in each interval); exp(-T) = exp(-T_k) exp(-u/4),
 // degree 9, constants from the same interpolation.  Largest relative errors
 // over 30000 arguments as those of the Taylor sums (2.1e-16 for F_L, 7.8e-16
 // for F_0 after eight steps down).

@@ -36,7 +36,7 @@ struct GradLists {
     const GPrim *prims;        // of pair i: prims[off[i] .. off[i] + cnt[i])
     const int *off, *cnt;
     const int *sh_atom;        // atom of every shell
-    const double *tab, *tabt, *etab;  // Boys tables of the basis
+    const double *tab, *tabt;  // Boys tables of the basis
     const double *D;
     int N, nat;
     double *copies;            // kGradCopies gradients, summed at the end

@@ -6,10 +6,13 @@
 //                 primitives), a wave per primitive quartet with its lanes
 //                 over (ab, k), tables in LDS.
 // The lane form serves a class until its unrolled steps outgrow the
-// registers by more than the cooperative form costs.  Measured on 3 waters
-// (45 functions), lane / cooperative: (dp|ps) 0.30 / 0.72 ms, (dd|ss) 0.73 /
-// 1.45, but (dp|pp) 2.16 / 0.48, (dp|ds) 1.36 / 1.07, (dd|ps) 1.78 / 1.01
-// (3 to 4 KB of spill a lane).
+// registers by more than the cooperative form costs on 3 waters (45
+// functions).  Kernel times there, lane / cooperative, ms: (pp|pp) 0.49 /
+// 0.14, (ds|ds) 0.16 / 0.78, (dp|ps) 0.31 / 0.74, (dd|ss) 0.71 / 1.42, but
+// (dp|pp) 2.17 / 0.29, (dp|ds) 1.34 / 0.93, (dd|ps) 1.75 / 0.96 (3 to 4 KB of
+// spill a lane).  The line moves with the list: on 1 water (dp|ps) 0.18 /
+// 0.10 and (dd|ss) 0.22 / 0.07; on 7 waters (dp|ds) 4.9 / 10.0 and (dd|ps)
+// 4.2 / 9.3, where a rule on the list's length would choose the lane form.
 #include <algorithm>
 
 #include "grad.hpp"
