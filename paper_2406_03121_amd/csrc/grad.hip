@@ -330,7 +330,8 @@ extern "C" int mess_hf_gradient(const mess_basis *basis, const double *D, const 
     // however this returns, the stream is waited for first: the copy reads tab
     struct Wait {
         hipStream_t s;
-        ~Wait() { (void)hipStreamSynchronize(s); }
+        bool due = true;
+        ~Wait() { if (due) (void)hipStreamSynchronize(s); }
     } wait{s};
     MESS_HIP(hipMemcpyAsync(ws, tab.data(), tab_bytes, hipMemcpyHostToDevice, s));
     MESS_TRY(zero_async(copies, 3 * (int64_t)nat * kGradCopies, s));
@@ -373,6 +374,7 @@ extern "C" int mess_hf_gradient(const mess_basis *basis, const double *D, const 
                        copies, d_g);
     MESS_LAUNCH_CHECK();
     MESS_HIP(hipMemcpyAsync(grad, d_g, sizeof(double) * 3 * nat, hipMemcpyDeviceToHost, s));
+    wait.due = false;
     MESS_HIP(hipStreamSynchronize(s));
     return MESS_OK;
 }

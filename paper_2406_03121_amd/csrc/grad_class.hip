@@ -36,9 +36,12 @@ __device__ __forceinline__ double quartet_mult(const PairInfo &bra, const PairIn
 
 constexpr double k2Pi52 = 34.986836655249725693;  // 2 pi^(5/2)
 
-// Bounded by FP64 arithmetic: about nnz(ab) (NK + 6) + NK nnz(ab) FMAs per
-// bra component after the L + 1 order R table (126 steps for (ds|ds)), with
-// the density contracted first, so no integral is formed.  The primitive
+// Bounded by FP64 arithmetic where it does not spill (vector work on 54 to 72 %
+// of the waves' cycles in (ds|ps), (pp|ps), (dp|ss)), by its scratch accesses
+// where it does (waits on 54 to 66 % in (pp|pp), (ds|pp), (dd|ss)): about
+// nnz(ab) (NK + 6) + NK nnz(ab) FMAs per bra component after the L + 1 order
+// R table (126 steps for (ds|ds)), with the density contracted first, so no
+// integral is formed.  The primitive
 // quartets of one shell quartet (the list leaves out those whose product
 // factor is below e^-70) fill the lanes; sums over lanes once per quartet.
 template <class Dm>
@@ -268,8 +271,10 @@ __constant__ CoopMap<Dm> kCoopMap = make_coop_map<Dm>();
 template <class Dm>
 inline constexpr int kGradChunk = Dm::NAB * Dm::NCD > 1000 ? 4 : 8;
 
-// Bounded by the LDS: a lane's (ab, k) entry reads three coefficients and
-// four R values for every Hermite index of ab (up to 12).  The ket's density
+// Bounded by latency: a lane's (ab, k) entry reads three coefficients and
+// four R values from LDS for every Hermite index of ab (up to 12), each chain
+// behind an index of its own; waves wait on 49 to 56 % of their cycles, issue
+// vector work on 22 to 24 % and to the LDS on 6 %.  The ket's density
 // T[ab][k] is formed once per ket primitive and shared by the block's waves,
 // which take its bra primitives in turn; V[ab][k] (the bra's potential at
 // the ket's indices) is summed over them in LDS, and gives the C - D part
