@@ -1,8 +1,8 @@
 /* A HIP runtime for host-logic tests without a GPU: device memory is host
  * memory, kernel launches do nothing, streams and events are numbers.  Every
  * call is counted by name; one call of a name can be made to fail; the order of
- * asynchronous copies and synchronisations is kept; launches can be held until
- * a number of threads has reached one.  Loaded before the library, whose
+ * asynchronous copies and synchronisations is kept; event records can be held
+ * until a number of threads has reached one.  Loaded before the library, whose
  * references to the HIP runtime then resolve to it. */
 #include <pthread.h>
 #include <stddef.h>
@@ -93,7 +93,17 @@ int hipStreamIsCapturing(void *s, int *st) { (void)s; *st = 0; return call("hipS
 int hipEventCreate(void **e) { *e = handle(); return call("hipEventCreate"); }
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; *e = handle(); return call("hipEventCreateWithFlags"); }
 int hipEventDestroy(void *e) { (void)e; return call("hipEventDestroy"); }
-int hipEventRecord(void *e, void *s) { (void)e; (void)s; return call("hipEventRecord"); }
+int hipEventRecord(void *e, void *s) {
+    (void)e; (void)s;
+    if (gate_need && !gate_passed) {  /* each thread waits once, at its first record */
+        gate_passed = 1;
+        pthread_mutex_lock(&mu);
+        if (++gate_seen == gate_need) pthread_cond_broadcast(&cv);
+        while (gate_seen < gate_need) pthread_cond_wait(&cv, &mu);
+        pthread_mutex_unlock(&mu);
+    }
+    return call("hipEventRecord");
+}
 int hipEventSynchronize(void *e) { (void)e; return call("hipEventSynchronize"); }
 int hipEventElapsedTime(float *t, void *a, void *b) { (void)a; (void)b; *t = 1.0f; return call("hipEventElapsedTime"); }
 int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return call("hipFuncSetAttribute"); }
@@ -101,14 +111,16 @@ int hipGetLastError(void) { return call("hipGetLastError"); }
 const char *hipGetErrorString(int e) { return e ? "injected" : "none"; }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; *p = symbol; return call("hipGetSymbolAddress"); }
 typedef struct { uint32_t x, y, z; } dim3_;
+static __thread struct { dim3_ g, b; size_t l; void *s; } config;
+int __hipPushCallConfiguration(dim3_ g, dim3_ b, size_t l, void *s) {
+    config.g = g; config.b = b; config.l = l; config.s = s;
+    return OK;
+}
+int __hipPopCallConfiguration(dim3_ *g, dim3_ *b, size_t *l, void **s) {
+    *g = config.g; *b = config.b; *l = config.l; *s = config.s;
+    return OK;
+}
 int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **a, size_t l, void *s) {
     (void)f; (void)g; (void)b; (void)a; (void)l; (void)s;
-    if (gate_need && !gate_passed) {  /* each thread waits once, at its first launch */
-        gate_passed = 1;
-        pthread_mutex_lock(&mu);
-        if (++gate_seen == gate_need) pthread_cond_broadcast(&cv);
-        while (gate_seen < gate_need) pthread_cond_wait(&cv, &mu);
-        pthread_mutex_unlock(&mu);
-    }
     return call("hipLaunchKernel");
 }

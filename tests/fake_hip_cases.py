@@ -144,5 +144,28 @@ def xc_buffers_stay():
         s[0].close()
 
 
+def tensor_workspace():
+    B, D, J, K = system()
+    jk((B, D, J, K))
+    out = np.zeros(B.nbf ** 4)
+
+    def eri(stream):
+        rc = mess.lib().mess_eri(B.handle, 0, 0, 0.0, p(out), out.nbytes, ctypes.c_void_p(stream))
+        assert rc == 0, mess.mess_last_error()
+        return fake.fake_count(b"hipLaunchKernel"), fake.fake_count(b"hipMalloc")
+
+    l0, _ = eri(0x10)
+    l1, m1 = eri(0x10)
+    assert eri(0x20) == (l1 + (l1 - l0), m1)  # kept, whatever the stream
+    B.close()
+    # without the workspace the tensor is built without it: one launch fewer
+    B, D, J, K = system()
+    jk((B, D, J, K))
+    k0 = fake.fake_count(b"hipLaunchKernel")
+    fake.fake_fail(b"hipMalloc", 1)
+    k1, _ = eri(0x10)
+    assert k1 - k0 == (l1 - l0) - 1
+
+
 globals()[sys.argv[2]]()
 print("ok")

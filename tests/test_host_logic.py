@@ -44,3 +44,7 @@ def test_gradient_waits_for_its_copy(fake):
 
 def test_xc_buffers_stay(fake):
     run(fake, "xc_buffers_stay")
+
+
+def test_tensor_workspace(fake):
+    run(fake, "tensor_workspace")
